@@ -16,11 +16,11 @@ Printed: one JSON line on stdout (diagnostics on stderr).
               stored oracle values (tests/golden/clumped_level.npz): the new
               spectrum and alpha, alpha' at every mode, the explicit local sum
               at 96 sampled springs and the residual of the per-step system there
-  roofline    the on-the-fly local sum (the dominant kernel), timed with HIP
-              events on the plan's stream in a second pass (while timing, the
-              library runs every stage on that stream, so the kernel is timed
-              alone); algorithmic flops per launch = ordered neighbour pairs x
-              1.6 kflop
+  roofline    the local sum by distance bins (the dominant kernel), timed with
+              HIP events on the plan's stream in a second pass (while timing,
+              the library runs every stage on that stream, so the kernel is
+              timed alone); flops per launch = springs x the table's nonzero
+              products + ordered neighbour pairs x one polynomial
   cpu_baseline  the FP64 CPU oracle on the same distribution at M = 1e4, run in
               a child process beside the GPU legs
 Secondary legs (each in its own key): the periodic multiband workload (M = 1e4)
@@ -79,7 +79,7 @@ def read_traffic(kernel):
     """HBM bytes per launch of a kernel from its committed counter summary, or
     None when it is missing or the kernel source has changed since the
     counters were taken."""
-    fn = KERNELS[kernel]["traffic"]
+    fn = KERNELS[kernel]["traffic"] if kernel in KERNELS else ""
     if not os.path.exists(fn):
         return None
     kv = {}
@@ -484,11 +484,13 @@ def batch_leg(n_inst, levels, m_max, trial_levels=3, uneven=True):
             "batched_over_plain": t_plain / t_batch}
 
 
-# Algorithmic FP64 operations of the on-the-fly local sum per ordered
-# neighbour pair: N_L = 35 quadrature nodes, each a node lag, a window weight
-# and a degree-7 interpolant of the source's history (about 46 flops), 1.6
-# kflop in all (the method's per-pair estimate).
-OTF_FLOPS_PER_PAIR = 1600.0
+# FP64 operations of the local sum by distance bins.  Per spring: the
+# coefficients of its polynomials, 8 in each of 699 bins, each a sum over the
+# lags with weight there (TABLE_LAGS of them over all bins, W = 35, p = 8).
+# Per ordered neighbour pair: a degree-7 polynomial and its addition.
+TABLE_LAGS = 17352
+BIN_FLOPS_PER_SPRING = 2.0 * 8 * TABLE_LAGS
+BIN_FLOPS_PER_PAIR = 15.0
 FP64_VECTOR_PEAK_TFLOPS = 78.6
 
 
@@ -699,16 +701,15 @@ def disordered_full(M=10_000, chunk=50_000, refines=(1, 2)):
 
 def lds_ceiling():
     """LDS read rates of this GPU from the committed probe program (built
-    beside the library): a dict with the ceiling (16-byte reads) and the rate
-    of the 8-byte pair reads the local sum issues, or None if it is missing or
-    fails."""
+    beside the library): a dict with the ceiling (16-byte reads), or None if
+    it is missing or fails."""
     probe = os.path.join(ROOT, "paper_2507_07823_amd", "lds_probe")
     if not os.path.exists(probe):
         return None
     try:
         r = subprocess.run([probe], capture_output=True, text=True, timeout=60)
         d = json.loads(r.stdout.strip().splitlines()[-1])
-        return {"ceiling": float(d["lds_read_bytes_per_s"]), "b64x2": float(d["ds_read2st64_b64_bytes_per_s"])}
+        return {"ceiling": float(d["lds_read_bytes_per_s"])}
     except (subprocess.SubprocessError, ValueError, IndexError, KeyError, OSError):
         return None
 
@@ -744,26 +745,24 @@ def headline(steps, warmup, profile_levels):
         stages = {k: {"avg_ms": v[0] / v[1], "launches": v[1]} for k, v in prof.items() if v[1]}
         ms, n = prof["local"]
         avg = ms / n
-        flops = info["n_pairs"] * OTF_FLOPS_PER_PAIR
+        flops = M * BIN_FLOPS_PER_SPRING + info["n_pairs"] * BIN_FLOPS_PER_PAIR
         achieved = flops / (avg * 1e-3) / 1e12
-        roofline = {"bound": "alu", "kernel": "wfp::k_local_otf_sym (+ k_local_otf_reduce)", "achieved": achieved,
+        roofline = {"bound": "alu", "kernel": "wfp::k_local_bins (+ k_local_bins_reduce)", "achieved": achieved,
                     "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / FP64_VECTOR_PEAK_TFLOPS,
-                    "traffic": read_traffic("wfp::k_local_otf_sym"), "avg_launch_ms": avg,
-                    "flops_per_launch": flops, "flop_count": "ordered neighbour pairs x 1.6 kflop",
+                    "traffic": read_traffic("wfp::k_local_bins"), "avg_launch_ms": avg,
+                    "flops_per_launch": flops,
+                    "flop_count": "springs x table products + ordered neighbour pairs x one polynomial",
                     "timed_with": "HIP events on the plan's stream"}
-        # the operands each lane reads from LDS per (unordered pair, node): the
-        # source and row stencils (p values each) and the window piece,
-        # against this GPU's LDS read throughput measured by the probe (its
-        # ceiling, 16-byte reads; and the rate of the 8-byte pair reads that
-        # carry the stencils)
-        lds = info["n_pairs"] / 2 * info["n_gl_local"] * (2 * info["p"] + 6) * 8.0
+        # the operands each lane reads from LDS per ordered pair: the 8
+        # coefficients of its polynomial and the two ends of its bin, against
+        # this GPU's LDS read throughput measured by the probe (16-byte reads)
+        lds = info["n_pairs"] * 10 * 8.0
         roofline["lds_operand_bytes_per_launch"] = lds
         roofline["lds_operand_GBps"] = lds / (avg * 1e-3) / 1e9
         ceiling = lds_ceiling()
         if ceiling:
             roofline["lds_ceiling_GBps"] = ceiling["ceiling"] / 1e9
             roofline["lds_frac"] = roofline["lds_operand_GBps"] / roofline["lds_ceiling_GBps"]
-            roofline["lds_read2_b64_GBps"] = ceiling["b64x2"] / 1e9
         log(f"stages: {json.dumps(stages)}")
     parity = clumped_parity(plan, p)
     log(f"parity vs oracle: {parity}")

@@ -105,10 +105,14 @@ typedef struct {
                               library's choice, which is one XCD's compute units when the local
                               sum reads at least 64 MB per level, else one stream   [0] */
   int32_t local_mode;      /* 1: local weights stored per pair (read every level); 2: evaluated on the
-                              fly every level (memory O(M), arithmetic O(pairs N_L p)); 3: stored once
+                              fly every level (memory O(M); pair by pair, arithmetic O(pairs N_L p), or,
+                              from 112 neighbours per spring on with p <= 8, by bins of the distance on
+                              each of which every Q_m is a polynomial: one small matrix product per
+                              spring and one polynomial per pair); 3: stored once
                               per unordered pair (Q_m depends on the distance alone) and applied to
                               both rows, about half the bytes of 1 (the gradient pass's
-                              derivative weights likewise); 0: 3 when half of
+                              derivative weights likewise); 0: 2 by bins from 512 neighbours per spring
+                              on (p <= 8, W + p/2 <= 46); else 3 when half of
                               the per-pair set-up fits in 60% of the free device memory and
                               either the springs have 96 or more neighbours on average or the
                               per-pair weights would not fit, else 1 when they fit, else on
@@ -241,9 +245,9 @@ wfp_status wfp_local_part(wfp_plan* plan, double* out);
  * density levels and one of checkpoint_every derivative terms; with grad_x,
  * derivative weights as large as the local weights (stored per ordered pair
  * or once per pair, as the weights are; with weights on the fly their
- * derivatives are evaluated on the fly too, each pair once, in the pass
- * that also forms the next adjoint level's local sum, and only three column
- * buffers of the size of the forward one are added).  With recorded levels
+ * derivatives are evaluated on the fly too: by bins, from a second table; else
+ * each pair once, in the pass that also forms the next adjoint level's local
+ * sum; a few buffers of the size of the forward one are added).  With recorded levels
  * (checkpoint_every < 0) the recorded blocks take the place of the replay.
  * Asynchronous on the plan's stream.
  * Errors: WFP_EINVAL, WFP_EDOMAIN (free space; grad_x with the weights on
@@ -302,7 +306,8 @@ wfp_status wfp_plan_autotune(wfp_plan* plan, int32_t trial_levels, int32_t* over
  *                     local_mode 0 here: stored for the instances with the fewest
  *                     neighbour pairs while their weights fit in 45 % of the free
  *                     device memory, once per pair where the springs have 96 or
- *                     more neighbours or only half fits, else on the fly).
+ *                     more neighbours or only half fits, else on the fly; on the
+ *                     fly by bins from 400 neighbours per spring on, p = 8 and W + p/2 <= 40).
  *                     Synchronous.
  *                     Errors: WFP_EDOMAIN (free space, or an instance whose
  *                     stages exceed the LDS), WFP_EINVAL (checkpoint_every != 0:

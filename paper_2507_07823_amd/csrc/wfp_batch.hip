@@ -21,7 +21,8 @@ struct wfp_batch {
   int2 *wl_inc = nullptr, *wl_loc4 = nullptr, *wl_loc8 = nullptr, *wl_a = nullptr, *wl_b = nullptr,
        *wl_c = nullptr, *wl_dir = nullptr, *wl_til = nullptr, *wl_rows = nullptr, *wl_otf = nullptr,
        *wl_swt = nullptr, *wl_sww = nullptr, *wl_g8 = nullptr, *wl_g4 = nullptr, *wl_rcv = nullptr,
-       *wl_otfr = nullptr, *wl_sp = nullptr, *wl_sym = nullptr, *wl_symr = nullptr;
+       *wl_otfr = nullptr, *wl_sp = nullptr, *wl_sym = nullptr, *wl_symr = nullptr, *wl_bin = nullptr, *wl_binr = nullptr;
+  int n_bin = 0, n_binr = 0;
   int n_otfr = 0, n_sp = 0, n_sym = 0, n_symr = 0;
   int n_inc = 0, n_loc4 = 0, n_loc8 = 0, n_a = 0, n_b = 0, n_c = 0, n_dir = 0, n_til = 0, n_rows = 0, n_otf = 0,
       n_swt = 0, n_sww = 0, n_g8 = 0, n_g4 = 0, n_rcv = 0;
@@ -68,6 +69,9 @@ struct wfp_batch {
 };
 
 namespace {
+
+// The batched kernel by distance bins takes up to 40 lags.
+bool batched_bins(const wfp_plan* P) { return P->use_bins && P->bins.ks == 10 && P->bins.bumps <= 2; }
 
 InstDesc describe(const wfp_plan* P) {
   InstDesc d{};
@@ -162,6 +166,7 @@ InstDesc describe(const wfp_plan* P) {
   d.otf_nw = P->otf_nw;
   d.otf_part = P->otf_part;
   d.otf_rowacc = P->otf_rowacc;
+  if (batched_bins(P)) d.bins = P->bin_args(P->bblk, P->bins.C);
   d.sym = P->sym_stored ? 1 : 0;
   d.sym_spl = P->sym_spl;
   d.sym_rb = P->sym_rb;
@@ -220,10 +225,14 @@ void build_batch(wfp_batch* B) {
   std::vector<InstDesc> desc(n);
   // otf, loc4, loc8, g8, g4: (instance, blocks); g8 / g4: instances whose
   // lag blocks are short (the plan's lanes per lag), 4 rows per block
-  std::vector<int2> inc, loc4, loc8, wa, wb, wc, dir, til, rows, otf, otfr, g8, g4, rcv, sp, sym, symr;
+  std::vector<int2> inc, loc4, loc8, wa, wb, wc, dir, til, rows, otf, otfr, g8, g4, rcv, sp, sym, symr, bin, binr;
   for (int i = 0; i < n; ++i) {
     // the spread grid of the separate spread pass
     if (!B->plans[i]->gsp) B->plans[i]->gsp = B->plans[i]->alloc<double>(B->plans[i]->nf);
+    if (B->plans[i]->use_bins && !batched_bins(B->plans[i])) {
+      B->plans[i]->otf_part = B->plans[i]->alloc<double>(B->plans[i]->otf_tot_part);
+      B->plans[i]->otf_rowacc = B->plans[i]->alloc<double>(B->plans[i]->M);
+    }
     const wfp_plan* P = B->plans[i];
     desc[i] = describe(P);
     for (int b = 0; b < (int)nblk(P->nf, 256); ++b) sp.push_back(make_int2(i, b));
@@ -235,9 +244,14 @@ void build_batch(wfp_batch* B) {
       for (int bb = 0; bb < (int)nblk(M, 64); ++bb) symr.push_back(make_int2(i, bb));
     } else if (P->otf) {
       if (P->p != 8) fail(WFP_EDOMAIN, "batched on-the-fly local sums take p = 8");
-      otf.push_back(make_int2(i, (int)nblk(M, kOtfRows)));
-      for (int bb = 0; bb < (int)nblk(M, 256); ++bb) otfr.push_back(make_int2(i, bb));
-      B->lds_otf = std::max(B->lds_otf, (size_t)(P->NQ + kOtfRows) * kOtfChunk * sizeof(double));
+      if (batched_bins(P)) {
+        bin.push_back(make_int2(i, P->bblk.nblk));
+        for (int bb = 0; bb < (int)nblk(M, 64); ++bb) binr.push_back(make_int2(i, bb));
+      } else {
+        otf.push_back(make_int2(i, (int)nblk(M, kOtfRows)));
+        for (int bb = 0; bb < (int)nblk(M, 256); ++bb) otfr.push_back(make_int2(i, bb));
+        B->lds_otf = std::max(B->lds_otf, (size_t)(P->NQ + kOtfRows) * kOtfChunk * sizeof(double));
+      }
     } else if (P->lgrp == 8) {
       g8.push_back(make_int2(i, (int)nblk(M, 4)));
     } else if (P->lgrp == 4) {
@@ -296,6 +310,8 @@ void build_batch(wfp_batch* B) {
   B->wl_rows = upload_work(B, rows, 1, B->n_rows);
   B->wl_otf = upload_work(B, xcd_balanced(otf), 8, B->n_otf);
   B->wl_otfr = upload_work(B, otfr, 1, B->n_otfr);
+  B->wl_bin = upload_work(B, xcd_balanced(bin), 8, B->n_bin);
+  B->wl_binr = upload_work(B, binr, 1, B->n_binr);
   B->wl_sym = upload_work(B, xcd_balanced(sym), 8, B->n_sym);
   B->wl_symr = upload_work(B, symr, 1, B->n_symr);
   B->wl_g8 = upload_work(B, xcd_balanced(g8), 8, B->n_g8);
@@ -310,6 +326,8 @@ void build_batch(wfp_batch* B) {
   if (B->n_otf)
     HIPCHK(hipFuncSetAttribute((const void*)kb_local_otf, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)B->lds_otf));
+  if (B->n_bin)
+    HIPCHK(hipFuncSetAttribute((const void*)kb_local_bins, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBinLds));
   B->level_d = B->alloc<int64_t>(1);
   if (B->lds_b > 160 * 1024 || B->lds_til > 160 * 1024) fail(WFP_EDOMAIN, "batched stage needs more than 160 KB of LDS");
   HIPCHK(hipFuncSetAttribute((const void*)kb_hist_b, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
@@ -363,6 +381,12 @@ void enqueue_level(wfp_batch* B) {
     hipLaunchKernelGGL(kb_local_otf, dim3(B->n_otf), dim3(64 * kOtfRows), B->lds_otf, s, bl);
     bl.work = B->wl_otfr;
     hipLaunchKernelGGL(kb_local_otf_reduce, dim3(B->n_otfr), dim3(256), 0, s, bl);
+  }
+  if (B->n_bin) {
+    bl.work = B->wl_bin;
+    hipLaunchKernelGGL(kb_local_bins, dim3(B->n_bin), dim3(kBinThreads), kBinLds, s, bl);
+    bl.work = B->wl_binr;
+    hipLaunchKernelGGL(kb_local_bins_reduce, dim3(B->n_binr), dim3(64 * kReduceWaves), 0, s, bl);
   }
   if (B->n_sym) {
     bl.work = B->wl_sym;
@@ -478,7 +502,8 @@ int64_t count_pairs(const double* x, int64_t M, double delta) {
 }
 
 // Local-weight mode of every instance whose parameters leave it to the
-// library: stored weights for the instances with the fewest pairs while their
+// library: by distance bins for springs with many neighbours; of the others,
+// stored weights for the instances with the fewest pairs while their
 // packed weights fit in 45 % of the free device memory (and the set-up array
 // of one instance in 25 %), on the fly for the rest.
 std::vector<int> choose_local_modes(int n, const wfp_problem* probs, const wfp_params* pars) {
@@ -499,6 +524,11 @@ std::vector<int> choose_local_modes(int n, const wfp_problem* probs, const wfp_p
     packed[i] = 8.0 * pairs * (W / 2 + p);        // nonzero lags per pair
     dense[i] = 8.0 * pairs * (W + p / 2);
     many[i] = pairs >= kPairOnceNeighbours * (double)probs[i].M ? 1 : 0;
+    // by distance bins (the batched kernel takes p = 8 and up to 40 lags)
+    if (p == 8 && W + p / 2 <= 40 && pairs >= kBatchBinsOverPairs * (double)probs[i].M) {
+      mode[i] = 2;
+      continue;
+    }
     cand.push_back({packed[i], i});
   }
   std::sort(cand.begin(), cand.end());

@@ -224,4 +224,26 @@ std::vector<double> window_pieces(const WindowSeries& ws, int pieces, int deg) {
   return out;
 }
 
+std::vector<double> bin_edges(int W, int p, const std::vector<double>& z, double hmax) {
+  std::vector<double> e{0.0, 1.0, (double)W};
+  for (double zi : z) {
+    const double a = 0.5 * (1.0 + zi);
+    for (int n = p / 2; n < W; ++n) {
+      const double D = W - (W - n) / a;
+      if (!(D > 0.0 && D < (double)W)) continue;
+      // below the lowest allowed start the stencil does not move yet
+      if (n - p / 2 + 1 > (D < 1.0 ? 0 : 1)) e.push_back(D);
+    }
+  }
+  std::sort(e.begin(), e.end());
+  e.erase(std::unique(e.begin(), e.end()), e.end());
+  std::vector<double> out{0.0};
+  for (size_t i = 1; i < e.size(); ++i) {
+    const int n = std::max(1, (int)std::ceil((e[i] - e[i - 1]) / hmax));
+    for (int k = 1; k < n; ++k) out.push_back(e[i - 1] + (e[i] - e[i - 1]) * k / n);
+    out.push_back(e[i]);
+  }
+  return out;
+}
+
 }  // namespace wfp

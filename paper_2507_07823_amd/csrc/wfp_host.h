@@ -65,6 +65,12 @@ void source_range(const std::vector<double>& xs, double x, double r, bool period
 bool upper_ranges(const std::vector<int>& nbs, const std::vector<int>& nbc, int rows, std::vector<int>& up,
                   std::vector<int>& blk_end, std::vector<int64_t>& part_off, int64_t& total);
 
+// Distance bins of the local weights, in units of dt: 0, 1 (the nearby class),
+// W, and every distance W - (W - n) / a at which a quadrature node of fraction
+// a = (1 + z) / 2 crosses the lag n and its stencil moves; wider gaps are cut
+// evenly to hmax.  Between consecutive edges every Q_m is smooth.
+std::vector<double> bin_edges(int W, int p, const std::vector<double>& z, double hmax);
+
 // 2^a 5^b test and the radix sequence (4s, at most one 2, then 5s) used by
 // the LDS FFT.
 bool is_pow2_pow5(int64_t n);

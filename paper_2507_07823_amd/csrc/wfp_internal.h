@@ -32,6 +32,23 @@ extern thread_local std::string g_last_error;
 // 35 % at 1373)
 constexpr double kPairOnceNeighbours = 96.0;
 
+// mean neighbours per spring from which weights on the fly are summed by
+// distance bins (measured on one MI355X, local sum in us by bins against pair
+// by pair: 85 / 74 at 97, M = 7e3; 999 / 733 at 101, M = 1e5, p = 6; 236 / 248
+// at 116, M = 2e4; 156 / 181 at 138, M = 1e4; 1047 / 3494 at 578, M = 1e5)
+constexpr double kBinNeighbours = 112.0;
+
+// and from which local_mode 0 prefers them to weights stored once per pair
+// (the same at 289, M = 5e4: 549 / 449; at 413, M = 3e4: 328 / 347; at 578,
+// M = 1e5: 1047 / 1563; at 687, M = 5e4: 581 / 900; stored weights overlap the
+// history chain, these do not)
+constexpr double kBinsOverPairs = 512.0;
+// and from which batch instances do (their launches fill the chip together)
+constexpr double kBatchBinsOverPairs = 400.0;
+// most lags of the on-the-fly position gradient: local_mode 0 leaves longer
+// windows to stored weights
+constexpr int kMaxOtfGradLags = 46;
+
 struct Error {
   wfp_status code;
   std::string msg;
@@ -224,6 +241,31 @@ struct wfp_plan {
   double *symd_q = nullptr, *symd_row1 = nullptr, *symd_row2 = nullptr, *symd_col1 = nullptr,
          *symd_col2 = nullptr, *symd_one = nullptr;
   double *otf_na = nullptr, *otf_nw = nullptr;
+  // local sum by distance bins (on the fly, many neighbours): the bins, padded
+  // to whole chunks, their lookup cells, the table of the weights and, for the
+  // gradient, of their derivatives
+  struct Bins {
+    int nbins = 0, nch = 0, ks = 0, bumps = 0;
+    double *D = nullptr, *edge = nullptr, *scales = nullptr, *C = nullptr, *Cd = nullptr;
+    unsigned* cells = nullptr;
+    int4* chunk = nullptr;
+  };
+  // its blocks of consecutive sources: the target windows, their sums, and the
+  // blocks that hold each row (the derivative sums take blocks of their own)
+  struct BinBlocks {
+    int nblk = 0;
+    int64_t total = 0;
+    int4* win = nullptr;
+    int2 *span = nullptr, *cov = nullptr;
+    int64_t* off = nullptr;
+    double *part = nullptr, *part2 = nullptr;
+  };
+  bool use_bins = false;
+  Bins bins;
+  BinBlocks bblk, bblkd;
+  BinArgs bin_args(const BinBlocks& K, const double* C) const {
+    return {bins.nch, K.nblk, C, bins.edge, bins.scales, bins.cells, bins.chunk, K.win, K.span, K.cov, K.off, K.part, K.part2};
+  }
   int otf_nblk = 0;
   // stored weights: the lags >= 2 part of the local sum of level L, in
   // locb[L & 1] (its lag-1 part is added after sigma^{L-1} is solved)

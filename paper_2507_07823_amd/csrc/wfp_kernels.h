@@ -58,6 +58,40 @@ constexpr int kPhiPieces = 512, kPhiDeg = 5;
 constexpr int kOtfRows = 16, kOtfChunk = 256;
 // wavefronts of a pair-once reduce workgroup (64 rows, one per lane)
 constexpr int kReduceWaves = 16;
+// Local sum by distance bins (wfp_bins.hip): columns (sources, or sources x
+// histories) per workgroup, bins per LDS chunk, targets side by side in a
+// wavefront, threads, lookup cells per chunk, the most lags (13 steps of 4) and
+// bins, steps between the K0
+constexpr int kBinColumns = 32, kBinChunk = 64, kBinTargets = 16, kBinThreads = 1024, kBinCells = 4096;
+constexpr int kMaxBinLags = 52, kMaxBins = 768, kBinSkip = 2;
+// LDS records of a column: a bin each, zero records on both sides; spaced so
+// that the columns a wavefront reads at once fall on different banks
+constexpr int kBinRecords = kBinChunk + 4;
+constexpr size_t kBinLds = (size_t)kBinColumns * kBinRecords * 8 * sizeof(double);
+template <int P>
+__global__ void k_bin_table(int nbins, int W, int NQ, int ks, int ngl, double dt, const double* __restrict__ D,
+                            const double* __restrict__ glz, const double* __restrict__ glw,
+                            const double* __restrict__ cheb_phi, const double* __restrict__ cheb_g, int ncheb,
+                            const double* __restrict__ lagw, int deriv, double* __restrict__ C);
+__global__ void k_bin_windows(int M, int nsrc, int nblk, int nch, int periodic, double tol,
+                              const double* __restrict__ xs, const double* __restrict__ edge,
+                              int4* __restrict__ win);
+// What the sums by bins read: the table, the bins' edges and lookup cells, and
+// the blocks of consecutive sources with their target windows and sums.
+struct BinArgs {
+  int nch, nblk;
+  const double *C, *edge, *scales;
+  const unsigned* cells;
+  const int4 *chunk, *win;
+  const int2 *span, *cov;
+  const int64_t* off;
+  double *part, *part2;
+};
+template <int KS, int BUMPS, int H>
+__global__ void k_local_bins(int M, int NH, int NQ, int64_t L, BinArgs A, const double* __restrict__ xs,
+                             const double* __restrict__ hist, const double* __restrict__ lin, int64_t r1);
+__global__ void k_local_bins_reduce(int M, BinArgs A, const double* __restrict__ part,
+                                    const double* __restrict__ scale, double* __restrict__ out);
 // sources per LDS chunk of the on-the-fly derivative local sums
 constexpr int kOtfDerivChunk = 112;
 constexpr int kMaxOtfLags = 48;      // lags 1 .. NQ - 1 of a row staged by the symmetric local sum
@@ -319,6 +353,7 @@ struct InstDesc {
   int otf_nblk;
   const double *otf_na, *otf_nw;
   double *otf_part, *otf_rowacc;
+  BinArgs bins;                // by distance bins instead (bins.nblk > 0)
   // weights stored once per unordered pair (otf_up_end, otf_rowacc shared)
   int sym, sym_spl;
   const int64_t* sym_rb;
@@ -348,6 +383,8 @@ __global__ void kb_local_g8(BatchLaunch b);
 __global__ void kb_local_g4(BatchLaunch b);
 __global__ void kb_local_otf(BatchLaunch b);
 __global__ void kb_local_otf_reduce(BatchLaunch b);
+__global__ void kb_local_bins(BatchLaunch bl);
+__global__ void kb_local_bins_reduce(BatchLaunch bl);
 __global__ void kb_local_sym(BatchLaunch b);
 __global__ void kb_local_sym_reduce(BatchLaunch b);
 __global__ void kb_spread_grid(BatchLaunch b);

@@ -7,15 +7,12 @@
 //         (circularly): Q[qoff[j] + m*n_j + i], m = 0..NQ-1, i = 0..n_j-1,
 //         holding (beta_j/2) Q_m(d) (scatterer rows) or (1/2) Q_m(d) (receivers).
 //   grid  fine grid of n_f points x_i = -pi + i h_f (NUFFT, periodic)
+#include "wfp_device.h"
 #include "wfp_kernels.h"
 
 namespace wfp {
 
 namespace {
-
-constexpr double kPi = 3.14159265358979323846;
-constexpr double kTwoPi = 6.28318530717958647692;
-constexpr double kInvTwoPi = 0.15915494309189533577;
 
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
@@ -29,27 +26,10 @@ __device__ __forceinline__ double2 cmul_mi(double2 a) { return make_double2(a.y,
 // multiply by +i
 __device__ __forceinline__ double2 cmul_pi(double2 a) { return make_double2(-a.y, a.x); }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 // exponential-of-semicircle spreading kernel psi(z) = exp(beta (sqrt(1 - z^2) - 1)), |z| < 1
 __device__ __forceinline__ double es_kernel(double z, double beta) {
   const double r = 1.0 - z * z;
   return r > 0.0 ? exp(beta * (sqrt(r) - 1.0)) : 0.0;
-}
-
-// Chebyshev series a_0/2 + sum a_k T_k(s) by Clenshaw
-__device__ __forceinline__ double cheb(const double* __restrict__ a, int n, double s) {
-  double b1 = 0.0, b2 = 0.0;
-  for (int k = n - 1; k >= 1; --k) {
-    const double b0 = fma(2.0 * s, b1, a[k] - b2);
-    b2 = b1;
-    b1 = b0;
-  }
-  return fma(s, b1, 0.5 * a[0] - b2);
 }
 
 // Storage position of Fourier mode q in every per-mode array (tables, spectra
@@ -61,11 +41,6 @@ __device__ __forceinline__ int64_t mode_pos(int64_t q, int n1, int n2) {
   const int b = (k2 == 0) ? 0 : min(k2, n2 - k2);
   const int c = (k2 == b) ? 0 : 1;
   return (int64_t)b * 2 * n1 + c * n1 + k1;
-}
-
-__device__ __forceinline__ int mod_slot(int64_t n, int N) {
-  int s = (int)(n % N);
-  return s < 0 ? s + N : s;
 }
 
 // ---------------------------------------------------------------------------
@@ -506,14 +481,6 @@ __global__ void k_count_nonzero(int M, int NQ, const int* __restrict__ nb_count,
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
   if (lane == 0) atomicAdd(out, c);
-}
-
-// XCD-aware block order: consecutive hardware block ids go round-robin over
-// the 8 XCDs; give each XCD a contiguous range of logical blocks so rows that
-// share density history share an L2.  A bijection when nblocks % 8 == 0.
-__device__ __forceinline__ int xcd_block(int b, int nblocks) {
-  const int per = (nblocks + 7) >> 3;
-  return (b & 7) * per + (b >> 3);
 }
 
 // Local sum of lags m0 <= m < m1 (m0 = 1 or 2 for the right-hand side, 0 for

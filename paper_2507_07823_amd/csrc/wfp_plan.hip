@@ -270,6 +270,184 @@ void set_overlap(wfp_plan* P, int cus) {
   P->overlap_cus = cus;
 }
 
+// Table of the bins' polynomials: the weights (deriv = 0) or half their
+// distance derivatives, and a spare chunk that the kernel loads ahead.
+double* bin_table(wfp_plan* P, int deriv) {
+  const wfp_plan::Bins& B = P->bins;
+  hipStream_t s = P->stream;
+  const size_t nc = (size_t)((B.nch + 1) * kBinChunk / 2) * B.ks * 64;
+  double* C = P->alloc<double>(nc);
+  hipLaunchKernelGGL(k_fill, dim3(nblk(nc, 256)), dim3(256), 0, s, C, (int64_t)nc, 0.0);
+#define WFP_BT(PP)                                                                                                \
+  hipLaunchKernelGGL(k_bin_table<PP>, dim3(B.nbins), dim3(64), 0, s, B.nbins, P->W, P->NQ, B.ks, P->ngl, P->dt,  \
+                     B.D, P->glz_d, P->glw_d, P->cheb_phi, P->cheb_g, P->ncheb, P->lagw_d, deriv, C)
+  switch (P->p) {
+    case 2: WFP_BT(2); break;
+    case 4: WFP_BT(4); break;
+    case 6: WFP_BT(6); break;
+    default: WFP_BT(8); break;
+  }
+#undef WFP_BT
+  HIPCHK(hipGetLastError());
+  return C;
+}
+
+// Blocks of nsrc consecutive sources: their target windows per chunk of bins,
+// the place of their sums, and the blocks that hold each range of 64 rows.
+void bin_blocks(wfp_plan* P, int nsrc, wfp_plan::BinBlocks& K) {
+  const wfp_plan::Bins& B = P->bins;
+  hipStream_t s = P->stream;
+  const int64_t M = P->M;
+  K.nblk = (int)nblk(M, nsrc);
+  K.win = P->alloc<int4>((size_t)K.nblk * B.nch);
+  hipLaunchKernelGGL(k_bin_windows, dim3(nblk((int64_t)K.nblk * B.nch, 256)), dim3(256), 0, s, (int)M, nsrc, K.nblk,
+                     B.nch, P->boundary == WFP_PERIODIC ? 1 : 0, 1e-9 * P->dt, P->xs, B.edge, K.win);
+  HIPCHK(hipGetLastError());
+  std::vector<int4> last(K.nblk);
+  HIPCHK(hipMemcpy2DAsync(last.data(), sizeof(int4), K.win + (B.nch - 1), B.nch * sizeof(int4), sizeof(int4), K.nblk,
+                          hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  std::vector<int2> span(K.nblk);
+  std::vector<int64_t> off(K.nblk);
+  K.total = 0;
+  for (int b = 0; b < K.nblk; ++b) {
+    span[b] = make_int2(last[b].x, last[b].w);
+    off[b] = K.total;
+    K.total += span[b].y - span[b].x;
+  }
+  // blocks that may hold rows 64 w .. 64 w + 63 at each image (l - M, l, l + M)
+  const int ng = (int)nblk(M, 64);
+  std::vector<int2> cov(3 * (size_t)ng);
+  for (int im = 0; im < 3; ++im) {
+    int a = 0, e = 0;
+    for (int w = 0; w < ng; ++w) {
+      const int64_t u0 = 64 * (int64_t)w + (im - 1) * M, u1 = std::min<int64_t>(64 * (int64_t)w + 63, M - 1) + (im - 1) * M;
+      while (a < K.nblk && span[a].y <= u0) ++a;
+      while (e < K.nblk && span[e].x <= u1) ++e;
+      cov[3 * (size_t)w + im] = make_int2(a, std::max(a, e));
+    }
+  }
+  K.span = P->alloc<int2>(K.nblk);
+  K.off = P->alloc<int64_t>(K.nblk);
+  K.cov = P->alloc<int2>(cov.size());
+  upload(K.span, span, s);
+  upload(K.off, off, s);
+  upload(K.cov, cov, s);
+  HIPCHK(hipStreamSynchronize(s));
+}
+
+// The bins of a window and a quadrature rule, on the host: edges (units of dt
+// and distances, padded to whole chunks), lookup cells and chunks.
+struct BinLayout {
+  int nbins = 0, nch = 0, ks = 0, bumps = 0;
+  std::vector<double> D, edge, scales;
+  std::vector<int4> chunk;
+  std::vector<unsigned char> cells;
+};
+
+// False where they do not fit the kernel's limits.
+bool bin_layout(const wfp_plan* P, const std::vector<double>& glz, BinLayout& B) {
+  if (P->p > 8 || P->NQ > kMaxBinLags) return false;
+  // bin width: 0.1 dt leaves the degree-7 polynomials of the default window
+  // (b / W = 0.79) and p <= 8 within 1.4e-16 of the weights (p = 10 and 12 need
+  // more terms); a steeper window takes narrower bins
+  const double hmax = 0.1 * std::min(1.0, P->W / P->b * (27.631 / 35.0));
+  B.D = bin_edges(P->W, P->p, glz, hmax);
+  std::vector<double>&D = B.D, &edge = B.edge, &scales = B.scales;
+  std::vector<int4>& chunk = B.chunk;
+  std::vector<unsigned char>& cells = B.cells;
+  B.nbins = (int)D.size() - 1;
+  B.nch = (int)nblk(B.nbins, kBinChunk);
+  const int npad = B.nch * kBinChunk;
+  if (npad > kMaxBins) return false;
+  D.resize(npad + 1, D.back());
+  edge.assign(npad + 1, P->delta);
+  for (int i = 0; i < B.nbins; ++i) edge[i] = D[i] * P->dt;
+  // lookup cells of a chunk: as narrow as its narrowest bin (then a cell holds
+  // one edge at most) while they fit in kBinCells; at each cell's start the
+  // record (0 below the chunk, then one per bin), four to a word
+  scales.resize(B.nch);
+  chunk.resize(B.nch);
+  for (int c = 0; c < B.nch; ++c) {
+    const double* e = &edge[c * kBinChunk];
+    const int n = std::min(kBinChunk, B.nbins - c * kBinChunk);   // padding bins are empty
+    double narrow = P->delta;
+    for (int i = 0; i < n; ++i) narrow = std::min(narrow, e[i + 1] - e[i]);
+    const double sc = scales[c] = std::min(1.01 / narrow, (kBinCells - 8) / (e[n] - e[0]));
+    auto record = [&](double v) {
+      const int r = (int)(std::upper_bound(e, e + n + 1, v) - e);
+      return r > n ? kBinChunk + 1 : r;
+    };
+    const int c0 = (int)std::floor(e[0] * sc) - 1, c1 = (int)std::floor(e[n] * sc) + 1;
+    chunk[c] = make_int4(c0, c1 - c0 + 1, (int)(cells.size() / 4), 0);
+    if (c1 - c0 + 1 > kBinCells) return false;
+    for (int i = c0; i <= c1; ++i) {
+      const int r0 = record(i / sc - 1e-12 * P->delta), r1 = record((i + 1) / sc + 1e-12 * P->delta);
+      cells.push_back((unsigned char)r0);
+      B.bumps = std::max(B.bumps, std::min(r1, n + 1) - r0);
+    }
+    while (cells.size() % 4) cells.push_back((unsigned char)(kBinChunk + 1));
+  }
+  B.ks = (int)nblk(P->NQ, 4) <= 10 && B.bumps <= 2 ? 10 : 13;
+  if (B.bumps > 4) return false;
+  // first lag with weight in each half of a chunk (the lowest node's stencil
+  // at its lower edge), as steps of four lags
+  const double amax = 0.5 * (1.0 + *std::max_element(glz.begin(), glz.end()));
+  auto step0 = [&](int bin) {
+    const double d = D[bin];
+    return std::max(0, (int)std::floor(P->W - (P->W - d) * amax - 1e-6) - P->p / 2 + 1) / 4;
+  };
+  for (int c = 0; c < B.nch; ++c) chunk[c].w = step0(c * kBinChunk) | step0(c * kBinChunk + kBinChunk / 2) << 16;
+  return true;
+}
+
+// The bins, the table and the blocks of the local sum on the device.
+void build_bins(wfp_plan* P, const BinLayout& H) {
+  wfp_plan::Bins& B = P->bins;
+  hipStream_t s = P->stream;
+  B.nbins = H.nbins;
+  B.nch = H.nch;
+  B.ks = H.ks;
+  B.bumps = H.bumps;
+  B.D = P->alloc<double>(H.D.size());
+  B.edge = P->alloc<double>(H.edge.size());
+  B.cells = P->alloc<unsigned>(H.cells.size() / 4);
+  B.chunk = P->alloc<int4>(B.nch);
+  B.scales = P->alloc<double>(B.nch);
+  upload(B.D, H.D, s);
+  upload(B.edge, H.edge, s);
+  HIPCHK(hipMemcpyAsync(B.cells, H.cells.data(), H.cells.size(), hipMemcpyHostToDevice, s));
+  upload(B.chunk, H.chunk, s);
+  upload(B.scales, H.scales, s);
+  B.C = bin_table(P, 0);
+  HIPCHK(hipStreamSynchronize(s));
+  bin_blocks(P, kBinColumns, P->bblk);
+  P->bblk.part = P->alloc<double>(P->bblk.total);
+  const void* fns[6] = {(const void*)k_local_bins<10, 1, 1>, (const void*)k_local_bins<10, 2, 1>,
+                        (const void*)k_local_bins<13, 4, 1>, (const void*)k_local_bins<10, 1, 2>,
+                        (const void*)k_local_bins<10, 2, 2>, (const void*)k_local_bins<13, 4, 2>};
+  for (const void* f : fns) HIPCHK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBinLds));
+  P->use_bins = true;
+}
+
+// Local sum by distance bins, scaled per row, or (fwd) both derivative sums of
+// a gradient level: forward densities from rows r1 - m of fwd into out,
+// adjoint ones from the ring into out2, scaled by ones.
+void launch_bins(wfp_plan* P, hipStream_t s, const double* hist, int64_t L, const double* scale, double* out,
+                 hipEvent_t ea = nullptr, hipEvent_t eb = nullptr, const double* fwd = nullptr, int64_t r1 = 0,
+                 double* out2 = nullptr) {
+  const wfp_plan::Bins& B = P->bins;
+  const wfp_plan::BinBlocks& K = fwd ? P->bblkd : P->bblk;
+  auto k1 = B.ks == 13 ? k_local_bins<13, 4, 1> : (B.bumps > 1 ? k_local_bins<10, 2, 1> : k_local_bins<10, 1, 1>);
+  auto k2 = B.ks == 13 ? k_local_bins<13, 4, 2> : (B.bumps > 1 ? k_local_bins<10, 2, 2> : k_local_bins<10, 1, 2>);
+  const BinArgs A = P->bin_args(K, fwd ? B.Cd : B.C);
+  const dim3 rows(nblk(P->M, 64)), threads(64 * kReduceWaves);
+  hipExtLaunchKernelGGL(fwd ? k2 : k1, dim3(8 * nblk(K.nblk, 8)), dim3(kBinThreads), kBinLds, s, ea, nullptr, 0,
+                        (int)P->M, P->NH, P->NQ, L, A, P->xs, hist, fwd, r1);
+  hipExtLaunchKernelGGL(k_local_bins_reduce, rows, threads, 0, s, nullptr, eb, 0, (int)P->M, A, K.part, scale, out);
+  if (fwd) hipLaunchKernelGGL(k_local_bins_reduce, rows, threads, 0, s, (int)P->M, A, K.part2, scale, out2);
+}
+
 void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
   validate(prob, par);
   const int64_t M = prob->M;
@@ -556,24 +734,30 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
     P->n_pairs += nbc[j];
   }
   // stored weights (dense per pair during set-up, then packed) or on the fly
+  BinLayout bins;
+  bool by_bins = false;
   {
     int mode = par->local_mode;
+    if ((mode == 0 || mode == 2) && (double)P->n_pairs >= kBinNeighbours * (double)M) by_bins = bin_layout(P, glz, bins);
     if (mode == 0) {
       // once per unordered pair (about half the set-up array and packed
       // weights) when that fits and either the springs have enough neighbours
       // (there the halved stream outweighs the prefix runs' idle lanes: it
       // measured faster from about 100 neighbours per spring on) or the
       // per-pair weights would not fit; else per ordered pair when they fit;
-      // else on the fly
+      // else on the fly.  With many more neighbours on the fly by distance bins,
+      // whose cost grows with the springs rather than with the pairs
       size_t fr = 0, to = 0;
       HIPCHK(hipMemGetInfo(&fr, &to));
       const double need = 8.0 * (double)tot * 1.7;
       const bool fits1 = need < 0.6 * (double)fr, fits3 = 0.5 * need < 0.6 * (double)fr;
       const bool dense = (double)P->n_pairs >= kPairOnceNeighbours * (double)M;
-      if (fits3 && (dense || !fits1)) mode = 3;
+      if (by_bins && P->NQ <= kMaxOtfGradLags && (double)P->n_pairs >= kBinsOverPairs * (double)M) mode = 2;
+      else if (fits3 && (dense || !fits1)) mode = 3;
       else if (fits1) mode = 1;
       else mode = 2;
     }
+    by_bins = by_bins && mode == 2;
     P->otf = mode == 2 || mode == 3;
     P->sym_stored = mode == 3;
   }
@@ -672,9 +856,9 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
       P->otf_up_end = P->alloc<int>(M);
       P->otf_blk_end = P->alloc<int>(nb);
       P->otf_part_off = P->alloc<int64_t>(nb);
-      P->otf_part = P->alloc<double>(tot_part);
+      if (!by_bins) P->otf_part = P->alloc<double>(tot_part);
       P->otf_tot_part = tot_part;
-      P->otf_rowacc = P->alloc<double>(M);
+      if (!by_bins) P->otf_rowacc = P->alloc<double>(M);
       upload(P->otf_up_end, up, s);
       upload(P->otf_blk_end, be, s);
       upload(P->otf_part_off, po, s);
@@ -785,6 +969,7 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
     upload(P->otf_nw, nhw, s);
     upload(P->phitab, tab, s);
     P->half_beta = hb_d;
+    if (by_bins) build_bins(P, bins);
   } else {
     launch_qw((int)M, P->xs, P->nb_start, P->nb_count, P->qoff, hb_d, pbase, mlo, P->Q);
   }
@@ -1276,6 +1461,10 @@ void launch_local_otf(wfp_plan* P, hipStream_t s, const double* hist, int64_t L,
                           P->sym_upb, P->otf_rowacc, P->sym_colpart);
     hipExtLaunchKernelGGL(k_local_sym_reduce, dim3(nblk(P->M, 64)), dim3(64 * kReduceWaves), 0, s, nullptr, eb, 0, (int)P->M,
                           P->sym_cov, P->sym_upb, P->otf_rowacc, P->sym_colpart, scale, out);
+    return;
+  }
+  if (P->use_bins) {
+    launch_bins(P, s, hist, L, scale, out, ea, eb);
     return;
   }
   switch (P->p) {
@@ -1889,6 +2078,14 @@ void gradx_setup(wfp_plan* P) {
   upload(hs, halfs, s);
   if (P->sym_stored) {
     gradx_setup_pair_once(P, hs);
+  } else if (P->use_bins) {
+    // by distance bins: the derivatives' table and the blocks' sums
+    P->bins.Cd = bin_table(P, 1);
+    bin_blocks(P, kBinColumns / 2, P->bblkd);
+    P->bblkd.part = P->alloc<double>(P->bblkd.total);
+    P->bblkd.part2 = P->alloc<double>(P->bblkd.total);
+    P->symd_one = P->alloc<double>(M);
+    upload(P->symd_one, std::vector<double>(M, 1.0), s);
   } else if (P->otf) {
     // on the fly: only the row and column buffers of the two sums
     const size_t lds = otf_deriv_lds(P);
@@ -2012,7 +2209,7 @@ void run_adjoint(wfp_plan* P, int64_t N, const double* e, double* grad_beta, dou
   zero_state_ref(P, adj);
   // weights on the fly: each level's derivative pass also forms the next
   // adjoint level's local sum (none before the first)
-  const bool fused = wx && P->otf && !P->sym_stored;
+  const bool fused = wx && P->otf && !P->sym_stored && !P->use_bins;
   bool next_ready = false;
   hipLaunchKernelGGL(k_fill, dim3(nblk(M, 256)), dim3(256), 0, s, P->gb_acc, M, 0.0);
   hipLaunchKernelGGL(k_fill, dim3(nblk(M, 256)), dim3(256), 0, s, P->gx_acc, M, 0.0);
@@ -2058,6 +2255,9 @@ void run_adjoint(wfp_plan* P, int64_t N, const double* e, double* grad_beta, dou
                              P->symd_row1, P->symd_col1, P->symd_one, P->xloc2);
           hipLaunchKernelGGL(k_local_sym_reduce, dim3(nblk(M, 64)), dim3(64 * kReduceWaves), 0, s, (int)M, P->sym_cov, P->sym_upb,
                              P->symd_row2, P->symd_col2, P->symd_one, P->xloc);
+        } else if (P->use_bins) {
+          launch_bins(P, s, P->ahist, Rv, P->symd_one, P->xloc2, nullptr, nullptr, segsig, (int64_t)(hd + L - a),
+                      P->xloc);
         } else if (P->otf) {
           launch_otf_deriv2(P, s, segsig, (int64_t)(hd + L - a), Rv);
           next_ready = fused;
