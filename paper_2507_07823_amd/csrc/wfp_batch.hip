@@ -31,7 +31,7 @@ struct wfp_batch {
   double** uout_d = nullptr;
   int64_t* lvl0_d = nullptr;
   bool uout_set = false;
-  size_t lds_a = 0, lds_b = 0, lds_c = 0, lds_til = 0, lds_otf = 0;
+  size_t lds_a = 0, lds_b = 0, lds_c = 0, lds_til = 0, lds_otf = 0, lds_sym = 0;
   // Jacobi sweeps of the global-solve instances, thread per row (swt) or
   // wavefront per row (sww); both lists are ordered by decreasing sweep count,
   // so sweep `it` launches the prefix of cnt_swt[it] (cnt_sww[it]) items
@@ -240,7 +240,8 @@ void build_batch(wfp_batch* B) {
     const int rpb = 256 / desc[i].pp;
     for (int b = 0; b < (int)nblk(M, rpb); ++b) inc.push_back(make_int2(i, b));
     if (P->sym_stored) {
-      sym.push_back(make_int2(i, (int)nblk(M, 4)));
+      sym.push_back(make_int2(i, (int)nblk(M, kBatchSymRows)));
+      B->lds_sym = std::max(B->lds_sym, sym_lds(P->NQ, 1));
       for (int bb = 0; bb < (int)nblk(M, 64); ++bb) symr.push_back(make_int2(i, bb));
     } else if (P->otf) {
       if (P->p != 8) fail(WFP_EDOMAIN, "batched on-the-fly local sums take p = 8");
@@ -390,7 +391,7 @@ void enqueue_level(wfp_batch* B) {
   }
   if (B->n_sym) {
     bl.work = B->wl_sym;
-    hipLaunchKernelGGL(kb_local_sym, dim3(B->n_sym), dim3(256), 0, s, bl);
+    hipLaunchKernelGGL(kb_local_sym, dim3(B->n_sym), dim3(kSymThreads), B->lds_sym, s, bl);
     bl.work = B->wl_symr;
     hipLaunchKernelGGL(kb_local_sym_reduce, dim3(B->n_symr), dim3(64 * kReduceWaves), 0, s, bl);
   }

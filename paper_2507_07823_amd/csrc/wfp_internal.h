@@ -45,6 +45,8 @@ constexpr double kBinNeighbours = 112.0;
 constexpr double kBinsOverPairs = 512.0;
 // and from which batch instances do (their launches fill the chip together)
 constexpr double kBatchBinsOverPairs = 400.0;
+// LDS of the pair-once stored local sum for H value sets.
+inline size_t sym_lds(int NQ, int H) { return (size_t)H * NQ * (kSymChunk / H + 2) * sizeof(double); }
 // most lags of the on-the-fly position gradient: local_mode 0 leaves longer
 // windows to stored weights
 constexpr int kMaxOtfGradLags = 46;

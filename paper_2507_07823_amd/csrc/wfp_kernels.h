@@ -94,6 +94,9 @@ __global__ void k_local_bins_reduce(int M, BinArgs A, const double* __restrict__
                                     const double* __restrict__ scale, double* __restrict__ out);
 // sources per LDS chunk of the on-the-fly derivative local sums
 constexpr int kOtfDerivChunk = 112;
+constexpr int kSymThreads = 512;      // pair-once stored local sum: threads of a block,
+constexpr int kSymChunk = 128;        // sources whose values it stages at a time,
+constexpr int kBatchSymRows = 16;     // and rows per block in a batch
 constexpr int kMaxOtfLags = 48;      // lags 1 .. NQ - 1 of a row staged by the symmetric local sum
 template <int P>
 __global__ void k_local_otf_sym(int M, int NH, int NQ, int64_t L, const int* __restrict__ up_end,
@@ -104,7 +107,7 @@ __global__ void k_local_otf_sym(int M, int NH, int NQ, int64_t L, const int* __r
                                 const double* __restrict__ phitab, double* __restrict__ rowacc,
                                 double* __restrict__ part);
 template <int SPL>
-__global__ void k_local_sym_rows(int M, int NH, int NQ, int64_t L, int mfirst, const int* __restrict__ up_end,
+__global__ void k_local_sym_rows(int M, int NH, int NQ, int64_t L, int mfirst, int rows, const int* __restrict__ up_end,
                                  const double* __restrict__ hist, const int64_t* __restrict__ rb,
                                  const uint2* __restrict__ sacx, const double* __restrict__ Qs,
                                  const int64_t* __restrict__ upb, double* __restrict__ rowacc,
@@ -119,7 +122,7 @@ __global__ void k_local_otf_deriv2(int M, int NH, int NQ, const int* __restrict_
                                    double* __restrict__ row1, double* __restrict__ row2, double* __restrict__ row3,
                                    double* __restrict__ part1, double* __restrict__ part2, double* __restrict__ part3);
 template <int SPL>
-__global__ void k_local_sym_deriv2(int M, int NQ, int NH, const int* __restrict__ up_end,
+__global__ void k_local_sym_deriv2(int M, int NQ, int NH, int rows, const int* __restrict__ up_end,
                                    const double* __restrict__ h1, int64_t r1, const double* __restrict__ h2,
                                    int64_t L2, const int64_t* __restrict__ rb, const uint2* __restrict__ sacx,
                                    const double* __restrict__ Qs, const int64_t* __restrict__ upb,

@@ -10,6 +10,8 @@
 #include "wfp_device.h"
 #include "wfp_kernels.h"
 
+#include <type_traits>
+
 namespace wfp {
 
 namespace {
@@ -982,154 +984,161 @@ WFP_OTFS_INST(10)
 WFP_OTFS_INST(12)
 #undef WFP_OTFS_INST
 
-// First lag m in [m0, NQ) whose run of sources reaches index i0 of the upper
-// range (c_m > i0), NQ if none.  The runs are prefixes whose length does not
-// decrease with the lag (a source carries the lags from its stencil's lowest
-// one up, and that grows with the distance), so the lags below it contribute
-// only zeros for sources i0 and beyond.
-__device__ __forceinline__ int first_lag_reaching(const uint2* __restrict__ cw, int m0, int NQ, int i0) {
-  int lo = m0, hi = NQ;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if ((int)cw[mid].x > i0) hi = mid;
-    else lo = mid + 1;
+// A local sum from stored weights, each unordered pair once.  A wavefront walks
+// the upper range [j, up_end[j]) of a row j (unwrapped: periodic ranges
+// continue past M - 1 at 0), each lane over SPL consecutive sources (2: one
+// 16-byte load of a pair's weights, for long ranges; 1: every lane busy on
+// short ones).  Row j's weights are one run per lag m over the first c_jm
+// sources of the range (those whose stencils reach lag m: a prefix whose length
+// does not decrease with the lag), at Qs[rb[j] + o_jm + i],
+// sacx[j NQ + m] = (c_jm, o_jm).  The row's own sum goes to row1[j], each
+// pair's column term sum_m Q v_j^{L-m} (row l's share) to col1[upb[j] + i] (0
+// for the row itself), times -1 where H = 2; H = 2 does the same for a second
+// set of values.  Lag m's values are row ra - m of `va` (rb_ - m of `vb`), plus
+// na (nb) where that is negative: rings, or linear buffers (na = 0).
+//
+// Bound by the stream of weights.  The values of the block's sources, rows of
+// consecutive springs that share most of them, are staged in LDS (kSymChunk
+// sources at a time): read per pair they double the lines that a wavefront asks
+// the L1 for, and it thrashes.  The lags' runs and the row's own values sit one
+// lag per lane and are read as scalars; the weight loads carry no branch (a
+// lane past a run reads the run's first weight and drops it).  Measured at
+// k_local_sym_rows.
+template <int SPL, int H>
+__device__ __forceinline__ void sym_block(int M, int NQ, int mfirst, int rows, const int* __restrict__ up_end,
+                                          const int64_t* __restrict__ rb, const uint2* __restrict__ sacx,
+                                          const double* __restrict__ Qs, const int64_t* __restrict__ upb,
+                                          const double* __restrict__ va, int64_t ra, int na,
+                                          const double* __restrict__ vb, int64_t rb_, int nb,
+                                          double* __restrict__ row1, double* __restrict__ row2,
+                                          double* __restrict__ col1, double* __restrict__ col2, int b) {
+  constexpr int CH = kSymChunk / H, CP = CH + 2;              // sources staged, row pitch (bank offset)
+  constexpr int U = 4;                                        // lags whose loads are in flight together
+  extern __shared__ double sv[];                              // [H][NQ][CP]
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j0 = b * rows, jend = min(j0 + rows, M);
+  const long long uend = up_end[jend - 1];                    // unwrapped end of the block's sources, <= 2M
+  auto line = [&](int64_t r, int n, int m) {                  // first element of lag m's values
+    const int64_t k = r - m;
+    return (k < 0 ? k + n : k) * M;
+  };
+  auto scalar = [](double v, int m) {
+    const long long x = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)x, m), hi = __builtin_amdgcn_readlane((int)(x >> 32), m);
+    return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+  };
+  for (long long cb = j0; cb < uend; cb += CH) {
+    if (cb > j0) __syncthreads();                             // the previous chunk is no longer read
+    const int cn = (int)(uend - cb < CH ? uend - cb : CH);    // sources of the chunk
+    for (int m = mfirst + wv; m < NQ; m += kSymThreads / 64) {
+      const double* __restrict__ pa = va + line(ra, na, m);
+      const double* __restrict__ pb = H == 2 ? vb + line(rb_, nb, m) : nullptr;
+#pragma unroll
+      for (int k0 = 0; k0 < CH; k0 += 64) {
+        const int k = k0 + lane;
+        if (k < cn) {
+          const long long u = cb + k;
+          const int l = (int)(u < M ? u : u - M);
+          sv[m * CP + k] = pa[l];
+          if (H == 2) sv[(NQ + m) * CP + k] = pb[l];
+        }
+      }
+    }
+    __syncthreads();
+    for (int j = j0 + wv; j < jend; j += kSymThreads / 64) {
+      const int n = up_end[j] - j;
+      // the part of the range within the chunk
+      const int ia = cb > j ? (int)(cb - j) : 0, ib = (int)(cb + cn - j < n ? cb + cn - j : n);
+      if (ia >= ib) continue;
+      uint2 c = make_uint2(0u, 0u);
+      double own[H] = {};
+      if (lane >= mfirst && lane < NQ) {
+        c = sacx[(int64_t)j * NQ + lane];
+        own[0] = va[line(ra, na, lane) + j];
+        if (H == 2) own[H - 1] = vb[line(rb_, nb, lane) + j];
+      }
+      const double* __restrict__ qrow = Qs + rb[j];
+      const int64_t ub = upb[j];
+      const int kj = (int)(j - cb);                           // place of i = 0 in the chunk
+      double acc[H][SPL] = {};
+      for (int i0 = ia; i0 < ib; i0 += 64 * SPL) {
+        const int i = i0 + SPL * lane;
+        const double* vp = sv + (i < ib ? kj + i : 0);
+        double pc[H][SPL] = {};
+        const unsigned long long reach = __ballot((int)c.x > i0);
+        for (int mb = reach ? __ffsll((long long)reach) - 1 : NQ; mb < NQ; mb += U) {
+          double w[U][SPL];
+#pragma unroll
+          for (int r = 0; r < U; ++r) {
+            const int m = mb + r;                             // < 64; lanes from NQ on hold empty runs
+            const int cx = min(__builtin_amdgcn_readlane((int)c.x, m), ib);
+            const double* qp = qrow + (unsigned)__builtin_amdgcn_readlane((int)c.y, m);
+            const unsigned off = (i < cx ? i : 0) * 8u;
+            if constexpr (SPL == 1) {
+              w[r][0] = *(const double*)((const char*)qp + off);
+            } else {
+              // (a weight one past a run may be read: the packed array carries
+              // two spare elements)
+              const d2u q = *(const d2u*)((const char*)qp + off);
+              w[r][0] = q.x;
+              w[r][1] = q.y;
+            }
+          }
+#pragma unroll
+          for (int r = 0; r < U; ++r) {
+            const int m = mb + r;
+            const int cx = min(__builtin_amdgcn_readlane((int)c.x, m), ib);
+            const int mv = min(m, NQ - 1) * CP;
+#pragma unroll
+            for (int t = 0; t < H; ++t) {
+              const double rv = scalar(own[t], m);
+#pragma unroll
+              for (int k = 0; k < SPL; ++k) {
+                // outside the run neither the weight nor the value counts
+                const bool on = i + k < cx;
+                const double wk = on ? w[r][k] : 0.0, v = vp[t * NQ * CP + mv + k], vk = on ? v : 0.0;
+                acc[t][k] = fma(wk, vk, acc[t][k]);
+                pc[t][k] = fma(wk, rv, pc[t][k]);
+              }
+            }
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < SPL; ++k)
+          if (i + k < ib) {
+            const bool self = i + k == 0;
+            col1[ub + i + k] = self ? 0.0 : (H == 2 ? -pc[0][k] : pc[0][k]);
+            if (H == 2) col2[ub + i + k] = self ? 0.0 : -pc[H - 1][k];
+          }
+      }
+#pragma unroll
+      for (int t = 0; t < H; ++t) {
+        // a row's chunks are its own wavefront's, in order
+        double v = wave_sum(SPL == 2 ? acc[t][0] + acc[t][SPL - 1] : acc[t][0]);
+        double* __restrict__ out = t == 0 ? row1 : row2;
+        if (lane == 0) out[j] = ia > 0 ? out[j] + v : v;
+      }
+    }
   }
-  return lo;
 }
 
 // Local sum of lags m >= mfirst (1, or 2 with the lag-1 part added by
-// k_local_sym_lag1) from stored weights, each unordered pair once.
-// One wavefront per row j walks its upper range [j, up_end[j]) (unwrapped:
-// periodic ranges continue past M - 1 at 0), each lane over SPL consecutive
-// sources (2: one 16-byte load of each pair's weights and densities, for long
-// ranges; 1: every lane busy on short ones), lags in groups of 8 / SPL with
-// every load of a group issued before its use.  Row j's
-// weights are one run per lag m over the first c_jm sources of the range
-// (those whose stencils reach lag m: a prefix, as the distance grows along the
-// range), at Qs[rb[j] + o_jm + i], sacx[j NQ + m] = (c_jm, o_jm), unscaled.
-// The row's own sum sum_m sum_i Q sigma_l goes to rowacc[j]; each pair's
-// column term sum_m Q sigma_j^{L-m} (row l's share) to colpart[upb[j] + i]
-// (0 for the row itself); k_local_sym_reduce adds them up per row.
+// k_local_sym_lag1) from stored weights, unscaled; k_local_sym_reduce adds a
+// row's own sum and its column terms up.  With the reduction, against densities
+// read per pair from the caches and a branch around each load: 287 us for 369
+// (M = 1e5, 50 sources per range, 941 MB of weights), 43.5 for 49.9 (M = 1e4,
+// 69), 323 for 339 (M = 3e4, 206).  Eight lags in flight instead of four: 299,
+// 46.0 and 339 us, the L1 thrashes.
 template <int SPL>
-__device__ __forceinline__ void k_local_sym_rows_body(int M, int NH, int NQ, int64_t L, int mfirst,
-                                                      const int* __restrict__ up_end, const double* __restrict__ hist,
-                                                      const int64_t* __restrict__ rb, const uint2* __restrict__ sacx,
-                                                      const double* __restrict__ Qs, const int64_t* __restrict__ upb,
-                                                      double* __restrict__ rowacc, double* __restrict__ colpart,
-                                                      int b) {
-  __shared__ double rv[4][kMaxOtfLags + 1];                   // each row's own history, lags 0 .. NQ - 1
-  __shared__ uint2 cw[4][kMaxOtfLags + 1];
-  __shared__ int64_t slot[kMaxOtfLags + 1];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int j = b * 4 + wv;
-  for (int m = threadIdx.x; m < NQ; m += blockDim.x) slot[m] = (int64_t)mod_slot(L - m, NH) * M;
-  __syncthreads();
-  for (int e = threadIdx.x; e < 4 * NQ; e += blockDim.x) {
-    const int w = e / NQ, m = e - w * NQ;
-    const int jr = b * 4 + w;
-    const bool ok = m >= 1 && jr < M;
-    rv[w][m] = ok ? hist[slot[m] + jr] : 0.0;
-    cw[w][m] = ok ? sacx[(int64_t)jr * NQ + m] : make_uint2(0u, 0u);
-  }
-  __syncthreads();
-  if (j >= M) return;                                         // no barrier below
-  const int n = up_end[j] - j;
-  const double* __restrict__ qrow = Qs + rb[j];
-  double* __restrict__ cp = colpart + upb[j];
-  if constexpr (SPL == 1) {
-    double acc = 0.0;
-    for (int i0 = 0; i0 < n; i0 += 64) {
-      const int i = i0 + lane;
-      const bool in = i < n;
-      int l = j + i;
-      if (l >= M) l -= M;
-      double pc = 0.0;
-      for (int mb = first_lag_reaching(cw[wv], mfirst, NQ, i0); mb < NQ; mb += 8) {
-        double w[8], h[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const int m = mb + r;
-          const uint2 c = m < NQ ? cw[wv][m] : make_uint2(0u, 0u);
-          const bool on = in && i < (int)c.x;
-          w[r] = on ? qrow[c.y + i] : 0.0;
-          h[r] = on ? hist[slot[m] + l] : 0.0;
-        }
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const int m = mb + r;
-          if (m < NQ) {
-            acc = fma(w[r], h[r], acc);
-            pc = fma(w[r], rv[wv][m], pc);
-          }
-        }
-      }
-      if (in) cp[i] = i == 0 ? 0.0 : pc;
-    }
-    acc = wave_sum(acc);
-    if (lane == 0) rowacc[j] = acc;
-  } else {
-    double acc0 = 0.0, acc1 = 0.0;
-    for (int i0 = 0; i0 < n; i0 += 128) {
-      // sources i and i + 1 of the range, one 16-byte load of each pair's
-      // weights and densities (a weight one past a run is read and dropped:
-      // the packed array carries two spare elements; a density pair that would
-      // run past source M - 1 continues at source 0)
-      const int i = i0 + 2 * lane;
-      const bool in0 = i < n, in1 = i + 1 < n;
-      int l = j + i;
-      if (l >= M) l -= M;
-      const bool adj = l + 1 < M;
-      double pc0 = 0.0, pc1 = 0.0;
-      for (int mb = first_lag_reaching(cw[wv], mfirst, NQ, i0); mb < NQ; mb += 4) {
-        d2u w[4], h[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = mb + r;
-          const uint2 c = m < NQ ? cw[wv][m] : make_uint2(0u, 0u);
-          w[r] = d2u{0.0, 0.0};
-          h[r] = d2u{0.0, 0.0};
-          if (in0 && i < (int)c.x) {
-            const double* __restrict__ hp = hist + slot[m];
-            w[r] = *(const d2u*)(qrow + c.y + i);
-            if (adj) {
-              h[r] = *(const d2u*)(hp + l);
-            } else {
-              h[r].x = hp[l];
-              h[r].y = hp[0];
-            }
-            if (!(in1 && i + 1 < (int)c.x)) {
-              w[r].y = 0.0;
-              h[r].y = 0.0;
-            }
-          }
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = mb + r;
-          if (m < NQ) {
-            acc0 = fma(w[r].x, h[r].x, acc0);
-            acc1 = fma(w[r].y, h[r].y, acc1);
-            pc0 = fma(w[r].x, rv[wv][m], pc0);
-            pc1 = fma(w[r].y, rv[wv][m], pc1);
-          }
-        }
-      }
-      if (in0) cp[i] = i == 0 ? 0.0 : pc0;
-      if (in1) cp[i + 1] = pc1;
-    }
-    const double acc = wave_sum(acc0 + acc1);
-    if (lane == 0) rowacc[j] = acc;
-  }
-}
-
-template <int SPL>
-__global__ void __launch_bounds__(256)
-k_local_sym_rows(int M, int NH, int NQ, int64_t L, int mfirst, const int* __restrict__ up_end,
+__global__ void __launch_bounds__(kSymThreads)
+k_local_sym_rows(int M, int NH, int NQ, int64_t L, int mfirst, int rows, const int* __restrict__ up_end,
                  const double* __restrict__ hist, const int64_t* __restrict__ rb, const uint2* __restrict__ sacx,
                  const double* __restrict__ Qs, const int64_t* __restrict__ upb, double* __restrict__ rowacc,
                  double* __restrict__ colpart) {
-  k_local_sym_rows_body<SPL>(M, NH, NQ, L, mfirst, up_end, hist, rb, sacx, Qs, upb, rowacc, colpart,
-                             xcd_block(blockIdx.x, gridDim.x));
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  if ((int64_t)b * rows >= M) return;                         // padding block (uniform)
+  sym_block<SPL, 1>(M, NQ, mfirst, rows, up_end, rb, sacx, Qs, upb, hist, mod_slot(L, NH), NH, nullptr, 0, 0,
+                    rowacc, nullptr, colpart, nullptr, b);
 }
 
 // The gradient pass's two signed derivative local sums (lags 0 .. NQ - 1)
@@ -1139,163 +1148,32 @@ k_local_sym_rows(int M, int NH, int NQ, int64_t L, int mfirst, const int* __rest
 // j's values.  Values for the first sum from a linear buffer (row r1 - m for
 // lag m: the forward densities of the segment and the NQ - 1 levels before
 // it), for the second from a ring (slot L2 - m mod NH: the adjoint state).
-// One wavefront per row, SPL sources per lane, as in k_local_sym_rows; each
-// pair's column terms, negated, go to col1 / col2[upb[j] + i] (0 for the row
-// itself), and k_local_sym_reduce adds them up per row.
+// k_local_sym_reduce adds the parts up per row.
 template <int SPL>
-__global__ void __launch_bounds__(256)
-k_local_sym_deriv2(int M, int NQ, int NH, const int* __restrict__ up_end, const double* __restrict__ h1, int64_t r1,
-                   const double* __restrict__ h2, int64_t L2, const int64_t* __restrict__ rb,
+__global__ void __launch_bounds__(kSymThreads)
+k_local_sym_deriv2(int M, int NQ, int NH, int rows, const int* __restrict__ up_end, const double* __restrict__ h1,
+                   int64_t r1, const double* __restrict__ h2, int64_t L2, const int64_t* __restrict__ rb,
                    const uint2* __restrict__ sacx, const double* __restrict__ Qs, const int64_t* __restrict__ upb,
                    double* __restrict__ row1, double* __restrict__ row2, double* __restrict__ col1,
                    double* __restrict__ col2) {
-  __shared__ double rv1[4][kMaxOtfLags + 1], rv2[4][kMaxOtfLags + 1];   // each row's own values, lags 0 .. NQ - 1
-  __shared__ uint2 cw[4][kMaxOtfLags + 1];
-  __shared__ int64_t s1[kMaxOtfLags + 1], s2[kMaxOtfLags + 1];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int nb = gridDim.x;
-  const int j = xcd_block(blockIdx.x, nb) * 4 + wv;
-  for (int m = threadIdx.x; m < NQ; m += blockDim.x) {
-    s1[m] = (r1 - m) * M;
-    s2[m] = (int64_t)mod_slot(L2 - m, NH) * M;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < 4 * NQ; e += blockDim.x) {
-    const int w = e / NQ, m = e - w * NQ;
-    const int jr = xcd_block(blockIdx.x, nb) * 4 + w;
-    const bool ok = jr < M;
-    rv1[w][m] = ok ? h1[s1[m] + jr] : 0.0;
-    rv2[w][m] = ok ? h2[s2[m] + jr] : 0.0;
-    cw[w][m] = ok ? sacx[(int64_t)jr * NQ + m] : make_uint2(0u, 0u);
-  }
-  __syncthreads();
-  if (j >= M) return;                                         // no barrier below
-  const int n = up_end[j] - j;
-  const double* __restrict__ qrow = Qs + rb[j];
-  double* __restrict__ cp1 = col1 + upb[j];
-  double* __restrict__ cp2 = col2 + upb[j];
-  if constexpr (SPL == 1) {
-    double a1 = 0.0, a2 = 0.0;
-    for (int i0 = 0; i0 < n; i0 += 64) {
-      const int i = i0 + lane;
-      const bool in = i < n;
-      int l = j + i;
-      if (l >= M) l -= M;
-      double p1 = 0.0, p2 = 0.0;
-      for (int mb = first_lag_reaching(cw[wv], 0, NQ, i0); mb < NQ; mb += 8) {
-        double w[8], g1[8], g2[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const int m = mb + r;
-          const uint2 c = m < NQ ? cw[wv][m] : make_uint2(0u, 0u);
-          const bool on = in && i < (int)c.x;
-          w[r] = on ? qrow[c.y + i] : 0.0;
-          g1[r] = on ? h1[s1[m] + l] : 0.0;
-          g2[r] = on ? h2[s2[m] + l] : 0.0;
-        }
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const int m = mb + r;
-          if (m < NQ) {
-            a1 = fma(w[r], g1[r], a1);
-            a2 = fma(w[r], g2[r], a2);
-            p1 = fma(w[r], rv1[wv][m], p1);
-            p2 = fma(w[r], rv2[wv][m], p2);
-          }
-        }
-      }
-      if (in) {
-        cp1[i] = i == 0 ? 0.0 : -p1;
-        cp2[i] = i == 0 ? 0.0 : -p2;
-      }
-    }
-    a1 = wave_sum(a1);
-    a2 = wave_sum(a2);
-    if (lane == 0) {
-      row1[j] = a1;
-      row2[j] = a2;
-    }
-  } else {
-    double a1 = 0.0, a2 = 0.0, b1 = 0.0, b2 = 0.0;
-    for (int i0 = 0; i0 < n; i0 += 128) {
-      // sources i and i + 1, 16-byte loads as in k_local_sym_rows
-      const int i = i0 + 2 * lane;
-      const bool in0 = i < n, in1 = i + 1 < n;
-      int l = j + i;
-      if (l >= M) l -= M;
-      const bool adj = l + 1 < M;
-      double p1 = 0.0, p2 = 0.0, q1 = 0.0, q2 = 0.0;
-      for (int mb = first_lag_reaching(cw[wv], 0, NQ, i0); mb < NQ; mb += 4) {
-        d2u w[4], g1[4], g2[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = mb + r;
-          const uint2 c = m < NQ ? cw[wv][m] : make_uint2(0u, 0u);
-          w[r] = d2u{0.0, 0.0};
-          g1[r] = d2u{0.0, 0.0};
-          g2[r] = d2u{0.0, 0.0};
-          if (in0 && i < (int)c.x) {
-            const double* __restrict__ hp1 = h1 + s1[m];
-            const double* __restrict__ hp2 = h2 + s2[m];
-            w[r] = *(const d2u*)(qrow + c.y + i);
-            if (adj) {
-              g1[r] = *(const d2u*)(hp1 + l);
-              g2[r] = *(const d2u*)(hp2 + l);
-            } else {
-              g1[r].x = hp1[l];
-              g1[r].y = hp1[0];
-              g2[r].x = hp2[l];
-              g2[r].y = hp2[0];
-            }
-            if (!(in1 && i + 1 < (int)c.x)) {
-              w[r].y = 0.0;
-              g1[r].y = 0.0;
-              g2[r].y = 0.0;
-            }
-          }
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = mb + r;
-          if (m < NQ) {
-            a1 = fma(w[r].x, g1[r].x, a1);
-            b1 = fma(w[r].y, g1[r].y, b1);
-            a2 = fma(w[r].x, g2[r].x, a2);
-            b2 = fma(w[r].y, g2[r].y, b2);
-            p1 = fma(w[r].x, rv1[wv][m], p1);
-            q1 = fma(w[r].y, rv1[wv][m], q1);
-            p2 = fma(w[r].x, rv2[wv][m], p2);
-            q2 = fma(w[r].y, rv2[wv][m], q2);
-          }
-        }
-      }
-      if (in0) {
-        cp1[i] = i == 0 ? 0.0 : -p1;
-        cp2[i] = i == 0 ? 0.0 : -p2;
-      }
-      if (in1) {
-        cp1[i + 1] = -q1;
-        cp2[i + 1] = -q2;
-      }
-    }
-    const double s1sum = wave_sum(a1 + b1), s2sum = wave_sum(a2 + b2);
-    if (lane == 0) {
-      row1[j] = s1sum;
-      row2[j] = s2sum;
-    }
-  }
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  if ((int64_t)b * rows >= M) return;                         // padding block (uniform)
+  sym_block<SPL, 2>(M, NQ, 0, rows, up_end, rb, sacx, Qs, upb, h1, r1, 0, h2, mod_slot(L2, NH), NH, row1, row2, col1,
+                    col2, b);
 }
 
-template __global__ void k_local_sym_rows<1>(int, int, int, int64_t, int, const int*, const double*, const int64_t*,
-                                             const uint2*, const double*, const int64_t*, double*, double*);
-template __global__ void k_local_sym_rows<2>(int, int, int, int64_t, int, const int*, const double*, const int64_t*,
-                                             const uint2*, const double*, const int64_t*, double*, double*);
-template __global__ void k_local_sym_deriv2<1>(int, int, int, const int*, const double*, int64_t, const double*,
-                                               int64_t, const int64_t*, const uint2*, const double*,
-                                               const int64_t*, double*, double*, double*, double*);
-template __global__ void k_local_sym_deriv2<2>(int, int, int, const int*, const double*, int64_t, const double*,
-                                               int64_t, const int64_t*, const uint2*, const double*,
-                                               const int64_t*, double*, double*, double*, double*);
+template __global__ void k_local_sym_rows<1>(int, int, int, int64_t, int, int, const int*, const double*,
+                                             const int64_t*, const uint2*, const double*, const int64_t*, double*,
+                                             double*);
+template __global__ void k_local_sym_rows<2>(int, int, int, int64_t, int, int, const int*, const double*,
+                                             const int64_t*, const uint2*, const double*, const int64_t*, double*,
+                                             double*);
+template __global__ void k_local_sym_deriv2<1>(int, int, int, int, const int*, const double*, int64_t, const double*,
+                                               int64_t, const int64_t*, const uint2*, const double*, const int64_t*,
+                                               double*, double*, double*, double*);
+template __global__ void k_local_sym_deriv2<2>(int, int, int, int, const int*, const double*, int64_t, const double*,
+                                               int64_t, const int64_t*, const uint2*, const double*, const int64_t*,
+                                               double*, double*, double*, double*);
 
 // The gradient pass's two signed derivative local sums (lags 0 .. NQ - 1)
 // with the weights evaluated on the fly, each unordered pair once.  For the
@@ -2577,17 +2455,18 @@ __global__ void __launch_bounds__(256) kb_local_otf_reduce(BatchLaunch b) {
 // plan's on-the-fly schedule): the rows over (instance, block of 4 rows)
 // items, then the per-row totals over (instance, 64 rows) items, scaled by
 // beta_j / 2 into the instance's local sum.
-__global__ void __launch_bounds__(256) kb_local_sym(BatchLaunch b) {
+__global__ void __launch_bounds__(kSymThreads) kb_local_sym(BatchLaunch b) {
   const int2 w = b.work[xcd_block(blockIdx.x, gridDim.x)];
   if (w.x < 0) return;   // block-uniform
   const InstDesc& d = b.desc[w.x];
   if (*b.level >= d.end) return;   // the instance has marched its own levels (block-uniform)
+  const int s0 = mod_slot(*b.level, d.NH);
   if (d.sym_spl == 2)
-    k_local_sym_rows_body<2>(d.M, d.NH, d.NQ, *b.level, 1, d.otf_up_end, d.hist, d.sym_rb, d.sym_acx, d.sym_q,
-                             d.sym_upb, d.otf_rowacc, d.sym_colpart, w.y);
+    sym_block<2, 1>(d.M, d.NQ, 1, kBatchSymRows, d.otf_up_end, d.sym_rb, d.sym_acx, d.sym_q, d.sym_upb, d.hist, s0,
+                    d.NH, nullptr, 0, 0, d.otf_rowacc, nullptr, d.sym_colpart, nullptr, w.y);
   else
-    k_local_sym_rows_body<1>(d.M, d.NH, d.NQ, *b.level, 1, d.otf_up_end, d.hist, d.sym_rb, d.sym_acx, d.sym_q,
-                             d.sym_upb, d.otf_rowacc, d.sym_colpart, w.y);
+    sym_block<1, 1>(d.M, d.NQ, 1, kBatchSymRows, d.otf_up_end, d.sym_rb, d.sym_acx, d.sym_q, d.sym_upb, d.hist, s0,
+                    d.NH, nullptr, 0, 0, d.otf_rowacc, nullptr, d.sym_colpart, nullptr, w.y);
 }
 
 __global__ void __launch_bounds__(64 * kReduceWaves) kb_local_sym_reduce(BatchLaunch b) {

@@ -63,8 +63,10 @@ namespace {
 // lag); 2 measured fastest of 1 to 4 at M = 1e4, 1e5 and 1e6
 constexpr int kLocalSplit = 2;
 // mean upper-range length (sources per row, each pair once) from which the
-// pair-once kernels take two consecutive sources per lane
-constexpr int kSymPairedRange = 96;
+// pair-once kernels take two consecutive sources per lane (one against two:
+// 287 / 296 us at 50 sources per range and M = 1e5; 44.9 / 43.5 at 69, 1e4;
+// 171 / 163 at 138, 2e4; 352 / 322 at 206, 3e4)
+constexpr int kSymPairedRange = 64;
 
 void zero_state(wfp_plan* P) {
   auto fill = [&](double* ptr, int64_t n) {
@@ -928,8 +930,7 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
         P->sym_upb = upb_d;
         P->sym_colpart = P->alloc<double>(np_up);
         // two sources per lane when the upper ranges are long enough to keep
-        // the lanes busy (measured: faster at 206 sources per range, slower at
-        // 69, where half the lanes would idle)
+        // the lanes busy
         P->sym_spl = np_up >= (int64_t)kSymPairedRange * M ? 2 : 1;
         // rows covering row l: j < l with up[j] > l, and j > l with up[j] > l + M
         // (periodic); up is non-decreasing, so each is a run ending at l - 1 or M - 1
@@ -1444,6 +1445,16 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
 // pipelined one (lags >= 2 ahead, lag 1 after the previous solve).
 bool otf_schedule(const wfp_plan* P) { return P->otf && !P->sym_stored; }
 
+// Rows per block of the pair-once stored local sum: one per wavefront, or two
+// once that leaves two blocks per compute unit.  More (the sources' values
+// staged for more rows) do not pay: at 206 sources per range 16 rows take 323 us
+// and 32 rows 362 us (M = 3e4), at 50 both 295 us (M = 1e5); at M = 1e3, 8 rows
+// 17.0 us and 16 rows 21.1.
+int sym_rows(const wfp_plan* P) {
+  const int w = kSymThreads / 64;
+  return P->M >= 2 * w * 512 ? 2 * w : w;
+}
+
 void launch_local_otf(wfp_plan* P, hipStream_t s, const double* hist, int64_t L, const double* scale, double* out,
                       hipEvent_t ea = nullptr, hipEvent_t eb = nullptr) {
   const int nblocks = 8 * (int)nblk(P->otf_nblk, 8);
@@ -1456,8 +1467,8 @@ void launch_local_otf(wfp_plan* P, hipStream_t s, const double* hist, int64_t L,
                         P->otf_rowacc, P->otf_part)
   if (P->sym_stored) {
     hipExtLaunchKernelGGL(P->sym_spl == 2 ? k_local_sym_rows<2> : k_local_sym_rows<1>,
-                          dim3(8 * nblk(nblk(P->M, 4), 8)), dim3(256), 0, s, ea, nullptr, 0,
-                          (int)P->M, P->NH, P->NQ, L, 1, P->otf_up_end, hist, P->sym_rb, P->sym_acx, P->sym_q,
+                          dim3(8 * nblk(nblk(P->M, sym_rows(P)), 8)), dim3(kSymThreads), sym_lds(P->NQ, 1), s, ea,
+                          nullptr, 0, (int)P->M, P->NH, P->NQ, L, 1, sym_rows(P), P->otf_up_end, hist, P->sym_rb, P->sym_acx, P->sym_q,
                           P->sym_upb, P->otf_rowacc, P->sym_colpart);
     hipExtLaunchKernelGGL(k_local_sym_reduce, dim3(nblk(P->M, 64)), dim3(64 * kReduceWaves), 0, s, nullptr, eb, 0, (int)P->M,
                           P->sym_cov, P->sym_upb, P->otf_rowacc, P->sym_colpart, scale, out);
@@ -1553,9 +1564,9 @@ void launch_local_big(wfp_plan* P, hipStream_t s, const double* hist, int64_t L,
                       hipEvent_t eb = nullptr) {
   if (P->sym_stored) {
     hipExtLaunchKernelGGL(P->sym_spl == 2 ? k_local_sym_rows<2> : k_local_sym_rows<1>,
-                          dim3(8 * nblk(nblk(P->M, 4), 8)), dim3(256), 0, s, ea, nullptr, 0,
-                          (int)P->M, P->NH, P->NQ, L, 2, P->otf_up_end, hist, P->sym_rb, P->sym_acx, P->sym_q,
-                          P->sym_upb, P->otf_rowacc, P->sym_colpart);
+                          dim3(8 * nblk(nblk(P->M, sym_rows(P)), 8)), dim3(kSymThreads), sym_lds(P->NQ, 1), s, ea,
+                          nullptr, 0, (int)P->M, P->NH, P->NQ, L, 2, sym_rows(P), P->otf_up_end, hist, P->sym_rb,
+                          P->sym_acx, P->sym_q, P->sym_upb, P->otf_rowacc, P->sym_colpart);
     hipExtLaunchKernelGGL(k_local_sym_reduce, dim3(nblk(P->M, 64)), dim3(64 * kReduceWaves), 0, s, nullptr, eb, 0, (int)P->M,
                           P->sym_cov, P->sym_upb, P->otf_rowacc, P->sym_colpart, P->half_beta,
                           P->locb + (L & 1) * P->M);
@@ -2247,8 +2258,8 @@ void run_adjoint(wfp_plan* P, int64_t N, const double* e, double* grad_beta, dou
         deriv_field(P, adj);
         if (P->sym_stored) {
           hipLaunchKernelGGL(P->sym_spl == 2 ? k_local_sym_deriv2<2> : k_local_sym_deriv2<1>,
-                             dim3(8 * nblk(nblk(M, 4), 8)), dim3(256), 0, s, (int)M, P->NQ,
-                             P->NH, P->otf_up_end, (const double*)segsig, (int64_t)(hd + L - a),
+                             dim3(8 * nblk(nblk(M, sym_rows(P)), 8)), dim3(kSymThreads), sym_lds(P->NQ, 2), s, (int)M,
+                             P->NQ, P->NH, sym_rows(P), P->otf_up_end, (const double*)segsig, (int64_t)(hd + L - a),
                              (const double*)P->ahist, Rv, P->symd_rb, P->symd_acx, P->symd_q, P->sym_upb,
                              P->symd_row1, P->symd_row2, P->symd_col1, P->symd_col2);
           hipLaunchKernelGGL(k_local_sym_reduce, dim3(nblk(M, 64)), dim3(64 * kReduceWaves), 0, s, (int)M, P->sym_cov, P->sym_upb,

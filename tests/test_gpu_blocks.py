@@ -1,0 +1,98 @@
+"""The pair-once stored local sum at the edges of its blocks (8 or 16 rows) and
+of the chunks of sources that it stages (128, 64 in the gradient pass)."""
+import math
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def wfp():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2507_07823_amd import wfp as w
+    w.load_library()
+    return w
+
+
+def _problem(M, width, dt, seam=False, free=False):
+    r = np.random.default_rng([5, M])
+    x = r.uniform(0.2, 0.2 + width, M) - (2.7 if width > 4.0 else 0.0)
+    if seam:
+        x = np.where(np.arange(M) % 2 == 0, np.pi - width * r.random(M), -np.pi + width * r.random(M))
+        x = np.minimum(x, np.pi - 1e-9)
+    beta = 0.005 / dt ** 2 * width / M
+    return dict(x=x, beta=np.full(M, beta), packets=np.array([[1.0, -2.0, 0.1, 0.0, 0.0]]), boundary=1 if free else 0,
+                x_recv=np.array([0.15, 0.25, 0.35]))
+
+
+def _state(plan, seed=11):
+    import torch
+    i = plan.info
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    z = dict(device="cuda", dtype=torch.float64)
+    s = dict(hist=torch.randn(i["m_max"], i["M"], generator=g, **z),
+             ring=torch.randn(i["W"], i["K"] + 1, 2, generator=g, **z),
+             alpha=torch.randn(i["K"] + 1, 2, generator=g, **z), dalpha=torch.randn(i["K"] + 1, 2, generator=g, **z))
+    for k in ("ring", "alpha", "dalpha"):
+        s[k][..., 0, 1] = 0.0
+    return s
+
+
+def _rel(a, b):
+    return float((a - b).abs().max() / b.abs().max())
+
+
+# The two modes store the same weights to rounding and add a row's n pairs x 40
+# lags in another order: relative to the largest sum of random histories
+# 4 eps sqrt(40 n), 3e-13 for n = 4000.
+LOCAL_TOL = 3e-13
+
+PAIRS = [
+    dict(M=1, width=0.1, dt=2e-3),
+    dict(M=7, width=0.05, dt=2e-3),                       # one block, not full
+    dict(M=17, width=0.01, dt=2e-3),
+    dict(M=129, width=0.05, dt=2e-3, p=6),                # ranges of 128 and fewer: one chunk and one source more
+    dict(M=300, width=0.06, dt=2e-3),                     # all in reach: ranges up to 300
+    dict(M=2000, width=1.0, dt=2e-3, free=True),
+    dict(M=501, width=0.05, dt=4e-3, seam=True),          # ranges that run on at source 0
+    dict(M=8191, width=5.0, dt=1e-3),                     # the last size with 8 rows per block,
+    dict(M=8192, width=5.0, dt=1e-3),                     # the first with 16
+    dict(M=9001, width=2.0, dt=1e-3, p=4),
+]
+
+
+@pytest.mark.parametrize("case", PAIRS, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+def test_pair_once_equals_per_pair(wfp, case):
+    prob = _problem(case["M"], case["width"], case["dt"], case.get("seam"), case.get("free"))
+    out = []
+    for mode in (1, 3):
+        plan = wfp.Plan(prob, case["dt"], p=case.get("p", 8), local_mode=mode)
+        assert plan.info["local_mode"] == mode
+        plan.set_state(50, **_state(plan))
+        out.append(plan.march(3)[0])
+        plan.close()
+    assert _rel(out[1], out[0]) < LOCAL_TOL
+
+
+@pytest.mark.parametrize("case", [PAIRS[i] for i in (1, 3, 4, 6)],
+                         ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+def test_pair_once_gradient_equals_per_pair(wfp, case):
+    import torch
+    prob = _problem(case["M"], case["width"], case["dt"], case.get("seam"))
+    prob["packets"] = np.array([[1.0, 0.2, 0.2, 0.0, 0.0]])
+    n = 12
+    dJdu = torch.randn((n, 3), generator=torch.Generator().manual_seed(3), dtype=torch.float64).cuda()
+    out = []
+    for mode in (1, 3):
+        plan = wfp.Plan(prob, case["dt"], p=case.get("p", 8), local_mode=mode, checkpoint_every=5)
+        u = torch.empty((n, 3), dtype=torch.float64, device="cuda")
+        plan.run(n, None, 1, u)
+        out.append(plan.gradient(dJdu))
+        plan.close()
+    # the gradients sum n levels of such terms
+    for a, b in zip(out[1], out[0]):
+        assert _rel(a, b) < LOCAL_TOL * math.sqrt(n)
