@@ -111,6 +111,7 @@ InstDesc describe(const wfp_plan* P) {
   d.sw = P->sw;
   d.tw = P->tw;
   d.tw1 = P->tw1;
+  d.spread_lanes = P->spread_lanes;
   d.T1 = P->T1;
   d.V = P->V;
   d.grid2 = P->grid2;
@@ -272,8 +273,8 @@ void build_batch(wfp_batch* B) {
       B->max_sweeps = std::max(B->max_sweeps, P->iters);
     }
     if (P->hist_threads != 256) fail(WFP_EDOMAIN, "batched instances need fine grids of at most 1024 butterflies per row stage");
-    B->lds_a = std::max(B->lds_a, (size_t)P->n2 * sizeof(double2));
-    B->lds_b = std::max(B->lds_b, 6 * (size_t)P->n1 * sizeof(double2) + 16 * (size_t)P->n1 * sizeof(double4));
+    B->lds_a = std::max(B->lds_a, 3 * (size_t)P->n2 * sizeof(double2));
+    B->lds_b = std::max(B->lds_b, P->lds_b);
     B->lds_til = std::max(B->lds_til, P->lds_jac);
   }
   // sweep lists: global-solve instances by decreasing sweep count
@@ -357,7 +358,7 @@ void enqueue_level(wfp_batch* B) {
     bc.work = B->wl_a;
     hipLaunchKernelGGL(kb_hist_a, dim3(B->n_a), dim3(256), B->lds_a, c, bc, B->spread_pass);
     bc.work = B->wl_b;
-    hipLaunchKernelGGL(kb_hist_b, dim3(B->n_b), dim3(512), B->lds_b, c, bc);
+    hipLaunchKernelGGL(kb_hist_b, dim3(B->n_b), dim3(kHistBThreads), B->lds_b, c, bc);
     bc.work = B->wl_c;
     hipLaunchKernelGGL(kb_hist_c, dim3(B->n_c), dim3(256), B->lds_c, c, bc);
     HIPCHK(hipEventRecord(B->ev_join, c));

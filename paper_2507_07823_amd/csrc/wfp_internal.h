@@ -156,7 +156,7 @@ struct wfp_plan {
   int hist_threads = 256;
   double* gsp = nullptr;    // spread grid of the 1024-thread row passes (nf)
   // FIR tap groups of the column pass and its LDS bytes
-  int fir_groups = 8;
+  int spread_lanes = 1;     // lanes that share a fine-grid cell's sources in the spreading
   size_t lds_b = 0;
   // boundary projection over workgroups for long grids: K = rbc_a rbc_b
   bool rbc_split = false;

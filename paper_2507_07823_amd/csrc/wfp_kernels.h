@@ -9,6 +9,8 @@ namespace wfp {
 constexpr int kMaxFftStages = 24;
 constexpr int kFftThreads = 1024;
 constexpr int kFftMaxB = 4;          // butterflies per thread per stage
+constexpr int kHistBThreads = 512;   // the column pass: one thread per mode of a column pair (2 n1 <= 512)
+constexpr int kSpreadSources = 6;    // sources a lane spreads onto a cell, on average (at most 64 lanes a cell)
 constexpr int kMaxP = 12;            // largest supported interpolation order
 constexpr int kRowThreads = 256;     // 4 wavefronts -> 4 target rows per block
 
@@ -232,25 +234,24 @@ __global__ void k_receivers(int M, int NQ, int NH, int64_t L, const int* __restr
 // ---- history part as three kernels (four-step transform, n = n1 n2) ----
 __global__ void k_hist_a(FftPlan f2, int n1, const double* __restrict__ sig, int M,
                          const int* __restrict__ cstart, const int* __restrict__ ccount,
-                         const int64_t* __restrict__ woff, const double* __restrict__ sw,
+                         const int64_t* __restrict__ woff, const double* __restrict__ sw, int lpc,
                          const double2* __restrict__ tw, double2* __restrict__ T1, ExtraSources ex);
-// FIR taps split over G groups whose partial sums meet in LDS ([G][2 n1] double4)
 __global__ void k_hist_b(int mode, FftPlan f1, int n2, int64_t K, int W, int64_t L, int64_t npos,
                          const double2* __restrict__ T1, const double2* __restrict__ tw,
                          const double2* __restrict__ tw1, const double* __restrict__ dk1, const double* __restrict__ dk2,
                          const double* __restrict__ pk, const double* __restrict__ qk,
                          const double* __restrict__ rot, double2* __restrict__ ring,
                          double2* __restrict__ alpha, double2* __restrict__ dalpha, double2* __restrict__ y,
-                         double2* __restrict__ V, int G, int vcol);
+                         double2* __restrict__ V, int vcol);
 __global__ void k_hist_c(FftPlan f2, int n1, const double2* __restrict__ V, const double2* __restrict__ tw,
                          double2* __restrict__ grid2);
-// the same row passes with 1024 threads, for rows of more than 1024 butterflies per stage at 256
+// the same row passes with 1024 threads, for rows of 1024 points or more
 __global__ void k_hist_a_wide(FftPlan f2, int n1, const double* __restrict__ grid, const double2* __restrict__ tw,
                               double2* __restrict__ T1);
-// type-1 spreading, one thread per fine-grid cell (feeds k_hist_a_wide)
+// type-1 spreading, lpc lanes per fine-grid cell (feeds k_hist_a_wide)
 __global__ void k_spread_grid(int nf, const double* __restrict__ sig, int M, const int* __restrict__ cstart,
                               const int* __restrict__ ccount, const int64_t* __restrict__ woff,
-                              const double* __restrict__ sw, ExtraSources ex, double* __restrict__ grid);
+                              const double* __restrict__ sw, int lpc, ExtraSources ex, double* __restrict__ grid);
 __global__ void k_hist_c_wide(FftPlan f2, int n1, const double2* __restrict__ V, const double2* __restrict__ tw,
                               double2* __restrict__ grid2);
 
@@ -331,6 +332,7 @@ struct InstDesc {
   const double* sw;
   const double2* tw;
   const double2* tw1;
+  int spread_lanes;
   double2 *T1, *V;
   double* grid2;
   double* gsp;                 // fine grid spread by a separate pass (batched spread_pass 1)

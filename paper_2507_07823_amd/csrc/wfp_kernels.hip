@@ -178,6 +178,47 @@ __device__ void fft_batch(double2* buf, int nb, const FftPlan& fp, const double2
   }
 }
 
+// The same transforms for short rows, for latency: the stages alternate between
+// two buffers (one barrier a stage instead of two, and no butterfly held in
+// registers across it), the n n-th roots of unity sit in LDS (a gather from
+// the L2 per stage costs more than the stage's arithmetic), and the index
+// divisions go through a float reciprocal, exact for j < 2^13.  At most two
+// rows.  Returns the buffer that holds the result.
+template <int R>
+__device__ __forceinline__ void fft_pp_stage(const double2* src, double2* dst, int n, int nb, int Ns,
+                                             const double2* w) {
+  const int per = n / R, step = per / Ns;
+  const float rNs = 1.0f / (float)Ns;
+  for (int idx = threadIdx.x; idx < per * nb; idx += blockDim.x) {
+    const int b = idx >= per ? 1 : 0, j = idx - b * per;
+    const int jq = (int)(((float)j + 0.5f) * rNs), k = j - jq * Ns;
+    double2 v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = src[b * n + j + r * per];
+#pragma unroll
+    for (int r = 1; r < R; ++r) v[r] = cmul(v[r], w[r * k * step]);
+    butterfly<R>(v);
+#pragma unroll
+    for (int r = 0; r < R; ++r) dst[b * n + jq * Ns * R + k + r * Ns] = v[r];
+  }
+  __syncthreads();
+}
+
+__device__ __forceinline__ double2* fft_pp(double2* src, double2* alt, int nb, const FftPlan& fp, const double2* w) {
+  int Ns = 1;
+  for (int s = 0; s < fp.nst; ++s) {
+    const int R = fp.radix[s];
+    if (R == 4) fft_pp_stage<4>(src, alt, fp.n, nb, Ns, w);
+    else if (R == 5) fft_pp_stage<5>(src, alt, fp.n, nb, Ns, w);
+    else fft_pp_stage<2>(src, alt, fp.n, nb, Ns, w);
+    Ns *= R;
+    double2* t = src;
+    src = alt;
+    alt = t;
+  }
+  return src;
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -464,6 +505,8 @@ __device__ __forceinline__ double interp_pre(int j, const int* __restrict__ i0s,
   int i = i0s[j] % nf;
   if (i < 0) i += nf;
   double uh = 0.0;
+  // the loads of eight cells before their first use: one wait on memory, not eight
+#pragma unroll 8
   for (int q = 0; q < width; ++q) {
     uh = fma(w[(int64_t)j * width + q], grid2[i], uh);
     if (++i == nf) i = 0;
@@ -1739,12 +1782,19 @@ __device__ __forceinline__ void k_solve_direct_body(int M, const int* __restrict
   const int e = threadIdx.x;
   int g = g0 + e;
   if (g >= M) g -= M;
-  if (e < n) c[e] = (ginc[g] - loc[g]) - beta[g] * interp_pre(g, i0s, iw, grid2, nf, width);
+  int cs = 0, cn = 0;
+  const double* __restrict__ row = inv;
+  if (e < n) {
+    // the run's row is requested with the right-hand side
+    cs = pt_cs[p0 + e];
+    cn = pt_cn[p0 + e];
+    row = inv + pt_inv[p0 + e];
+    c[e] = (ginc[g] - loc[g]) - beta[g] * interp_pre(g, i0s, iw, grid2, nf, width);
+  }
   __syncthreads();
   if (e < n) {
-    const int cs = pt_cs[p0 + e], cn = pt_cn[p0 + e];
-    const double* __restrict__ row = inv + pt_inv[p0 + e];
     double acc = 0.0;
+#pragma unroll 4
     for (int k = 0; k < cn; ++k) acc = fma(row[k], c[cs + k], acc);
     sig_out[g] = acc;
     if (save_row) save_row[perm[g]] = acc;
@@ -2027,81 +2077,99 @@ k_rbc_modes_unpack(int64_t K, int n1, int n2, const double2* __restrict__ X, con
 //    run the first inverse step (FFT over k1, twiddle) -> V[j1][k2].
 // C: for one j1, inverse FFT over k2 -> z_{j1 + n1 j2} -> grid cells.
 // ===========================================================================
-__device__ __forceinline__ double spread_cell(int cell, const double* __restrict__ sig, int M,
+// Value of one fine-grid cell, the sources split over `lpc` neighbouring lanes
+// (a power of two; `sub` is this lane's place): the plan takes at most six
+// sources a lane on average, so that no lane waits for a long chain of loads and
+// the weight loads of a cell coalesce (one lane a cell against this: the spread
+// and row pass 14.3 / 12.6 us at M = 1e4 and 12.5 sources a cell, 39.5 / 33.2 at
+// 4e4, 135 / 104 at 1e6).  Every lane of the group gets the sum.
+__device__ __forceinline__ double spread_cell(int cell, int sub, int lpc, const double* __restrict__ sig, int M,
                                               const int* __restrict__ cstart, const int* __restrict__ ccount,
                                               const int64_t* __restrict__ woff, const double* __restrict__ sw) {
   const int st = cstart[cell], cnt = ccount[cell];
   const double* __restrict__ w = sw + woff[cell];
   double acc = 0.0;
-  for (int c = 0; c < cnt; ++c) {
+#pragma unroll 4
+  for (int c = sub; c < cnt; c += lpc) {
     int j = st + c;
     if (j >= M) j -= M;
     acc = fma(sig[j], w[c], acc);
   }
+  for (int o = 1; o < lpc; o <<= 1) acc += __shfl_xor(acc, o, 64);
   return acc;
 }
 
+// Row pass of the forward transform for rows of n2 < 1024: the row's 2 n2 cells
+// spread by the block (or read from `grid`), the transform with its roots in
+// LDS.  A chain of latencies, not of bytes: the roots, the output's twiddle
+// factors and the cell lists are requested together.
 __device__ __forceinline__ void k_hist_a_body(FftPlan f2, int n1, const double* __restrict__ sig, int M, const int* __restrict__ cstart,
-         const int* __restrict__ ccount, const int64_t* __restrict__ woff, const double* __restrict__ sw,
+         const int* __restrict__ ccount, const int64_t* __restrict__ woff, const double* __restrict__ sw, int lpc,
          const double2* __restrict__ tw, double2* __restrict__ T1, ExtraSources ex, int bid,
          const double* __restrict__ grid = nullptr) {
   extern __shared__ double2 buf[];
   const int n2 = f2.n, j1 = bid;
-  const int n = n1 * n2;
+  double2* w = buf + 2 * n2;
   double* bd = (double*)buf;
-  for (int c = threadIdx.x; c < 2 * n2; c += blockDim.x) {
-    const int cell = 2 * (j1 + n1 * (c >> 1)) + (c & 1);
-    if (grid) {
-      bd[c] = grid[cell];   // spread beforehand by k_spread_grid
-      continue;
+  for (int k = threadIdx.x; k < n2; k += blockDim.x) w[k] = tw[(int64_t)2 * n1 * k];
+  if (grid) {
+    for (int c = threadIdx.x; c < 2 * n2; c += blockDim.x)
+      bd[c] = grid[2 * (j1 + n1 * (c >> 1)) + (c & 1)];   // spread beforehand by k_spread_grid
+  } else {
+    const int sh = __ffs(lpc) - 1, sub = threadIdx.x & (lpc - 1);
+    // a whole number of lane groups: the lanes of a cell stay together
+    for (int it = threadIdx.x; it < 2 * n2 * lpc; it += blockDim.x) {
+      const int c = it >> sh, cell = 2 * (j1 + n1 * (c >> 1)) + (c & 1);
+      double v = spread_cell(cell, sub, lpc, sig, M, cstart, ccount, woff, sw);
+      if (ex.val) v += spread_cell(cell, sub, lpc, ex.val, ex.n, ex.cstart, ex.ccount, ex.woff, ex.w);
+      if (sub == 0) bd[c] = v;
     }
-    double v = spread_cell(cell, sig, M, cstart, ccount, woff, sw);
-    if (ex.val) v += spread_cell(cell, ex.val, ex.n, ex.cstart, ex.ccount, ex.woff, ex.w);
-    bd[c] = v;
   }
   __syncthreads();
-  fft_batch(buf, 1, f2, tw, 2 * n1);
-  for (int k2 = threadIdx.x; k2 < n2; k2 += blockDim.x) {
-    const int q = j1 * k2;                 // < n
-    T1[(int64_t)k2 * n1 + j1] = cmul(buf[k2], tw[2 * (q % n)]);
-  }
+  const double2* X = fft_pp(buf, buf + n2, 1, f2, w);
+  for (int k2 = threadIdx.x; k2 < n2; k2 += blockDim.x)
+    T1[(int64_t)k2 * n1 + j1] = cmul(X[k2], tw[2 * (j1 * k2)]);   // j1 k2 < n1 n2
 }
 
 __global__ void __launch_bounds__(256)
 k_hist_a(FftPlan f2, int n1, const double* __restrict__ sig, int M, const int* __restrict__ cstart,
-         const int* __restrict__ ccount, const int64_t* __restrict__ woff, const double* __restrict__ sw,
+         const int* __restrict__ ccount, const int64_t* __restrict__ woff, const double* __restrict__ sw, int lpc,
          const double2* __restrict__ tw, double2* __restrict__ T1, ExtraSources ex) {
-  k_hist_a_body(f2, n1, sig, M, cstart, ccount, woff, sw, tw, T1, ex, blockIdx.x);
+  k_hist_a_body(f2, n1, sig, M, cstart, ccount, woff, sw, lpc, tw, T1, ex, blockIdx.x);
 }
 
-// Rows longer than 1024 butterflies per stage for 256 threads take 1024 threads.
-// Long rows: the cells are spread beforehand into `grid` by k_spread_grid (one
-// thread per cell, coalesced), and the rows are read from it; blocks of
+// Rows of n2 >= 1024 take 1024 threads.  The cells are spread beforehand into
+// `grid` by k_spread_grid (coalesced), and the rows are read from it; blocks of
 // neighbouring rows share the grid's cache lines, so they run on one XCD.  The
 // grid is padded to a multiple of 8 blocks (the remap's bijection); blocks
 // past the last row return as a whole, before any barrier.
 __global__ void __launch_bounds__(1024)
 k_hist_a_wide(FftPlan f2, int n1, const double* __restrict__ grid, const double2* __restrict__ tw,
               double2* __restrict__ T1) {
+  extern __shared__ double2 buf[];
   const int j1 = xcd_block(blockIdx.x, gridDim.x);
   if (j1 >= n1) return;
-  const ExtraSources none{nullptr, 0, nullptr, nullptr, nullptr, nullptr};
-  k_hist_a_body(f2, n1, nullptr, 0, nullptr, nullptr, nullptr, nullptr, tw, T1, none, j1, grid);
+  const int n2 = f2.n;
+  const double2* __restrict__ row = (const double2*)grid + j1;
+  for (int c = threadIdx.x; c < n2; c += blockDim.x) buf[c] = row[(int64_t)n1 * c];
+  __syncthreads();
+  fft_batch(buf, 1, f2, tw, 2 * n1);
+  for (int k2 = threadIdx.x; k2 < n2; k2 += blockDim.x)
+    T1[(int64_t)k2 * n1 + j1] = cmul(buf[k2], tw[2 * (j1 * k2)]);   // j1 k2 < n1 n2
 }
 
-// Type-1 spreading onto the fine grid, one thread per cell.
+// Type-1 spreading onto the fine grid, lpc lanes per cell.
 __global__ void __launch_bounds__(256)
 k_spread_grid(int nf, const double* __restrict__ sig, int M, const int* __restrict__ cstart,
               const int* __restrict__ ccount, const int64_t* __restrict__ woff, const double* __restrict__ sw,
-              ExtraSources ex, double* __restrict__ grid) {
-  const int cell = blockIdx.x * blockDim.x + threadIdx.x;
-  if (cell >= nf) return;
-  double v = spread_cell(cell, sig, M, cstart, ccount, woff, sw);
-  if (ex.val) v += spread_cell(cell, ex.val, ex.n, ex.cstart, ex.ccount, ex.woff, ex.w);
-  grid[cell] = v;
+              int lpc, ExtraSources ex, double* __restrict__ grid) {
+  const int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int cell = (int)(it >> (__ffs(lpc) - 1)), sub = threadIdx.x & (lpc - 1);
+  if (cell >= nf) return;   // whole groups of lpc lanes
+  double v = spread_cell(cell, sub, lpc, sig, M, cstart, ccount, woff, sw);
+  if (ex.val) v += spread_cell(cell, sub, lpc, ex.val, ex.n, ex.cstart, ex.ccount, ex.woff, ex.w);
+  if (sub == 0) grid[cell] = v;
 }
-
-constexpr int kFirGroups = 8;
 
 // Partner of position (c, k1) in the column pair: where Z_{n - q} sits, q = col[c] + n2 k1.
 __device__ __forceinline__ int partner(int c, int k1, int k2c, int ncol, int n1) {
@@ -2113,61 +2181,81 @@ __device__ __forceinline__ int partner(int c, int k1, int k2c, int ncol, int n1)
 // mode 0: forward step 2 + modes + inverse step 1; mode 1: forward step 2 +
 // modes, writing y (the type-2 input) for a later projection; mode 2: inverse
 // step 1 from y.
+// The block's 512 threads hold the np <= 512 modes of a column pair one each,
+// and G = 512 / np threads share a mode's taps.  Short columns are a chain of
+// latencies, long ones stream the taps: everything that does not depend on
+// T1 (the tables of the thread's mode, the taps of the W - 1 older spectra,
+// the roots of unity) is requested before the transform, so the chain holds
+// one wait on memory.  The kernel alone on the chip, by events, against taps
+// summed after the transform with roots and tables gathered where they are
+// used: 17.1 us for 28.1 (K = 24000, columns of 200), 12.4 for 19.6 (K = 3141),
+// 166 for 246 (K = 524288).
 __device__ __forceinline__ void k_hist_b_body(int mode, FftPlan f1, int n2, int64_t K, int W, int64_t L, int64_t npos, const double2* __restrict__ T1,
          const double2* __restrict__ tw, const double2* __restrict__ tw1, const double* __restrict__ dk1, const double* __restrict__ dk2,
          const double* __restrict__ pk, const double* __restrict__ qk, const double* __restrict__ rot,
          double2* __restrict__ ring, double2* __restrict__ alpha, double2* __restrict__ dalpha,
-         double2* __restrict__ y, double2* __restrict__ V, int G, int bid, int vcol = 0) {
+         double2* __restrict__ y, double2* __restrict__ V, int bid, int vcol = 0) {
   extern __shared__ double2 smb[];
   const int n1 = f1.n;
-  const int n = n1 * n2;
-  double2* buf = smb;                         // [2][n1]
-  double2* yl = smb + 2 * n1;                 // [2][n1]
-  double2* sS = smb + 4 * n1;                 // [2][n1]
-  double4* red = (double4*)(smb + 6 * n1);    // [G][2 n1]
+  double2* bufA = smb;                        // [2][n1]
+  double2* bufB = smb + 2 * n1;               // [2][n1]
+  double2* wr = smb + 4 * n1;                 // [n1] e^{-2 pi i q / n1}
+  double4* red = (double4*)(smb + 5 * n1 + (n1 & 1));   // [G][np], G np <= 512
   const int k2a = bid, k2b = (n2 - k2a) % n2;
   const int ncol = (k2a == k2b) ? 1 : 2;
   const int np = ncol * n1;
-  const int64_t stride = npos;
-  const int64_t pb = (int64_t)k2a * 2 * n1;   // position of this block's first mode
-  auto colk2 = [&](int c) { return c == 0 ? k2a : k2b; };
+  const int tid = threadIdx.x;
+  const bool own = tid < np;                  // holds mode e = tid
+  // this thread's element: column c, place k1, mode q at position pb + e
+  const int G = kHistBThreads / np;
+  const int g = tid / np, e = tid - g * np;
+  const int c = e >= n1 ? 1 : 0, k1 = e - c * n1;
+  const int k2 = c ? k2b : k2a;
+  const int64_t q = k2 + (int64_t)n2 * k1;
+  const bool live = q <= K;
+  const int64_t ps = (int64_t)k2a * 2 * n1 + e;
+  double2 t1 = make_double2(0.0, 0.0);
+  if (own && mode != 2) t1 = T1[(int64_t)k2 * n1 + k1];
+  double2 yq = make_double2(0.0, 0.0);
+  if (own && mode == 2 && live) yq = y[q];
+  if (tid < n1) {
+    // e^{-2 pi i k1 / (2 n1)} at even places, and its negative half a turn on
+    const int h = 2 * tid < n1 ? 2 * tid : 2 * tid - n1;
+    const double2 v = tw1[h];
+    wr[tid] = 2 * tid < n1 ? v : make_double2(-v.x, -v.y);
+  }
+  // e^{-2 pi i q / N} = e^{-2 pi i k2 / N} e^{-2 pi i k1 / (2 n1)}: the column's
+  // factor and a short table instead of a stride-n2 gather; and the twiddle of V
+  double2 tq = make_double2(0.0, 0.0), tv = tq;
+  if (own) {
+    tq = cmul(tw[k2], tw1[k1]);
+    tv = tw[2 * (k1 * k2)];                   // k1 k2 < n1 n2
+  }
   if (mode != 2) {
-    for (int e = threadIdx.x; e < np; e += blockDim.x) {
-      const int c = e / n1, k1 = e - c * n1;
-      buf[e] = T1[(int64_t)colk2(c) * n1 + k1];
-    }
-    __syncthreads();
-    fft_batch(buf, ncol, f1, tw, 2 * n2);
     const int64_t nn = L - 1;
-    // spectra S_q of the modes q <= K held by this block
-    for (int e = threadIdx.x; e < np; e += blockDim.x) {
-      const int c = e / n1, k1 = e - c * n1;
-      const int64_t q = colk2(c) + (int64_t)n2 * k1;
-      double2 S = make_double2(0.0, 0.0);
-      if (q <= K) {
-        const double2 zk = buf[e];
-        const double2 zc = cconj(buf[partner(c, k1, k2a, ncol, n1)]);
-        const double2 E = cscale(cadd(zk, zc), 0.5);
-        const double2 O = cscale(cmul_mi(csub(zk, zc)), 0.5);
-        // e^{-2 pi i q / N} = e^{-2 pi i k2 / N} e^{-2 pi i k1 / (2 n1)}: the column's
-        // factor and a short table instead of a stride-n2 gather
-        const double2 X = cadd(E, cmul(cmul(tw[colk2(c)], tw1[k1]), O));
-        S = cscale(cconj(X), dk1[pb + e]);
-      }
-      sS[e] = S;
+    const int sn = mod_slot(nn, W);
+    double d1 = 0.0, d2 = 0.0, p0 = 0.0, q0 = 0.0, cr = 0.0, sr = 0.0, rr = 0.0;
+    double2 a = make_double2(0.0, 0.0), da = a;
+    if (own && live) {
+      d1 = dk1[ps];
+      d2 = dk2[ps];
+      p0 = pk[ps];
+      q0 = qk[ps];
+      cr = rot[3 * ps];
+      sr = rot[3 * ps + 1];
+      rr = rot[3 * ps + 2];
+      a = alpha[ps];
+      da = dalpha[ps];
     }
-    __syncthreads();
-    // FIR partial sums: work item (e, g) takes taps m = g, g + G, ...
-    for (int wi = threadIdx.x; wi < np * G; wi += blockDim.x) {
-      const int g = wi / np, e = wi - g * np;
-      const int c = e / n1, k1 = e - c * n1;
-      const int64_t q = colk2(c) + (int64_t)n2 * k1;
-      double4 acc = make_double4(0.0, 0.0, 0.0, 0.0);
-      if (q <= K) {
-#pragma unroll 2
-        for (int m = g; m < W; m += G) {
-          const double2 Sm = (m == 0) ? sS[e] : ring[(int64_t)mod_slot(nn - m, W) * stride + pb + e];
-          const double p = pk[(int64_t)m * stride + pb + e], qq = qk[(int64_t)m * stride + pb + e];
+    // FIR sums of the older spectra: taps m = 1 + g, 1 + g + G, ...
+    double4 acc = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (g < G) {
+      if (live) {
+#pragma unroll 6
+        for (int m = 1 + g; m < W; m += G) {
+          const int sl = sn >= m ? sn - m : sn - m + W;
+          const double2 Sm = ring[(int64_t)sl * npos + ps];
+          const double p = pk[(int64_t)m * npos + ps], qq = qk[(int64_t)m * npos + ps];
           acc.x = fma(p, Sm.x, acc.x);
           acc.y = fma(p, Sm.y, acc.y);
           acc.z = fma(qq, Sm.x, acc.z);
@@ -2176,85 +2264,78 @@ __device__ __forceinline__ void k_hist_b_body(int mode, FftPlan f1, int n2, int6
       }
       red[g * np + e] = acc;
     }
+    if (own) bufA[e] = t1;
     __syncthreads();
-    for (int e = threadIdx.x; e < np; e += blockDim.x) {
-      const int c = e / n1, k1 = e - c * n1;
-      const int64_t q = colk2(c) + (int64_t)n2 * k1;
-      double2 yq = make_double2(0.0, 0.0);
-      if (q <= K) {
-        double2 h = make_double2(0.0, 0.0), g = make_double2(0.0, 0.0);
-        for (int gg = 0; gg < G; ++gg) {
-          const double4 v = red[gg * np + e];
-          h.x += v.x;
-          h.y += v.y;
-          g.x += v.z;
-          g.y += v.w;
-        }
-        const int64_t ps = pb + e;
-        ring[(int64_t)mod_slot(nn, W) * stride + ps] = sS[e];
-        const double cr = rot[3 * ps], sr = rot[3 * ps + 1], rr = rot[3 * ps + 2];
-        const double2 a = alpha[ps], da = dalpha[ps];
-        const double2 an = make_double2(cr * a.x + sr * da.x + h.x, cr * a.y + sr * da.y + h.y);
-        const double2 dan = make_double2(rr * a.x + cr * da.x + g.x, rr * a.y + cr * da.y + g.y);
-        alpha[ps] = an;
-        dalpha[ps] = dan;
-        yq = cscale(cconj(an), dk2[ps]);
-        if (mode == 1) y[q] = yq;
+    const double2* X = fft_pp(bufA, bufB, ncol, f1, wr);
+    if (own && live) {
+      // the spectrum S_q, and the mode's new values
+      const double2 zk = X[e];
+      const double2 zc = cconj(X[partner(c, k1, k2a, ncol, n1)]);
+      const double2 E = cscale(cadd(zk, zc), 0.5);
+      const double2 O = cscale(cmul_mi(csub(zk, zc)), 0.5);
+      const double2 S = cscale(cconj(cadd(E, cmul(tq, O))), d1);
+      ring[(int64_t)sn * npos + ps] = S;
+      double2 h = cscale(S, p0), gs = cscale(S, q0);
+      for (int gg = 0; gg < G; ++gg) {
+        const double4 v = red[gg * np + e];
+        h.x += v.x;
+        h.y += v.y;
+        gs.x += v.z;
+        gs.y += v.w;
       }
-      yl[e] = yq;
+      const double2 an = make_double2(cr * a.x + sr * da.x + h.x, cr * a.y + sr * da.y + h.y);
+      alpha[ps] = an;
+      dalpha[ps] = make_double2(rr * a.x + cr * da.x + gs.x, rr * a.y + cr * da.y + gs.y);
+      yq = cscale(cconj(an), d2);
+      if (mode == 1) y[q] = yq;
     }
     if (mode == 1) return;   // block-uniform
-  } else {
-    for (int e = threadIdx.x; e < np; e += blockDim.x) {
-      const int c = e / n1, k1 = e - c * n1;
-      const int64_t q = colk2(c) + (int64_t)n2 * k1;
-      yl[e] = (q <= K) ? y[q] : make_double2(0.0, 0.0);
-    }
+    // y goes to the buffer that X does not use
+    bufA = X == bufA ? bufB : bufA;
+    bufB = smb + (bufA == smb ? 2 * n1 : 0);
+  }
+  if (own) bufA[e] = yq;
+  __syncthreads();
+  // pack: Z'_q = (y_q + conj(y_{n-q})) + i e^{+2 pi i q/N} (y_q - conj(y_{n-q})); conj(Z') is transformed
+  if (own) {
+    const double2 ym = (q == 0) ? make_double2(0.0, 0.0) : cconj(bufA[partner(c, k1, k2a, ncol, n1)]);
+    bufB[e] = cconj(cadd(cadd(yq, ym), cmul_pi(cmul(cconj(tq), csub(yq, ym)))));
   }
   __syncthreads();
-  // pack: Z'_q = (y_q + conj(y_{n-q})) + i e^{+2 pi i q/N} (y_q - conj(y_{n-q})); buf = conj(Z')
-  for (int e = threadIdx.x; e < np; e += blockDim.x) {
-    const int c = e / n1, k1 = e - c * n1;
-    const int q = colk2(c) + n2 * k1;
-    const double2 yk = yl[e];
-    const double2 ym = (q == 0) ? make_double2(0.0, 0.0) : cconj(yl[partner(c, k1, k2a, ncol, n1)]);
-    const double2 zq = cadd(cadd(yk, ym), cmul_pi(cmul(cconj(cmul(tw[colk2(c)], tw1[k1])), csub(yk, ym))));
-    buf[e] = cconj(zq);
-  }
-  __syncthreads();
-  fft_batch(buf, ncol, f1, tw, 2 * n2);
-  // V[j1][k2] = conj(buf) * e^{+2 pi i j1 k2 / n}
-  for (int e = threadIdx.x; e < np; e += blockDim.x) {
-    const int c = e / n1, j1 = e - c * n1;
-    const int k2 = colk2(c);
-    const int qq = (j1 * k2) % n;
-    const double2 v = cmul(cconj(buf[e]), cconj(tw[2 * qq]));
-    if (vcol) V[(int64_t)k2 * n1 + j1] = v;   // column-major: this column contiguous
-    else V[(int64_t)j1 * n2 + k2] = v;
+  const double2* Z = fft_pp(bufB, bufA, ncol, f1, wr);
+  // V[j1][k2] = conj(Z) * e^{+2 pi i j1 k2 / n}, j1 in k1's place
+  if (own) {
+    const double2 v = cmul(cconj(Z[e]), cconj(tv));
+    if (vcol) V[(int64_t)k2 * n1 + k1] = v;   // column-major: this column contiguous
+    else V[(int64_t)k1 * n2 + k2] = v;
   }
 }
 
 // at most 128 VGPRs, so that two blocks share a compute unit: the chain runs
 // its n2/2 + 1 blocks on one XCD's 32 compute units in one round
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(kHistBThreads) __attribute__((amdgpu_waves_per_eu(4)))
 k_hist_b(int mode, FftPlan f1, int n2, int64_t K, int W, int64_t L, int64_t npos, const double2* __restrict__ T1,
          const double2* __restrict__ tw, const double2* __restrict__ tw1, const double* __restrict__ dk1,
          const double* __restrict__ dk2, const double* __restrict__ pk, const double* __restrict__ qk,
          const double* __restrict__ rot, double2* __restrict__ ring, double2* __restrict__ alpha,
-         double2* __restrict__ dalpha, double2* __restrict__ y, double2* __restrict__ V, int G, int vcol) {
-  k_hist_b_body(mode, f1, n2, K, W, L, npos, T1, tw, tw1, dk1, dk2, pk, qk, rot, ring, alpha, dalpha, y, V, G,
+         double2* __restrict__ dalpha, double2* __restrict__ y, double2* __restrict__ V, int vcol) {
+  k_hist_b_body(mode, f1, n2, K, W, L, npos, T1, tw, tw1, dk1, dk2, pk, qk, rot, ring, alpha, dalpha, y, V,
                 blockIdx.x, vcol);
 }
 
+// Row pass of the inverse transform, n2 < 1024: the counterpart of k_hist_a.
 __device__ __forceinline__ void k_hist_c_body(FftPlan f2, int n1, const double2* __restrict__ V, const double2* __restrict__ tw,
-         double2* __restrict__ grid2, int bid, int vcol = 0) {
+         double2* __restrict__ grid2, int bid) {
   extern __shared__ double2 buf[];
   const int n2 = f2.n, j1 = bid;
-  for (int k2 = threadIdx.x; k2 < n2; k2 += blockDim.x)
-    buf[k2] = cconj(vcol ? V[(int64_t)k2 * n1 + j1] : V[(int64_t)j1 * n2 + k2]);
+  double2* w = buf + 2 * n2;
+  for (int k = threadIdx.x; k < n2; k += blockDim.x) {
+    buf[k] = cconj(V[(int64_t)j1 * n2 + k]);
+    w[k] = tw[(int64_t)2 * n1 * k];
+  }
   __syncthreads();
-  fft_batch(buf, 1, f2, tw, 2 * n1);
-  for (int j2 = threadIdx.x; j2 < n2; j2 += blockDim.x) grid2[j1 + n1 * j2] = cconj(buf[j2]);
+  const double2* Z = fft_pp(buf, buf + n2, 1, f2, w);
+  for (int j2 = threadIdx.x; j2 < n2; j2 += blockDim.x) grid2[j1 + n1 * j2] = cconj(Z[j2]);
 }
 
 __global__ void __launch_bounds__(256)
@@ -2271,7 +2352,12 @@ k_hist_c_wide(FftPlan f2, int n1, const double2* __restrict__ V, const double2* 
   // 8 blocks and blocks past the last row return as a whole
   const int j1 = xcd_block(blockIdx.x, gridDim.x);
   if (j1 >= n1) return;
-  k_hist_c_body(f2, n1, V, tw, grid2, j1, 1);
+  extern __shared__ double2 buf[];
+  const int n2 = f2.n;
+  for (int k2 = threadIdx.x; k2 < n2; k2 += blockDim.x) buf[k2] = cconj(V[(int64_t)k2 * n1 + j1]);
+  __syncthreads();
+  fft_batch(buf, 1, f2, tw, 2 * n1);
+  for (int j2 = threadIdx.x; j2 < n2; j2 += blockDim.x) grid2[j1 + n1 * j2] = cconj(buf[j2]);
 }
 
 // ---------------------------------------------------------------------------
@@ -2488,7 +2574,7 @@ __global__ void __launch_bounds__(256) kb_spread_grid(BatchLaunch b) {
   const int cell = w.y * 256 + (int)threadIdx.x;
   if (cell >= d.nf) return;
   const double* sig = d.hist + (int64_t)mod_slot(*b.level - 1, d.NH) * d.M;
-  d.gsp[cell] = spread_cell(cell, sig, d.M, d.cstart, d.ccount, d.swoff, d.sw);
+  d.gsp[cell] = spread_cell(cell, 0, 1, sig, d.M, d.cstart, d.ccount, d.swoff, d.sw);
 }
 
 // Row pass of the fine-grid transform; from_grid = 0 spreads the row's cells
@@ -2500,20 +2586,20 @@ __global__ void __launch_bounds__(256) kb_hist_a(BatchLaunch b, int from_grid) {
   if (*b.level >= d.end) return;   // the instance has marched its own levels (block-uniform)
   const ExtraSources none{nullptr, 0, nullptr, nullptr, nullptr, nullptr};
   if (from_grid) {
-    k_hist_a_body(d.f2, d.n1, nullptr, 0, nullptr, nullptr, nullptr, nullptr, d.tw, d.T1, none, w.y, d.gsp);
+    k_hist_a_body(d.f2, d.n1, nullptr, 0, nullptr, nullptr, nullptr, nullptr, 1, d.tw, d.T1, none, w.y, d.gsp);
     return;
   }
   const double* sig = d.hist + (int64_t)mod_slot(*b.level - 1, d.NH) * d.M;
-  k_hist_a_body(d.f2, d.n1, sig, d.M, d.cstart, d.ccount, d.swoff, d.sw, d.tw, d.T1, none, w.y);
+  k_hist_a_body(d.f2, d.n1, sig, d.M, d.cstart, d.ccount, d.swoff, d.sw, d.spread_lanes, d.tw, d.T1, none, w.y);
 }
 
-__global__ void __launch_bounds__(512) kb_hist_b(BatchLaunch b) {
+__global__ void __launch_bounds__(kHistBThreads) __attribute__((amdgpu_waves_per_eu(4))) kb_hist_b(BatchLaunch b) {
   const int2 w = b.work[blockIdx.x];
   if (w.x < 0) return;
   const InstDesc& d = b.desc[w.x];
   if (*b.level >= d.end) return;   // the instance has marched its own levels (block-uniform)
   k_hist_b_body(0, d.f1, d.n2, d.K, d.W, *b.level, d.npos, d.T1, d.tw, d.tw1, d.dk1, d.dk2, d.pk, d.qk, d.rot, d.ring,
-                d.alpha, d.dalpha, d.ybuf, d.V, kFirGroups, w.y);
+                d.alpha, d.dalpha, d.ybuf, d.V, w.y);
 }
 
 __global__ void __launch_bounds__(256) kb_hist_c(BatchLaunch b) {

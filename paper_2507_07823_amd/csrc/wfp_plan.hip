@@ -530,6 +530,8 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
     for (int i = 0; i < P->fft_n2.nst; ++i)
       if (P->n2 / P->fft_n2.radix[i] > kFftMaxB * 256) P->hist_threads = 1024;
     P->npos = (int64_t)(P->n2 / 2 + 1) * 2 * P->n1;
+    while (P->spread_lanes < 64 && (double)P->width * M > (double)kSpreadSources * P->spread_lanes * P->nf)
+      P->spread_lanes *= 2;
     // batched LDS stages run on 256 threads with at most kFftMaxB butterflies each
     for (int i = 0; i < P->fft_n1.nst; ++i)
       if (2 * P->n1 / P->fft_n1.radix[i] > kFftMaxB * 256) fail(WFP_EDOMAIN, "four-step factor n1 too long");
@@ -1412,13 +1414,9 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
     const int sdyn = (int)((size_t)(P->NQ + kOtfRows) * kOtfChunk * sizeof(double));
     for (const void* f : sfns) HIPCHK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, sdyn));
   }
-  // the column pass holds 6 n1 complex values and the FIR partial sums of G
-  // tap groups ([G][2 n1] double4); column pairs of 400 modes or more keep one
-  // or two modes per thread with G = 2 (and fit two blocks per compute unit),
-  // shorter ones split the taps 8 ways to give every thread work
-  P->fir_groups = 2 * P->n1 >= 400 ? 2 : 8;
-  P->lds_b = 6 * (size_t)P->n1 * sizeof(double2) + (size_t)P->fir_groups * 2 * P->n1 * sizeof(double4);
-  if (P->lds_b > 160 * 1024) fail(WFP_EDOMAIN, "four-step factor n1 too long for the history kernel's LDS");
+  // the column pass holds 5 n1 complex values (two buffers of a column pair and
+  // the roots) and one partial sum of the taps per thread
+  P->lds_b = (5 * (size_t)P->n1 + 1) * sizeof(double2) + kHistBThreads * sizeof(double4);
   {
     hipDeviceProp_t prop;
     HIPCHK(hipGetDeviceProperties(&prop, P->device));
@@ -1508,11 +1506,11 @@ StateRef main_state(wfp_plan* P) { return {P->hist, P->ring, P->alpha, P->dalpha
 void launch_hist_a(wfp_plan* P, hipStream_t s, const double* sig, ExtraSources ex) {
   const size_t lds = P->n2 * sizeof(double2);
   if (P->hist_threads == 256)
-    hipLaunchKernelGGL(k_hist_a, dim3(P->n1), dim3(256), lds, s, P->fft_n2, P->n1, sig, (int)P->M, P->cstart,
-                       P->ccount, P->swoff, P->sw, P->tw, P->T1, ex);
+    hipLaunchKernelGGL(k_hist_a, dim3(P->n1), dim3(256), 3 * lds, s, P->fft_n2, P->n1, sig, (int)P->M, P->cstart,
+                       P->ccount, P->swoff, P->sw, P->spread_lanes, P->tw, P->T1, ex);
   else {
-    hipLaunchKernelGGL(k_spread_grid, dim3(nblk(P->nf, 256)), dim3(256), 0, s, P->nf, sig, (int)P->M, P->cstart,
-                       P->ccount, P->swoff, P->sw, ex, P->gsp);
+    hipLaunchKernelGGL(k_spread_grid, dim3(nblk((int64_t)P->nf * P->spread_lanes, 256)), dim3(256), 0, s, P->nf, sig,
+                       (int)P->M, P->cstart, P->ccount, P->swoff, P->sw, P->spread_lanes, ex, P->gsp);
     hipLaunchKernelGGL(k_hist_a_wide, dim3(8 * nblk(P->n1, 8)), dim3(1024), lds, s, P->fft_n2, P->n1, P->gsp, P->tw,
                        P->T1);
   }
@@ -1521,7 +1519,7 @@ void launch_hist_a(wfp_plan* P, hipStream_t s, const double* sig, ExtraSources e
 void launch_hist_c(wfp_plan* P, hipStream_t s, double2* grid) {
   const size_t lds = P->n2 * sizeof(double2);
   if (P->hist_threads == 256)
-    hipLaunchKernelGGL(k_hist_c, dim3(P->n1), dim3(256), lds, s, P->fft_n2, P->n1, P->V, P->tw, grid);
+    hipLaunchKernelGGL(k_hist_c, dim3(P->n1), dim3(256), 3 * lds, s, P->fft_n2, P->n1, P->V, P->tw, grid);
   else
     hipLaunchKernelGGL(k_hist_c_wide, dim3(8 * nblk(P->n1, 8)), dim3(1024), lds, s, P->fft_n2, P->n1, P->V, P->tw,
                        grid);
@@ -1669,9 +1667,9 @@ void march_level(wfp_plan* P, const StateRef& S, int64_t L, bool driven, const E
   const bool rbc = !periodic && L > 0 && L % P->rbc_period == 0;
   {
     StageTimer st(P, WFP_STAGE_MODES, sc);
-    hipLaunchKernelGGL(k_hist_b, dim3(nb_b), dim3(512), lds_b, sc, rbc ? 1 : 0, P->fft_n1, P->n2, P->K, P->W, L,
+    hipLaunchKernelGGL(k_hist_b, dim3(nb_b), dim3(kHistBThreads), lds_b, sc, rbc ? 1 : 0, P->fft_n1, P->n2, P->K, P->W, L,
                        P->npos, P->T1, P->tw, P->tw1, P->dk1, P->dk2, P->pk, P->qk, P->rot, S.ring, S.alpha,
-                       S.dalpha, P->ybuf, P->V, P->fir_groups, P->hist_threads == 1024 ? 1 : 0);
+                       S.dalpha, P->ybuf, P->V, P->hist_threads == 1024 ? 1 : 0);
   }
   if (rbc) {
     StageTimer st(P, WFP_STAGE_RBC, sc);
@@ -1700,9 +1698,9 @@ void march_level(wfp_plan* P, const StateRef& S, int64_t L, bool driven, const E
       hipLaunchKernelGGL(k_rbc_modes_unpack, dim3((unsigned)nblk(2 * (P->K + 1), 256)), dim3(256), 0, sc, P->K,
                          P->n1, P->n2, P->rbc_z, P->tw_rbc, P->dk2, S.alpha, S.dalpha, P->ybuf);
     }
-    hipLaunchKernelGGL(k_hist_b, dim3(nb_b), dim3(512), lds_b, sc, 2, P->fft_n1, P->n2, P->K, P->W, L, P->npos,
+    hipLaunchKernelGGL(k_hist_b, dim3(nb_b), dim3(kHistBThreads), lds_b, sc, 2, P->fft_n1, P->n2, P->K, P->W, L, P->npos,
                        P->T1, P->tw, P->tw1, P->dk1, P->dk2, P->pk, P->qk, P->rot, S.ring, S.alpha, S.dalpha,
-                       P->ybuf, P->V, P->fir_groups, P->hist_threads == 1024 ? 1 : 0);
+                       P->ybuf, P->V, P->hist_threads == 1024 ? 1 : 0);
   }
   {
     StageTimer st(P, WFP_STAGE_FFT_INV, sc);
@@ -2166,9 +2164,9 @@ void deriv_field(wfp_plan* P, const StateRef& S) {
   const size_t lds_b = P->lds_b;
   hipLaunchKernelGGL(k_deriv_y, dim3(nblk(P->K + 1, 256)), dim3(256), 0, s, P->K, P->n1, P->n2, S.alpha, P->dk2,
                      P->yd);
-  hipLaunchKernelGGL(k_hist_b, dim3(nb_b), dim3(512), lds_b, s, 2, P->fft_n1, P->n2, P->K, P->W, (int64_t)0,
+  hipLaunchKernelGGL(k_hist_b, dim3(nb_b), dim3(kHistBThreads), lds_b, s, 2, P->fft_n1, P->n2, P->K, P->W, (int64_t)0,
                      P->npos, P->T1, P->tw, P->tw1, P->dk1, P->dk2, P->pk, P->qk, P->rot, S.ring, S.alpha,
-                     S.dalpha, P->yd, P->V, P->fir_groups, P->hist_threads == 1024 ? 1 : 0);
+                     S.dalpha, P->yd, P->V, P->hist_threads == 1024 ? 1 : 0);
   launch_hist_c(P, s, (double2*)P->gridd);
 }
 

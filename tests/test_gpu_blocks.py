@@ -1,9 +1,13 @@
 """The pair-once stored local sum at the edges of its blocks (8 or 16 rows) and
-of the chunks of sources that it stages (128, 64 in the gradient pass)."""
+of the chunks of sources that it stages (128, 64 in the gradient pass), and the
+history part at the edges of its lanes, columns and rows."""
 import math
 
 import numpy as np
 import pytest
+
+from oracle.history import mode_step, pq_tables, rotation
+from oracle.rows import spectrum_direct
 
 pytestmark = pytest.mark.gpu
 
@@ -96,3 +100,48 @@ def test_pair_once_gradient_equals_per_pair(wfp, case):
     # the gradients sum n levels of such terms
     for a, b in zip(out[1], out[0]):
         assert _rel(a, b) < LOCAL_TOL * math.sqrt(n)
+
+
+# A spectrum sums M spread terms that carry about 16 eps of rounding each,
+# relative to the largest one of random densities 16 eps sqrt(M); a mode adds 40
+# taps of such spectra.  K is a few hundred at most: the direct sum's phases k x
+# carry k eps besides.
+def _tol(M):
+    return 16 * 2.2e-16 * math.sqrt(max(M, 40))
+
+
+HISTORY = [
+    dict(M=1, dt=0.0511),                                 # n1 = 5, n2 = 25
+    dict(M=3, dt=0.08),                                   # K = 39
+    dict(M=240, dt=0.02),                                 # 6 sources a cell on average: one lane,
+    dict(M=241, dt=0.02),                                 # then two
+    dict(M=700, dt=0.0101, free=True),                    # n1 = n2 = 25
+    dict(M=6000, dt=0.02),                                # 32 lanes a cell
+]
+
+
+@pytest.mark.parametrize("case", HISTORY, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+def test_history_step(wfp, case):
+    """One level's spectrum and mode update against the direct sums."""
+    M, dt = case["M"], case["dt"]
+    prob = _problem(M, 2.0 if case.get("free") else 2.9, dt, free=case.get("free"))
+    prob["x"] = prob["x"] - 1.3
+    prob["x_recv"] = np.zeros(0)
+    plan = wfp.Plan(prob, dt)
+    i, s = plan.info, _state(plan)
+    assert (50 % i["rbc_period"]) or not case.get("free")   # no boundary projection at this level
+    plan.set_state(50, **s)
+    plan.run(1)
+    now = plan.get_state()
+    plan.close()
+
+    def cplx(t):
+        t = t.cpu().numpy()
+        return t[..., 0] + 1j * t[..., 1]
+    K, W = i["K"], i["W"]
+    S = spectrum_direct(prob["x"], s["hist"][0].cpu().numpy(), K)
+    ring = np.concatenate([S[None], cplx(s["ring"])[:-1]])
+    P, Q = pq_tables(K, dt, W, W * dt, math.log(1e12))
+    al, da = mode_step(cplx(s["alpha"]), cplx(s["dalpha"]), ring, P, Q, rotation(K, dt), dt)
+    for got, want in ((now["ring"][0], S), (now["alpha"], al), (now["dalpha"], da)):
+        assert np.abs(cplx(got) - want).max() <= _tol(M) * np.abs(want).max()
