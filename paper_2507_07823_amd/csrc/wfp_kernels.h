@@ -255,6 +255,66 @@ __global__ void k_spread_grid(int nf, const double* __restrict__ sig, int M, con
 __global__ void k_hist_c_wide(FftPlan f2, int n1, const double2* __restrict__ V, const double2* __restrict__ tw,
                               double2* __restrict__ grid2);
 
+// ---- the chain's passes and the stored-weight local sum in the same launches ----
+struct HistAArgs {
+  FftPlan f2;
+  int n1;
+  const double* sig;
+  int M;
+  const int *cstart, *ccount;
+  const int64_t* woff;
+  const double* sw;
+  int lpc;
+  const double2* tw;
+  double2* T1;
+  ExtraSources ex;
+};
+struct HistBArgs {
+  int mode;
+  FftPlan f1;
+  int n2;
+  int64_t K;
+  int W;
+  int64_t L, npos;
+  const double2 *T1, *tw, *tw1;
+  const double *dk1, *dk2, *pk, *qk, *rot;
+  double2 *ring, *alpha, *dalpha, *y, *V;
+};
+struct HistCArgs {
+  FftPlan f2;
+  int n1;
+  const double2 *V, *tw;
+  double2* grid2;
+};
+// The local sum of level L from stored weights: lags >= 2 into `big` (parts
+// into big2, or row sums and column terms first), lag 1 and the total into loc.
+struct StoredArgs {
+  int M, NQ, NH;
+  int64_t L;
+  const double* hist;
+  const int64_t* rb;          // per row: first weight
+  const uint2* acx;           // per row and lag: the run
+  const double* Q;
+  double *big, *big2, *loc;
+  // per ordered pair
+  const int* nb_start;
+  int nsplit;
+  // once per unordered pair
+  int rows, periodic, kmax;
+  const int* up_end;
+  const int64_t* upb;
+  double *rowacc, *colpart;
+  const int2* cov;
+  const double* scale;
+};
+template <int G>
+__global__ void k_hist_a_local(int nc, HistAArgs h, StoredArgs d);
+template <int SPL>
+__global__ void k_hist_a_sym(int nc, HistAArgs h, StoredArgs d);
+__global__ void k_hist_b_reduce(int nc, HistBArgs h, StoredArgs d);
+__global__ void k_hist_c_lag1(int nc, HistCArgs h, StoredArgs d);
+__global__ void k_hist_c_sym_lag1(int nc, HistCArgs h, StoredArgs d);
+
 // ---- free-space radiation boundary projection ----
 __global__ void k_rbc_to_grid(FftPlan fp, int64_t K, int n1, int n2, const double2* __restrict__ alpha,
                               const double2* __restrict__ dalpha, const double2* __restrict__ tw,

@@ -576,6 +576,7 @@ __device__ __forceinline__ void k_local_rhs_body(int M, int NQ, int NH, int64_t 
   if (lane >= m0 && lane < m1) mine = acx[(int64_t)j * NQ + lane];
   const double* __restrict__ q = Qc + rowbase[j];
   const int grp = lane / G, gl = lane % G;
+  const int s0 = mod_slot(L, NH);
   double acc0 = 0.0, acc1 = 0.0;
   for (int mb = m0; mb < m1; mb += 64 / G) {
     const int m = mb + grp;
@@ -583,7 +584,8 @@ __device__ __forceinline__ void k_local_rhs_body(int M, int NQ, int NH, int64_t 
     const unsigned vx = __shfl(mine.x, src, 64), vy = __shfl(mine.y, src, 64);
     const int c = m < m1 ? (int)(vx >> 16) : 0;
     const double* __restrict__ qp = q + vy;
-    const double* __restrict__ hp = hist + (int64_t)mod_slot(L - m, NH) * M;
+    const int sm = s0 - (m < m1 ? m : 0);                     // m < NQ = NH
+    const double* __restrict__ hp = hist + (int64_t)(sm < 0 ? sm + NH : sm) * M;
     int l0 = st + (int)(vx & 0xffff);
     if (l0 >= M) l0 -= M;
     for (int i0 = 0; i0 < c; i0 += 8 * G) {
@@ -651,13 +653,12 @@ k_local_rhs_g4(int M, int NQ, int NH, int64_t L, int m0, int m1, const int* __re
 // level L - 1 is still being solved).  A row's lag-1 block is short (pairs
 // closer than about p/2 dt), so 16 lanes take a row, two consecutive elements
 // per lane and load as in k_local_rhs, and a wavefront takes four rows.
-__global__ void __launch_bounds__(256)
-k_local_lag1(int M, int NQ, int NH, int64_t L, const int* __restrict__ nb_start, const int64_t* __restrict__ rowbase,
-             const uint2* __restrict__ acx, const double* __restrict__ Qc, const double* __restrict__ hist,
-             const double* __restrict__ addin, const double* __restrict__ addin2, int nadd2,
-             double* __restrict__ loc) {
+__device__ __forceinline__ void k_local_lag1_body(int M, int NQ, int NH, int64_t L, const int* __restrict__ nb_start,
+             const int64_t* __restrict__ rowbase, const uint2* __restrict__ acx, const double* __restrict__ Qc,
+             const double* __restrict__ hist, const double* __restrict__ addin, const double* __restrict__ addin2,
+             int nadd2, double* __restrict__ loc, int bid) {
   const int gl = threadIdx.x & 15;
-  const int j = xcd_block(blockIdx.x, gridDim.x) * (blockDim.x >> 4) + (threadIdx.x >> 4);
+  const int j = bid * (blockDim.x >> 4) + (threadIdx.x >> 4);
   if (j >= M) return;   // no barrier; the reduction below stays inside the row's 16 lanes
   const uint2 v = acx[(int64_t)j * NQ + 1];
   const int c = (int)(v.x >> 16);
@@ -703,6 +704,15 @@ k_local_lag1(int M, int NQ, int NH, int64_t L, const int* __restrict__ nb_start,
     for (int q = 0; q < nadd2; ++q) a += addin2[(int64_t)q * M + j];
     loc[j] = a + sum;
   }
+}
+
+__global__ void __launch_bounds__(256)
+k_local_lag1(int M, int NQ, int NH, int64_t L, const int* __restrict__ nb_start, const int64_t* __restrict__ rowbase,
+             const uint2* __restrict__ acx, const double* __restrict__ Qc, const double* __restrict__ hist,
+             const double* __restrict__ addin, const double* __restrict__ addin2, int nadd2,
+             double* __restrict__ loc) {
+  k_local_lag1_body(M, NQ, NH, L, nb_start, rowbase, acx, Qc, hist, addin, addin2, nadd2, loc,
+                    xcd_block(blockIdx.x, gridDim.x));
 }
 
 // The gradient pass's two signed derivative local sums (lags 0 .. NQ - 1) in
@@ -1525,12 +1535,12 @@ k_local_sym_reduce(int M, const int2* __restrict__ cov, const int64_t* __restric
 // but number up to ~100 in dense media: 16 lanes per row (16 rows per
 // workgroup), each lane over every 16th term, the lanes' sums added by a
 // fixed butterfly.
-__global__ void __launch_bounds__(256)
-k_local_sym_lag1(int M, int NQ, int NH, int64_t L, int periodic, int kmax, const int64_t* __restrict__ rb,
-                 const uint2* __restrict__ sacx, const double* __restrict__ Qs, const double* __restrict__ hist,
-                 const double* __restrict__ scale, const double* __restrict__ base, double* __restrict__ out) {
+__device__ __forceinline__ void k_local_sym_lag1_body(int M, int NQ, int NH, int64_t L, int periodic, int kmax,
+                 const int64_t* __restrict__ rb, const uint2* __restrict__ sacx, const double* __restrict__ Qs,
+                 const double* __restrict__ hist, const double* __restrict__ scale, const double* __restrict__ base,
+                 double* __restrict__ out, int bid) {
   const int g = threadIdx.x & 15;
-  const int l = blockIdx.x * 16 + (threadIdx.x >> 4);
+  const int l = bid * 16 + (threadIdx.x >> 4);
   const bool act = l < M;   // every lane stays for the butterfly
   double a = 0.0;
   if (act) {
@@ -1555,6 +1565,13 @@ k_local_sym_lag1(int M, int NQ, int NH, int64_t L, int periodic, int kmax, const
 #pragma unroll
   for (int o = 8; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
   if (act && g == 0) out[l] = base[l] + scale[l] * a;
+}
+
+__global__ void __launch_bounds__(256)
+k_local_sym_lag1(int M, int NQ, int NH, int64_t L, int periodic, int kmax, const int64_t* __restrict__ rb,
+                 const uint2* __restrict__ sacx, const double* __restrict__ Qs, const double* __restrict__ hist,
+                 const double* __restrict__ scale, const double* __restrict__ base, double* __restrict__ out) {
+  k_local_sym_lag1_body(M, NQ, NH, L, periodic, kmax, rb, sacx, Qs, hist, scale, base, out, blockIdx.x);
 }
 
 
@@ -2188,7 +2205,7 @@ __device__ __forceinline__ int partner(int c, int k1, int k2c, int ncol, int n1)
 // the roots of unity) is requested before the transform, so the chain holds
 // one wait on memory.  The kernel alone on the chip, by events, against taps
 // summed after the transform with roots and tables gathered where they are
-// used: 17.1 us for 28.1 (K = 24000, columns of 200), 12.4 for 19.6 (K = 3141),
+// used: 17.1 us for 28.1 (K = 20480, columns of 200), 12.4 for 19.6 (K = 3141),
 // 166 for 246 (K = 524288).
 __device__ __forceinline__ void k_hist_b_body(int mode, FftPlan f1, int n2, int64_t K, int W, int64_t L, int64_t npos, const double2* __restrict__ T1,
          const double2* __restrict__ tw, const double2* __restrict__ tw1, const double* __restrict__ dk1, const double* __restrict__ dk2,
@@ -2358,6 +2375,69 @@ k_hist_c_wide(FftPlan f2, int n1, const double2* __restrict__ V, const double2* 
   __syncthreads();
   fft_batch(buf, 1, f2, tw, 2 * n1);
   for (int j2 = threadIdx.x; j2 < n2; j2 += blockDim.x) grid2[j1 + n1 * j2] = cconj(buf[j2]);
+}
+
+// ---------------------------------------------------------------------------
+// The history chain and the stored-weight local sum of a level in the same
+// launches.  Neither reads what the other writes before the solve, and on one
+// stream a level of a small problem is a queue of dependent launches, each too
+// short and too narrow to fill the chip: the first `nc` blocks run the chain's
+// pass, the others the part of the local sum that is due, with the bodies (and
+// so the values) of the separate kernels.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void hist_a_part(const HistAArgs& h, int bid) {
+  k_hist_a_body(h.f2, h.n1, h.sig, h.M, h.cstart, h.ccount, h.woff, h.sw, h.lpc, h.tw, h.T1, h.ex, bid);
+}
+
+template <int G>
+__global__ void __launch_bounds__(256) k_hist_a_local(int nc, HistAArgs h, StoredArgs d) {
+  const int b = blockIdx.x;
+  if (b < nc) hist_a_part(h, b);
+  else
+    k_local_rhs_body<G>(d.M, d.NQ, d.NH, d.L, 2, d.NQ, d.nb_start, d.rb, d.acx, d.Q, d.hist, nullptr, d.big,
+                        xcd_block(b - nc, gridDim.x - nc), d.big2, d.nsplit);
+}
+template __global__ void k_hist_a_local<4>(int, HistAArgs, StoredArgs);
+template __global__ void k_hist_a_local<8>(int, HistAArgs, StoredArgs);
+template __global__ void k_hist_a_local<16>(int, HistAArgs, StoredArgs);
+
+template <int SPL>
+__global__ void __launch_bounds__(kSymThreads) k_hist_a_sym(int nc, HistAArgs h, StoredArgs d) {
+  if ((int)blockIdx.x < nc) {
+    hist_a_part(h, blockIdx.x);
+    return;
+  }
+  const int b = xcd_block(blockIdx.x - nc, gridDim.x - nc);
+  if ((int64_t)b * d.rows >= d.M) return;                     // padding block (uniform)
+  sym_block<SPL, 1>(d.M, d.NQ, 2, d.rows, d.up_end, d.rb, d.acx, d.Q, d.upb, d.hist, mod_slot(d.L, d.NH), d.NH, nullptr,
+                    0, 0, d.rowacc, nullptr, d.colpart, nullptr, b);
+}
+template __global__ void k_hist_a_sym<1>(int, HistAArgs, StoredArgs);
+template __global__ void k_hist_a_sym<2>(int, HistAArgs, StoredArgs);
+
+// (the column pass leaves the threads past kHistBThreads idle)
+__global__ void __launch_bounds__(64 * kReduceWaves) k_hist_b_reduce(int nc, HistBArgs h, StoredArgs d) {
+  if ((int)blockIdx.x < nc)
+    k_hist_b_body(h.mode, h.f1, h.n2, h.K, h.W, h.L, h.npos, h.T1, h.tw, h.tw1, h.dk1, h.dk2, h.pk, h.qk, h.rot, h.ring,
+                  h.alpha, h.dalpha, h.y, h.V, blockIdx.x);
+  else
+    k_local_sym_reduce_body(d.M, d.cov, d.upb, d.rowacc, d.colpart, d.scale, d.big, blockIdx.x - nc);
+}
+
+__global__ void __launch_bounds__(256) k_hist_c_lag1(int nc, HistCArgs h, StoredArgs d) {
+  const int b = blockIdx.x;
+  if (b < nc) k_hist_c_body(h.f2, h.n1, h.V, h.tw, h.grid2, b);
+  else
+    k_local_lag1_body(d.M, d.NQ, d.NH, d.L, d.nb_start, d.rb, d.acx, d.Q, d.hist, d.big, d.big2, d.nsplit - 1, d.loc,
+                      xcd_block(b - nc, gridDim.x - nc));
+}
+
+__global__ void __launch_bounds__(256) k_hist_c_sym_lag1(int nc, HistCArgs h, StoredArgs d) {
+  const int b = blockIdx.x;
+  if (b < nc) k_hist_c_body(h.f2, h.n1, h.V, h.tw, h.grid2, b);
+  else
+    k_local_sym_lag1_body(d.M, d.NQ, d.NH, d.L, d.periodic, d.kmax, d.rb, d.acx, d.Q, d.hist, d.scale, d.big, d.loc,
+                          b - nc);
 }
 
 // ---------------------------------------------------------------------------

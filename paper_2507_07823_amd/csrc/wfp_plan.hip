@@ -1612,6 +1612,66 @@ void launch_local_lag1(wfp_plan* P, hipStream_t s, const double* hist, int64_t L
                      P->loc);
 }
 
+// The chain's passes and the stored-weight local sum in the same launches (see
+// the kernels): on one stream, where the row passes are the short ones.  Per-stage
+// timing takes the separate kernels, with the same values.  One hides behind the
+// other: 18.6 us a level for 23.8 at M = 16, 28.6 for 40.8 at M = 1e3 with 100
+// neighbours, 36.5 for 43.1 with few neighbours and 20480 modes, 61 for 77 at
+// M = 1e4 with 139 MB of weights.  Pair-once plans with more column pairs stay
+// with the separate kernels: beside the reduction a compute unit holds one block
+// of the column pass (at 101 blocks, M = 3e4, 146 us for 141; at 63, M = 1e4, still 57.5 for 69.9).
+bool fused_schedule(const wfp_plan* P) {
+  return !otf_schedule(P) && P->hist_threads == 256 && !P->profiling && !(P->sym_stored && P->n2 / 2 + 1 > 64);
+}
+
+StoredArgs stored_args(wfp_plan* P, const double* hist, int64_t L) {
+  StoredArgs d{};
+  d.M = (int)P->M;
+  d.NQ = P->NQ;
+  d.NH = P->NH;
+  d.L = L;
+  d.hist = hist;
+  d.big = P->locb + (L & 1) * P->M;
+  d.loc = P->loc;
+  if (P->sym_stored) {
+    d.rb = P->sym_rb;
+    d.acx = P->sym_acx;
+    d.Q = P->sym_q;
+    d.rows = sym_rows(P);
+    d.periodic = P->boundary == WFP_PERIODIC ? 1 : 0;
+    d.kmax = P->sym_kmax;
+    d.up_end = P->otf_up_end;
+    d.upb = P->sym_upb;
+    d.rowacc = P->otf_rowacc;
+    d.colpart = P->sym_colpart;
+    d.cov = P->sym_cov;
+    d.scale = P->half_beta;
+  } else {
+    d.rb = P->rowbase;
+    d.acx = P->acx;
+    d.Q = P->Qc;
+    d.big2 = locb_second(P, L);
+    d.nb_start = P->nb_start;
+    d.nsplit = P->lsplit;
+  }
+  return d;
+}
+
+void launch_hist_a_local(wfp_plan* P, hipStream_t s, const double* sig, ExtraSources ex, const StoredArgs& d) {
+  const HistAArgs h{P->fft_n2, P->n1, sig, (int)P->M, P->cstart, P->ccount, P->swoff, P->sw, P->spread_lanes, P->tw,
+                    P->T1, ex};
+  const size_t lds = 3 * P->n2 * sizeof(double2);
+  if (P->sym_stored) {
+    hipLaunchKernelGGL(P->sym_spl == 2 ? k_hist_a_sym<2> : k_hist_a_sym<1>,
+                       dim3(P->n1 + 8 * nblk(nblk(P->M, d.rows), 8)), dim3(kSymThreads),
+                       std::max(lds, sym_lds(P->NQ, 1)), s, P->n1, h, d);
+    return;
+  }
+  const dim3 grid(P->n1 + 8 * nblk(nblk((int64_t)d.nsplit * P->M, kRowThreads / 64), 8));
+  hipLaunchKernelGGL(P->lgrp == 16 ? k_hist_a_local<16> : (P->lgrp == 8 ? k_hist_a_local<8> : k_hist_a_local<4>), grid,
+                     dim3(256), lds, s, P->n1, h, d);
+}
+
 // One level L, in stream order: driving data (unless `driven`: P->ginc already
 // holds it), local sum (levels < L), the history part (three kernels; the
 // free-space projection when due), solve, receivers.  Stored weights: the
@@ -1634,6 +1694,8 @@ void march_level(wfp_plan* P, const StateRef& S, int64_t L, bool driven, const E
   const size_t lds_b = P->lds_b;
   const double* sig_prev = S.hist + (int64_t)(((L - 1) % P->NH + P->NH) % P->NH) * P->M;
   const double* gin = driven ? P->ginc : driving_row(P, s, L);
+  const bool fused = !overlap && !local_ready && fused_schedule(P);
+  const StoredArgs sa = fused ? stored_args(P, S.hist, L) : StoredArgs{};
   {
     // timed with events bound to the kernel's own dispatch (no marker gaps)
     hipEvent_t ea = nullptr, eb = nullptr;
@@ -1642,7 +1704,9 @@ void march_level(wfp_plan* P, const StateRef& S, int64_t L, bool driven, const E
       ea = take_event(P);
       eb = take_event(P);
     }
-    if (local_ready) {
+    if (fused) {
+      // with the chain's passes below
+    } else if (local_ready) {
       HIPCHK(hipMemcpyAsync(P->loc, local_ready, P->M * sizeof(double), hipMemcpyDeviceToDevice, s));
     } else if (otf_schedule(P) && overlap) {
       // on the local sum's compute units, joined before the solve
@@ -1662,14 +1726,22 @@ void march_level(wfp_plan* P, const StateRef& S, int64_t L, bool driven, const E
   }
   {
     StageTimer st(P, WFP_STAGE_SPREAD, sc);
-    launch_hist_a(P, sc, sig_prev, ex);
+    if (fused) launch_hist_a_local(P, sc, sig_prev, ex, sa);
+    else launch_hist_a(P, sc, sig_prev, ex);
   }
   const bool rbc = !periodic && L > 0 && L % P->rbc_period == 0;
   {
     StageTimer st(P, WFP_STAGE_MODES, sc);
-    hipLaunchKernelGGL(k_hist_b, dim3(nb_b), dim3(kHistBThreads), lds_b, sc, rbc ? 1 : 0, P->fft_n1, P->n2, P->K, P->W, L,
-                       P->npos, P->T1, P->tw, P->tw1, P->dk1, P->dk2, P->pk, P->qk, P->rot, S.ring, S.alpha,
-                       S.dalpha, P->ybuf, P->V, P->hist_threads == 1024 ? 1 : 0);
+    if (fused && P->sym_stored) {
+      const HistBArgs h{rbc ? 1 : 0, P->fft_n1, P->n2, P->K, P->W, L, P->npos, P->T1, P->tw, P->tw1, P->dk1, P->dk2,
+                        P->pk, P->qk, P->rot, S.ring, S.alpha, S.dalpha, P->ybuf, P->V};
+      hipLaunchKernelGGL(k_hist_b_reduce, dim3(nb_b + nblk(P->M, 64)), dim3(64 * kReduceWaves), lds_b, sc, (int)nb_b, h,
+                         sa);
+    } else {
+      hipLaunchKernelGGL(k_hist_b, dim3(nb_b), dim3(kHistBThreads), lds_b, sc, rbc ? 1 : 0, P->fft_n1, P->n2, P->K,
+                         P->W, L, P->npos, P->T1, P->tw, P->tw1, P->dk1, P->dk2, P->pk, P->qk, P->rot, S.ring,
+                         S.alpha, S.dalpha, P->ybuf, P->V, P->hist_threads == 1024 ? 1 : 0);
+    }
   }
   if (rbc) {
     StageTimer st(P, WFP_STAGE_RBC, sc);
@@ -1704,7 +1776,16 @@ void march_level(wfp_plan* P, const StateRef& S, int64_t L, bool driven, const E
   }
   {
     StageTimer st(P, WFP_STAGE_FFT_INV, sc);
-    launch_hist_c(P, sc, (double2*)P->grid2);
+    if (fused) {
+      const HistCArgs h{P->fft_n2, P->n1, P->V, P->tw, (double2*)P->grid2};
+      const size_t lds = 3 * P->n2 * sizeof(double2);
+      if (P->sym_stored)
+        hipLaunchKernelGGL(k_hist_c_sym_lag1, dim3(P->n1 + nblk(P->M, 16)), dim3(256), lds, sc, P->n1, h, sa);
+      else
+        hipLaunchKernelGGL(k_hist_c_lag1, dim3(P->n1 + 8 * nblk(nblk(P->M, 16), 8)), dim3(256), lds, sc, P->n1, h, sa);
+    } else {
+      launch_hist_c(P, sc, (double2*)P->grid2);
+    }
   }
   if (overlap && sc != s) {
     HIPCHK(hipEventRecord(P->ev_chain, sc));
@@ -1714,7 +1795,7 @@ void march_level(wfp_plan* P, const StateRef& S, int64_t L, bool driven, const E
   {
     StageTimer st(P, WFP_STAGE_SOLVE, s);
     if (ahead) HIPCHK(hipStreamWaitEvent(s, P->ev_big[L & 1], 0));   // driving data and local sum of level L
-    else if (!otf_schedule(P)) launch_local_lag1(P, s, S.hist, L);
+    else if (!otf_schedule(P) && !fused) launch_local_lag1(P, s, S.hist, L);
     if (P->n_direct_tiles > 0)
       hipLaunchKernelGGL(k_solve_direct, dim3(P->n_direct_tiles), dim3(256), 0, s, (int)P->M, P->dt_g0, P->dt_n,
                          P->dt_p0, P->pt_cs, P->pt_cn, P->pt_inv, P->inv, gin, P->loc, P->i0s, P->iw,
