@@ -20,24 +20,22 @@ struct wfp_batch {
   // work lists (device) and their lengths
   int2 *wl_inc = nullptr, *wl_loc4 = nullptr, *wl_loc8 = nullptr, *wl_a = nullptr, *wl_b = nullptr,
        *wl_c = nullptr, *wl_dir = nullptr, *wl_til = nullptr, *wl_rows = nullptr, *wl_otf = nullptr,
-       *wl_swt = nullptr, *wl_sww = nullptr, *wl_g8 = nullptr, *wl_g4 = nullptr, *wl_rcv = nullptr,
+       *wl_sw = nullptr, *wl_g8 = nullptr, *wl_g4 = nullptr, *wl_rcv = nullptr,
        *wl_otfr = nullptr, *wl_sp = nullptr, *wl_sym = nullptr, *wl_symr = nullptr, *wl_bin = nullptr, *wl_binr = nullptr;
   int n_bin = 0, n_binr = 0;
   int n_otfr = 0, n_sp = 0, n_sym = 0, n_symr = 0;
   int n_inc = 0, n_loc4 = 0, n_loc8 = 0, n_a = 0, n_b = 0, n_c = 0, n_dir = 0, n_til = 0, n_rows = 0, n_otf = 0,
-      n_swt = 0, n_sww = 0, n_g8 = 0, n_g4 = 0, n_rcv = 0;
+      n_sw = 0, n_g8 = 0, n_g4 = 0, n_rcv = 0;
   // receiver outputs of the current run: per instance a device pointer (or
   // NULL) and the level the run started at, read by the captured level
   double** uout_d = nullptr;
   int64_t* lvl0_d = nullptr;
   bool uout_set = false;
   size_t lds_a = 0, lds_b = 0, lds_c = 0, lds_til = 0, lds_otf = 0, lds_sym = 0;
-  // Jacobi sweeps of the global-solve instances, thread per row (swt) or
-  // wavefront per row (sww); both lists are ordered by decreasing sweep count,
-  // so sweep `it` launches the prefix of cnt_swt[it] (cnt_sww[it]) items
-  // whose instances still iterate
+  // Jacobi sweeps of the global-solve instances, 16 or 64 rows an item, by decreasing
+  // sweep count: sweep `it` launches the prefix of cnt_sw[it] items
   int max_sweeps = 0;
-  std::vector<int> cnt_swt, cnt_sww;
+  std::vector<int> cnt_sw;
   // launch shape of the local sum: rows per block (4 or 8) and the XCD remap
   int loc_rows = 4, loc_xcd = 1;
   // spread tile: 0 = one fine-grid row per workgroup, spread inside the row
@@ -144,8 +142,9 @@ InstDesc describe(const wfp_plan* P) {
   d.sval = P->sval;
   d.i0s = P->i0s;
   d.iw = P->iw;
-  d.g_ptr = P->g_ptr;
-  d.g_col = P->g_col;
+  d.g_off = P->g_off;
+  d.g_lim = P->g_lim;
+  d.g_ud = P->g_ud;
   d.g_val = P->g_val;
   d.g_dinv = P->g_dinv;
   d.g_rhs = P->g_rhs;
@@ -283,16 +282,12 @@ void build_batch(wfp_batch* B) {
     if (B->plans[i]->solve_global && B->plans[i]->iters > 1) order.push_back(i);
   std::stable_sort(order.begin(), order.end(),
                    [&](int a, int c) { return B->plans[a]->iters > B->plans[c]->iters; });
-  std::vector<int2> swt, sww;
-  B->cnt_swt.assign(std::max(B->max_sweeps, 1), 0);
-  B->cnt_sww.assign(std::max(B->max_sweeps, 1), 0);
+  std::vector<int2> sw;
+  B->cnt_sw.assign(std::max(B->max_sweeps, 1), 0);
   for (int i : order) {
     const wfp_plan* P = B->plans[i];
-    std::vector<int2>& lst = P->g_wave ? sww : swt;
-    const int rpb = P->g_wave ? 4 : 256;
-    for (int b = 0; b < (int)nblk(P->M, rpb); ++b) lst.push_back(make_int2(i, b));
-    std::vector<int>& cnt = P->g_wave ? B->cnt_sww : B->cnt_swt;
-    for (int it = 1; it < P->iters; ++it) cnt[it] = (int)lst.size();
+    for (int b = 0; b < (int)nblk(P->M, sweep_rows(P->M)); ++b) sw.push_back(make_int2(i, b));
+    for (int it = 1; it < P->iters; ++it) B->cnt_sw[it] = (int)sw.size();
   }
   B->lds_c = B->lds_a;
   B->ends.assign(n, INT64_MAX);
@@ -323,8 +318,7 @@ void build_batch(wfp_batch* B) {
   B->lvl0_d = B->alloc<int64_t>(1);
   HIPCHK(hipMemsetAsync(B->uout_d, 0, n * sizeof(double*), B->bs));
   HIPCHK(hipMemsetAsync(B->lvl0_d, 0, sizeof(int64_t), B->bs));
-  B->wl_swt = upload_work(B, swt, 1, B->n_swt);
-  B->wl_sww = upload_work(B, sww, 1, B->n_sww);
+  B->wl_sw = upload_work(B, sw, 1, B->n_sw);
   if (B->n_otf)
     HIPCHK(hipFuncSetAttribute((const void*)kb_local_otf, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)B->lds_otf));
@@ -409,14 +403,9 @@ void enqueue_level(wfp_batch* B) {
     bl.work = B->wl_rows;
     hipLaunchKernelGGL(kb_solve_rhs, dim3(B->n_rows), dim3(256), 0, s, bl);
     for (int it = 1; it < B->max_sweeps; ++it) {
-      if (B->cnt_swt[it]) {
-        bl.work = B->wl_swt;
-        hipLaunchKernelGGL(kb_jacobi_sweep, dim3(B->cnt_swt[it]), dim3(256), 0, s, bl, it);
-      }
-      if (B->cnt_sww[it]) {
-        bl.work = B->wl_sww;
-        hipLaunchKernelGGL(kb_jacobi_sweep_wave, dim3(B->cnt_sww[it]), dim3(256), 0, s, bl, it);
-      }
+      if (!B->cnt_sw[it]) continue;
+      bl.work = B->wl_sw;
+      hipLaunchKernelGGL(kb_jacobi_sweep, dim3(B->cnt_sw[it]), dim3(64 * kSweepWaves), 0, s, bl, it);
     }
   }
   if (B->n_rcv) {

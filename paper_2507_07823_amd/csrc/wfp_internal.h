@@ -288,7 +288,8 @@ struct wfp_plan {
   hipEvent_t ev_big[2] = {nullptr, nullptr};
   // global-sweep solve (when tiles do not fit in LDS)
   bool solve_global = false, g_wave = false;
-  int *g_ptr = nullptr, *g_col = nullptr;
+  int64_t* g_off = nullptr;               // sweeps: first value of each 64 rows,
+  int2 *g_lim = nullptr, *g_ud = nullptr; // their longest upper and lower run, and each row's
   double *g_val = nullptr, *g_dinv = nullptr, *g_rhs = nullptr, *g_xa = nullptr, *g_xb = nullptr;
   // direct solve of small runs
   int n_direct_tiles = 0;

@@ -1709,7 +1709,7 @@ k_solve(int M, int iters, int ext_max, const int* __restrict__ tile_r0, const in
 }
 
 // Per-step solve when the tiles do not fit in LDS (dense nearby coupling along
-// long runs): global Jacobi sweeps, one launch each, CSR over all rows.
+// long runs): global Jacobi sweeps, one launch each.
 // k_solve_rhs completes the right-hand side b_j = part_j - beta_j u_H(x_j) and
 // the first sweep from zero, x_j = b_j / (1 + S_jj); k_jacobi_sweep does
 // x'_j = (b_j - sum_{l != j} S_jl x_l) / (1 + S_jj) and, on the last sweep,
@@ -1732,54 +1732,102 @@ __global__ void k_solve_rhs(int M, const double* __restrict__ ginc, const double
   k_solve_rhs_body(M, ginc, loc, beta, i0s, iw, grid2, nf, width, dinv, rhs, x, blockIdx.x);
 }
 
-__device__ __forceinline__ void k_jacobi_sweep_body(int M, const int* __restrict__ ptr, const int* __restrict__ col,
-                               const double* __restrict__ val, const double* __restrict__ dinv,
+// S_jl / beta_j depends on the distance only, so each unordered pair is stored
+// once, by diagonals: of spring j and the k-th spring above it at
+// val[off[j / 64] + 64 (k - 1) + j % 64], k up to the longest such run up[j] of
+// the 64 rows (zero past a row's own).  A row's lower entries are those of the
+// springs down[j] .. 1 places below it.  A block takes RW = 64 rows, its
+// wavefronts every kSweepWaves-th diagonal, or 16 rows and four diagonals a
+// wavefront where 64 would leave the chip idle; the parts are added in order.
+// Bound by the values' stream; against a row's values and columns stored per
+// ordered pair (24 bytes a pair for 8), the solve with its 10 sweeps takes 3.77
+// ms for 6.74 at M = 1e6 and 266 nearby springs a row.
+template <int RW>
+__device__ __forceinline__ void k_jacobi_sweep_body(int M, const int64_t* __restrict__ off, const int2* __restrict__ lim,
+                               const int2* __restrict__ updown, const double* __restrict__ val,
+                               const double* __restrict__ beta, const double* __restrict__ dinv,
                                const double* __restrict__ rhs, const double* __restrict__ xin,
                                double* __restrict__ xout, double* __restrict__ save_row,
                                const int* __restrict__ perm, int bid) {
-  const int j = bid * blockDim.x + threadIdx.x;
-  if (j >= M) return;
-  double acc = rhs[j];
-  for (int k = ptr[j]; k < ptr[j + 1]; ++k) acc = fma(-val[k], xin[col[k]], acc);
-  const double v = acc * dinv[j];
-  xout[j] = v;
-  if (save_row) save_row[perm[j]] = v;
-}
-
-__global__ void k_jacobi_sweep(int M, const int* __restrict__ ptr, const int* __restrict__ col,
-                               const double* __restrict__ val, const double* __restrict__ dinv,
-                               const double* __restrict__ rhs, const double* __restrict__ xin,
-                               double* __restrict__ xout, double* __restrict__ save_row,
-                               const int* __restrict__ perm) {
-  k_jacobi_sweep_body(M, ptr, col, val, dinv, rhs, xin, xout, save_row, perm, blockIdx.x);
-}
-
-// The same sweep with one wavefront per row (lanes over the row's entries),
-// for rows with many nearby sources: the entry loads coalesce.
-__device__ __forceinline__ void k_jacobi_sweep_wave_body(int M, const int* __restrict__ ptr,
-                               const int* __restrict__ col, const double* __restrict__ val,
-                               const double* __restrict__ dinv, const double* __restrict__ rhs,
-                               const double* __restrict__ xin, double* __restrict__ xout,
-                               double* __restrict__ save_row, const int* __restrict__ perm, int bid) {
-  const int lane = threadIdx.x & 63;
-  const int j = bid * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (j >= M) return;
+  constexpr int U = RW == 64 ? 4 : 8;                         // diagonals whose loads are in flight together
+  constexpr int D = kSweepWaves * 64 / RW;                    // diagonals side by side
+  __shared__ double part[D][RW];
+  const int row = threadIdx.x & (RW - 1), kd = threadIdx.x / RW;
+  const int j = bid * RW + row;
+  const bool act = j < M;
+  const int jc = act ? j : M - 1;
+  const int2 ud = act ? updown[j] : make_int2(0, 0), top = lim[bid * RW / 64];
+  const double* __restrict__ vj = val + off[bid * RW / 64] + (j & 63);
   double acc = 0.0;
-  for (int k = ptr[j] + lane; k < ptr[j + 1]; k += 64) acc = fma(val[k], xin[col[k]], acc);
-  acc = wave_sum(acc);
-  if (lane == 0) {
-    const double v = (rhs[j] - acc) * dinv[j];
-    xout[j] = v;
-    if (save_row) save_row[perm[j]] = v;
+  for (int k0 = 1 + kd; k0 <= top.x; k0 += U * D) {
+    double v[U], x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + u * D;
+      const bool on = k <= ud.x;
+      int l = on ? j + k : jc;
+      if (l >= M) l -= M;
+      v[u] = vj[on ? (int64_t)64 * (k - 1) : 0];
+      x[u] = xin[l];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc = k0 + u * D <= ud.x ? fma(v[u], x[u], acc) : acc;
+  }
+  for (int k0 = 1 + kd; k0 <= top.y; k0 += U * D) {
+    double v[U], x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + u * D;
+      const bool on = k <= ud.y;
+      int r = on ? j - k : jc;
+      if (r < 0) r += M;
+      v[u] = val[on ? off[r >> 6] + (int64_t)64 * (k - 1) + (r & 63) : 0];
+      x[u] = xin[r];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc = k0 + u * D <= ud.y ? fma(v[u], x[u], acc) : acc;
+  }
+  part[kd][row] = acc;
+  __syncthreads();
+  if (kd == 0 && act) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < D; ++w) s += part[w][row];
+    const double y = (rhs[j] - beta[j] * s) * dinv[j];
+    xout[j] = y;
+    if (save_row) save_row[perm[j]] = y;
   }
 }
 
-__global__ void __launch_bounds__(256)
-k_jacobi_sweep_wave(int M, const int* __restrict__ ptr, const int* __restrict__ col,
-                    const double* __restrict__ val, const double* __restrict__ dinv,
-                    const double* __restrict__ rhs, const double* __restrict__ xin, double* __restrict__ xout,
-                    double* __restrict__ save_row, const int* __restrict__ perm) {
-  k_jacobi_sweep_wave_body(M, ptr, col, val, dinv, rhs, xin, xout, save_row, perm, blockIdx.x);
+// (the grid is padded to a multiple of 8 blocks: neighbouring blocks share
+// diagonals and run on one XCD; padding blocks return as a whole)
+template <int RW>
+__global__ void __launch_bounds__(64 * kSweepWaves)
+k_jacobi_sweep(int M, const int64_t* __restrict__ off, const int2* __restrict__ lim, const int2* __restrict__ updown,
+               const double* __restrict__ val, const double* __restrict__ beta, const double* __restrict__ dinv,
+               const double* __restrict__ rhs, const double* __restrict__ xin, double* __restrict__ xout,
+               double* __restrict__ save_row, const int* __restrict__ perm) {
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  if ((int64_t)b * RW >= M) return;
+  k_jacobi_sweep_body<RW>(M, off, lim, updown, val, beta, dinv, rhs, xin, xout, save_row, perm, b);
+}
+template __global__ void k_jacobi_sweep<16>(int, const int64_t*, const int2*, const int2*, const double*, const double*,
+                                            const double*, const double*, const double*, double*, double*, const int*);
+template __global__ void k_jacobi_sweep<64>(int, const int64_t*, const int2*, const int2*, const double*, const double*,
+                                            const double*, const double*, const double*, double*, double*, const int*);
+
+// The diagonals of the sweeps, from the lag-0 weights of the nearby pairs (row
+// j's own at q0[j], its upper ones after it); a thread per (diagonal, row) of
+// the chunk blockIdx.x.
+__global__ void k_pack_diagonals(int M, const int64_t* __restrict__ off, const int2* __restrict__ lim,
+                                 const int2* __restrict__ updown, const int64_t* __restrict__ q0,
+                                 const double* __restrict__ Q, const double* __restrict__ beta,
+                                 double* __restrict__ val) {
+  const int c = blockIdx.x;
+  for (int64_t t = threadIdx.x; t < (int64_t)64 * lim[c].x; t += blockDim.x) {
+    const int k = (int)(t >> 6) + 1, j = c * 64 + (int)(t & 63);
+    val[off[c] + t] = j < M && k <= updown[j].x ? Q[q0[j] + k] / beta[j] : 0.0;
+  }
 }
 
 // Per-step solve on small nearby-runs: I + S is block diagonal over maximal
@@ -2724,30 +2772,21 @@ __global__ void __launch_bounds__(256) kb_solve_rhs(BatchLaunch b) {
 // Sweep `it` (1-based) of the instances whose sweep count exceeds it; the
 // buffers alternate as in the single-instance solve and the last sweep writes
 // the history slot.
-__global__ void __launch_bounds__(256) kb_jacobi_sweep(BatchLaunch b, int it) {
+__global__ void __launch_bounds__(64 * kSweepWaves) kb_jacobi_sweep(BatchLaunch b, int it) {
   const int2 w = b.work[blockIdx.x];
-  if (w.x < 0) return;
+  if (w.x < 0) return;   // block-uniform
   const InstDesc& d = b.desc[w.x];
   if (*b.level >= d.end) return;   // the instance has marched its own levels (block-uniform)
   if (it >= d.iters) return;
   double* slot = d.hist + (int64_t)mod_slot(*b.level, d.NH) * d.M;
   const double* xin = (it & 1) ? d.g_xa : d.g_xb;
   double* xout = (it == d.iters - 1) ? slot : ((it & 1) ? d.g_xb : d.g_xa);
-  k_jacobi_sweep_body(d.M, d.g_ptr, d.g_col, d.g_val, d.g_dinv, d.g_rhs, xin, xout, nullptr, nullptr, w.y);
-}
-
-// The same sweep with one wavefront per row (4 rows per block), for instances
-// whose rows hold many nearby sources.
-__global__ void __launch_bounds__(256) kb_jacobi_sweep_wave(BatchLaunch b, int it) {
-  const int2 w = b.work[blockIdx.x];
-  if (w.x < 0) return;
-  const InstDesc& d = b.desc[w.x];
-  if (*b.level >= d.end) return;   // the instance has marched its own levels (block-uniform)
-  if (it >= d.iters) return;
-  double* slot = d.hist + (int64_t)mod_slot(*b.level, d.NH) * d.M;
-  const double* xin = (it & 1) ? d.g_xa : d.g_xb;
-  double* xout = (it == d.iters - 1) ? slot : ((it & 1) ? d.g_xb : d.g_xa);
-  k_jacobi_sweep_wave_body(d.M, d.g_ptr, d.g_col, d.g_val, d.g_dinv, d.g_rhs, xin, xout, nullptr, nullptr, w.y);
+  if (sweep_rows(d.M) == 64)
+    k_jacobi_sweep_body<64>(d.M, d.g_off, d.g_lim, d.g_ud, d.g_val, d.beta, d.g_dinv, d.g_rhs, xin, xout, nullptr,
+                            nullptr, w.y);
+  else
+    k_jacobi_sweep_body<16>(d.M, d.g_off, d.g_lim, d.g_ud, d.g_val, d.beta, d.g_dinv, d.g_rhs, xin, xout, nullptr,
+                            nullptr, w.y);
 }
 
 // Receivers of every instance at the level being computed: instance i writes

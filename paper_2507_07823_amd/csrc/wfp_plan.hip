@@ -1274,38 +1274,48 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
       // every row by global sweeps; the direct and tiled paths are not used
       P->n_direct_tiles = 0;
       P->ntile = 0;
-      std::vector<int> gp(M + 1, 0), gc;
-      std::vector<int64_t> geq, grq(M);
+      // per row: nearby springs above and below it (contiguous both ways); per
+      // 64 rows: the longest of them
+      const int64_t nch = nblk(M, 64);
+      std::vector<int2> ud(M), lim(nch, make_int2(0, 0));
+      std::vector<int64_t> goff(nch), grq(M);
+      int64_t entries = 0, total = 0;
       for (int64_t g = 0; g < M; ++g) {
+        const int below = (int)((g - ns[g] + M) % M);
+        ud[g] = make_int2(nc[g] - 1 - below, below);
+        entries += nc[g] - 1;
         grq[g] = lag0(g, g);
-        for (int k = 0; k < nc[g]; ++k) {
-          const int64_t l = (ns[g] + k) % M;
-          if (l == g) continue;
-          gc.push_back((int)l);
-          geq.push_back(lag0(g, l));
-        }
-        gp[g + 1] = (int)gc.size();
+        lim[g / 64].x = std::max(lim[g / 64].x, ud[g].x);
       }
-      // a wavefront per row when rows are long
-      P->g_wave = gc.size() > (size_t)16 * M;
-      P->g_ptr = P->alloc<int>(M + 1);
-      P->g_col = P->alloc<int>(gc.size());
-      P->g_val = P->alloc<double>(gc.size());
+      for (int64_t g = 0; g < M; ++g) {
+        // the pair's value is read from the lower spring's run
+        while (ud[g].y > 0 && ud[(g - ud[g].y + M) % M].x < ud[g].y) --ud[g].y;
+        lim[g / 64].y = std::max(lim[g / 64].y, ud[g].y);
+      }
+      for (int64_t c = 0; c < nch; ++c) {
+        goff[c] = total;
+        total += 64 * (int64_t)lim[c].x;
+      }
+      P->g_wave = entries > 16 * M;
+      P->g_off = P->alloc<int64_t>(nch);
+      P->g_lim = P->alloc<int2>(nch);
+      P->g_ud = P->alloc<int2>(M);
+      P->g_val = P->alloc<double>(std::max<int64_t>(total, 1));
       P->g_dinv = P->alloc<double>(M);
       P->g_rhs = P->alloc<double>(M);
       P->g_xa = P->alloc<double>(M);
       P->g_xb = P->alloc<double>(M);
-      upload(P->g_ptr, gp, s);
-      upload(P->g_col, gc, s);
-      int64_t* eq_d = P->alloc<int64_t>(geq.size());
+      upload(P->g_off, goff, s);
+      upload(P->g_lim, lim, s);
+      upload(P->g_ud, ud, s);
       int64_t* rq_d = P->alloc<int64_t>(M);
-      upload(eq_d, geq, s);
       upload(rq_d, grq, s);
-      hipLaunchKernelGGL(k_gather_solve, dim3(nblk(std::max<int64_t>((int64_t)geq.size(), M), 256)), dim3(256), 0,
-                         s, (int64_t)geq.size(), eq_d, P->Q, P->g_val, (int64_t)M, rq_d, P->g_dinv);
+      hipLaunchKernelGGL(k_gather_solve, dim3(nblk(M, 256)), dim3(256), 0, s, (int64_t)0, (const int64_t*)nullptr, P->Q,
+                         (double*)nullptr, (int64_t)M, rq_d, P->g_dinv);
+      hipLaunchKernelGGL(k_pack_diagonals, dim3((unsigned)nch), dim3(256), 0, s, (int)M, P->g_off, P->g_lim, P->g_ud,
+                         rq_d, P->Q, P->beta, P->g_val);
       HIPCHK(hipGetLastError());
       HIPCHK(hipStreamSynchronize(s));
-      P->release(eq_d);
       P->release(rq_d);
     }
     if (P->ntile > 0) {
@@ -1816,12 +1826,10 @@ void march_level(wfp_plan* P, const StateRef& S, int64_t L, bool driven, const E
       for (int it = 1; it < P->iters; ++it) {
         const bool last = it == P->iters - 1;
         double* out = last ? slot : xb;
-        if (P->g_wave)
-          hipLaunchKernelGGL(k_jacobi_sweep_wave, dim3(nblk(P->M, 4)), dim3(256), 0, s, (int)P->M, P->g_ptr,
-                             P->g_col, P->g_val, P->g_dinv, P->g_rhs, xa, out, last ? save : nullptr, P->perm);
-        else
-          hipLaunchKernelGGL(k_jacobi_sweep, dim3(nb), dim3(256), 0, s, (int)P->M, P->g_ptr, P->g_col, P->g_val,
-                             P->g_dinv, P->g_rhs, xa, out, last ? save : nullptr, P->perm);
+        const int rw = sweep_rows(P->M);
+        hipLaunchKernelGGL(rw == 64 ? k_jacobi_sweep<64> : k_jacobi_sweep<16>, dim3(8 * nblk(nblk(P->M, rw), 8)),
+                           dim3(64 * kSweepWaves), 0, s, (int)P->M, P->g_off, P->g_lim, P->g_ud, P->g_val, P->beta,
+                           P->g_dinv, P->g_rhs, xa, out, last ? save : nullptr, P->perm);
         std::swap(xa, xb);
       }
     }

@@ -145,3 +145,52 @@ def test_history_step(wfp, case):
     al, da = mode_step(cplx(s["alpha"]), cplx(s["dalpha"]), ring, P, Q, rotation(K, dt), dt)
     for got, want in ((now["ring"][0], S), (now["alpha"], al), (now["dalpha"], da)):
         assert np.abs(cplx(got) - want).max() <= _tol(M) * np.abs(want).max()
+
+
+# Dense coupling solved by global sweeps, 16 or 64 rows a block: the densities
+# satisfy (I + S) sigma = b, so a march equals one whose springs' order and
+# whose tiles differ only to the sums' rounding and the sweeps' 1e-18: with n
+# nearby springs a row 4 eps sqrt(n), 4e-14 for the 2000 here, on top of the
+# local sums.
+SWEEPS = [
+    dict(M=700, width=0.002, dt=2e-3),                    # all coupled; the last block has 12 rows of 16
+    dict(M=2049, width=0.01, dt=2e-3, seam=True),         # runs across source 0, one row in the last 64
+    dict(M=40001, width=0.4, dt=2e-3),                    # 64 rows a block, one row in the last
+]
+
+
+@pytest.mark.parametrize("case", SWEEPS, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+def test_global_sweeps_solve_the_level(wfp, case):
+    """The solved level against the residual of its own equation, the coupling
+    by the oracle's weights."""
+    from oracle.local import local_weights
+    M, dt = case["M"], case["dt"]
+    prob = _problem(M, case["width"], dt, case.get("seam"))
+    prob["x_recv"] = np.zeros(0)
+    out = []
+    for it in (0, 14):
+        plan = wfp.Plan(prob, dt, local_mode=2, solve_iters=it)
+        i = plan.info
+        assert i["solve_mode"] == 1
+        plan.set_state(50, **_state(plan))
+        out.append(plan.march(1)[0][0].cpu().numpy())
+        plan.close()
+    # more sweeps change nothing
+    assert np.abs(out[1] - out[0]).max() <= LOCAL_TOL * np.abs(out[0]).max()
+    # one sweep from zero is the right-hand side over the diagonal
+    plan = wfp.Plan(prob, dt, local_mode=2, solve_iters=1)
+    plan.set_state(50, **_state(plan))
+    x1 = plan.march(1)[0][0].cpu().numpy()
+    plan.close()
+    order = np.argsort(np.mod(prob["x"], 2 * np.pi) if case.get("seam") else prob["x"], kind="stable")
+    x, beta, sig, x1 = (v[order] for v in (np.mod(prob["x"], 2 * np.pi) if case.get("seam") else prob["x"],
+                                           prob["beta"], out[0], x1))
+    prm = dict(W=i["W"], p=8, delta=i["W"] * dt, b=math.log(1e12), n_gl=i["W"])
+    s0 = 0.5 * beta * local_weights(np.zeros(1), dt, **prm)[0, 0]
+    rows = np.unique(np.r_[0, 1, M // 2, M - 2, M - 1, np.random.default_rng(1).integers(0, M, 20)])
+    for j in rows:
+        near = np.flatnonzero(np.abs(x - x[j]) < dt)
+        q = 0.5 * beta[j] * local_weights(np.abs(x[near] - x[j]), dt, **prm)[:, 0]
+        lhs = sig[j] + q @ sig[near]
+        rhs = x1[j] * (1.0 + s0[j])
+        assert abs(lhs - rhs) <= LOCAL_TOL * np.abs(out[0]).max()
