@@ -576,7 +576,6 @@ __device__ __forceinline__ void k_local_rhs_body(int M, int NQ, int NH, int64_t 
   if (lane >= m0 && lane < m1) mine = acx[(int64_t)j * NQ + lane];
   const double* __restrict__ q = Qc + rowbase[j];
   const int grp = lane / G, gl = lane % G;
-  const int s0 = mod_slot(L, NH);
   double acc0 = 0.0, acc1 = 0.0;
   for (int mb = m0; mb < m1; mb += 64 / G) {
     const int m = mb + grp;
@@ -584,8 +583,7 @@ __device__ __forceinline__ void k_local_rhs_body(int M, int NQ, int NH, int64_t 
     const unsigned vx = __shfl(mine.x, src, 64), vy = __shfl(mine.y, src, 64);
     const int c = m < m1 ? (int)(vx >> 16) : 0;
     const double* __restrict__ qp = q + vy;
-    const int sm = s0 - (m < m1 ? m : 0);                     // m < NQ = NH
-    const double* __restrict__ hp = hist + (int64_t)(sm < 0 ? sm + NH : sm) * M;
+    const double* __restrict__ hp = hist + (int64_t)mod_slot(L - m, NH) * M;
     int l0 = st + (int)(vx & 0xffff);
     if (l0 >= M) l0 -= M;
     for (int i0 = 0; i0 < c; i0 += 8 * G) {
