@@ -141,7 +141,7 @@ typedef struct {
   int64_t n_weights_lag1;      /* nonzero stored local weights of lag 1 (part of n_weights_nonzero) */
   int32_t n_solve_tiles;       /* solve_mode 0: LDS tiles of the Jacobi solve (long nearby runs) */
   int32_t n_direct_tiles;      /* solve_mode 0: groups of small nearby runs solved by stored inverses */
-  int32_t sweep_wave;          /* solve_mode 1: 1 when a wavefront sweeps each row (long rows), else 0 */
+  int32_t sweep_wave;          /* solve_mode 1: 1 when rows are long (over 16 nearby springs on average), else 0 */
   int32_t reserved2;
 } wfp_info;
 
