@@ -1433,10 +1433,14 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
     const int ncu = prop.multiProcessorCount;
     if (P->overlap_cus == 0) {
       // the chain on one XCD (its own L2) while the local sum streams its
-      // weights on the others, when the local sum is long enough to hide it
+      // weights on the others, when the local sum is long enough to hide it and
+      // not so long that the XCD is worth more to it than the chain's time (study,
+      // beside each other against one stream: 121 / 146 us a level at 0.28 GB of
+      // weights, 353 / 368 at 0.94, 997 / 1029 at 2.8, 3282 / 3205 at 9.3)
       int nx = 1;
       if (hipDeviceGetAttribute(&nx, hipDeviceAttributeNumberOfXccs, P->device) != hipSuccess || nx < 2) nx = 1;
-      const bool worth = 8.0 * (double)P->n_weights_stored >= 64.0 * 1024 * 1024;
+      const double bytes = 8.0 * (double)P->n_weights_stored;
+      const bool worth = bytes >= 64.0 * 1024 * 1024 && bytes < 6e9;
       P->overlap_cus = (nx > 1 && worth) ? ncu / nx : -1;
     }
   }
