@@ -103,7 +103,7 @@ typedef struct {
                               sum (lags >= 2) overlapping the current level's chain and solve
                               (results are the same bit for bit); < 0: one stream; 0: the
                               library's choice, which is one XCD's compute units when the local
-                              sum reads at least 64 MB per level, else one stream   [0] */
+                              sum reads 64 MB to 6 GB per level, else one stream   [0] */
   int32_t local_mode;      /* 1: local weights stored per pair (read every level); 2: evaluated on the
                               fly every level (memory O(M); pair by pair, arithmetic O(pairs N_L p), or,
                               from 112 neighbours per spring on with p <= 8, by bins of the distance on
