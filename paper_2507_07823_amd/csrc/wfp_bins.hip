@@ -14,6 +14,7 @@
 // cores), then eight multiply-adds per ordered pair.
 #include <type_traits>
 
+#include "wfp_bins.h"
 #include "wfp_device.h"
 #include "wfp_kernels.h"
 
@@ -378,7 +379,7 @@ __device__ __forceinline__ void local_bins_body(int M, int NH, int NQ, int64_t L
             }
             z[i] = fabs(z[i]);
             if (seam) z[i] = wrap ? kTwoPi - z[i] : z[i];
-            rec[i] = cellb[min(max((int)(z[i] * scale) - c0, 0), ctop)];
+            rec[i] = cellb[bin_cell(z[i], scale, c0, ctop)];
           }
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
