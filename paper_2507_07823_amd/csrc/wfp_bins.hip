@@ -160,37 +160,15 @@ WFP_BIN_TABLE(8)
 // Target windows.  Block b holds nsrc consecutive sources; chunk
 // c the distances [edge[c kBinChunk], edge[(c + 1) kBinChunk)).  win[b nch + c]
 // = (l0, l1, r0, r1): every target within the chunk of some source of the block
-// has its unwrapped index in [l0, l1) (below) or [r0, r1) (above); where both
-// meet the first is empty.  Unwrapped: in the periodic box the coordinate of
-// index u is xs[u mod M] + 2 pi floor(u / M), u in [-M, 2M).
+// has its unwrapped index in [l0, l1) (below) or [r0, r1) (above).
 __global__ void k_bin_windows(int M, int nsrc, int nblk, int nch, int periodic, double tol, const double* __restrict__ xs,
                               const double* __restrict__ edge, int4* __restrict__ win) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= nblk * nch) return;
   const int b = e / nch, c = e - b * nch;
   const double xa = xs[(int64_t)b * nsrc], xb = xs[min((b + 1) * nsrc, M) - 1];
-  const double elo = edge[c * kBinChunk], ehi = edge[(c + 1) * kBinChunk];
-  // first unwrapped index at or above coordinate v
-  auto lower = [&](double v) {
-    int lo = periodic ? -M : 0, hi = periodic ? 2 * M : M;
-    while (lo < hi) {
-      const int mid = lo + (hi - lo) / 2;
-      const double x = mid < 0 ? xs[mid + M] - kTwoPi : (mid >= M ? xs[mid - M] + kTwoPi : xs[mid]);
-      if (x < v) lo = mid + 1;
-      else hi = mid;
-    }
-    return lo;
-  };
-  int4 w;
-  w.x = lower(xa - ehi - tol);
-  w.y = lower(xb - elo + tol);
-  w.z = lower(xa + elo - tol);
-  w.w = lower(xb + ehi + tol);
-  if (c == 0 || w.z < w.y) {
-    w.z = w.x;
-    w.y = w.x;
-  }
-  win[e] = w;
+  const BinWindow w = bin_window(xs, M, periodic != 0, xa, xb, edge[c * kBinChunk], edge[(c + 1) * kBinChunk], tol, c == 0);
+  win[e] = make_int4(w.l0, w.l1, w.r0, w.r1);
 }
 
 // One workgroup per block of kBinColumns consecutive sources.  Chunk by chunk

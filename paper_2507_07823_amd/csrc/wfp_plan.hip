@@ -1,4 +1,5 @@
 // Plan creation, the level loop and the exported C ABI (include/wfp.h).
+#include "wfp_bins.h"
 #include "wfp_internal.h"
 
 #include <map>
@@ -303,7 +304,7 @@ void bin_blocks(wfp_plan* P, int nsrc, wfp_plan::BinBlocks& K) {
   K.nblk = (int)nblk(M, nsrc);
   K.win = P->alloc<int4>((size_t)K.nblk * B.nch);
   hipLaunchKernelGGL(k_bin_windows, dim3(nblk((int64_t)K.nblk * B.nch, 256)), dim3(256), 0, s, (int)M, nsrc, K.nblk,
-                     B.nch, P->boundary == WFP_PERIODIC ? 1 : 0, 1e-9 * P->dt, P->xs, B.edge, K.win);
+                     B.nch, P->boundary == WFP_PERIODIC ? 1 : 0, bin_tol(P->dt), P->xs, B.edge, K.win);
   HIPCHK(hipGetLastError());
   std::vector<int4> last(K.nblk);
   HIPCHK(hipMemcpy2DAsync(last.data(), sizeof(int4), K.win + (B.nch - 1), B.nch * sizeof(int4), sizeof(int4), K.nblk,

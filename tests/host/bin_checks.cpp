@@ -1,9 +1,11 @@
 // Checks of the index arithmetic of the sums by distance bins
 // (paper_2507_07823_amd/csrc/wfp_bins.h), built with UndefinedBehaviorSanitizer
 // by tests/test_host_bins.py.  Exit status 0 when every check holds.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <random>
+#include <vector>
 
 #include "../../paper_2507_07823_amd/csrc/wfp_bins.h"
 
@@ -40,8 +42,56 @@ static void check_cells() {
   }
 }
 
+// Every pair whose distance, as the sum computes it, lies in a chunk has its
+// target in the chunk's window: springs at the chunk's edges from one another, to
+// the last places, at steps down to 1e-7 (where the rounding of the coordinates
+// outweighs any fixed part of the step).
+static void check_windows() {
+  constexpr double pi = 3.14159265358979323846;
+  std::mt19937_64 g(9);
+  std::uniform_real_distribution<double> u(0.0, 1.0);
+  for (int k = 0; k < 3000; ++k) {
+    const double dt = std::pow(10.0, -2.0 - 5.0 * u(g)), elo = 30.0 * dt * u(g), ehi = elo + 3.0 * dt;
+    const bool periodic = k % 2, seam = periodic && k % 4 == 1;
+    std::vector<double> xs;
+    const double base = seam ? pi - 20.0 * dt * u(g) : 6.0 * (u(g) - 0.5);
+    auto add = [&](double x) {
+      if (x >= pi) x -= 2.0 * pi;
+      if (periodic || std::fabs(x) < pi) xs.push_back(x);
+    };
+    for (int i = 0; i < 6; ++i) {
+      const double x = base + dt * u(g);
+      add(x);
+      for (double e : {elo, ehi})
+        for (int n = -3; n <= 3; ++n)
+          for (int side : {-1, 1}) add(x + side * e + n * 2.2e-16);
+    }
+    std::sort(xs.begin(), xs.end());
+    const int M = (int)xs.size(), nsrc = 8;
+    for (int b = 0; b * nsrc < M; ++b) {
+      const int j1 = std::min((b + 1) * nsrc, M);
+      const BinWindow w = bin_window(xs.data(), M, periodic, xs[b * nsrc], xs[j1 - 1], elo, ehi, bin_tol(dt), false);
+      CHECK(w.l0 <= w.l1 && w.r0 <= w.r1 && (w.l1 <= w.r0 || w.l1 == w.l0), "overlapping runs");
+      for (int j = b * nsrc; j < j1; ++j)
+        for (int v = periodic ? -M : 0; v < (periodic ? 2 * M : M); ++v) {
+          const double x = xs[v < 0 ? v + M : (v >= M ? v - M : v)];
+          double z = std::fabs(x - xs[j]);
+          if (v < 0 || v >= M) {
+            if (v < 0 ? x < xs[j] : x > xs[j]) continue;      // more than a turn apart
+            z = 2.0 * pi - z;
+          }
+          if (!(z >= elo && z < ehi)) continue;
+          CHECK((v >= w.l0 && v < w.l1) || (v >= w.r0 && v < w.r1), "target %d of source %d (%.17g in [%.17g, %.17g), dt %g)",
+                v, j, z, elo, ehi, dt);
+          if (failures > 5) return;
+        }
+    }
+  }
+}
+
 int main() {
   check_cells();
+  check_windows();
   if (failures) return 1;
   std::printf("bin checks passed\n");
   return 0;
