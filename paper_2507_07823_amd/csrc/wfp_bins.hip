@@ -160,15 +160,17 @@ WFP_BIN_TABLE(8)
 // Target windows.  Block b holds nsrc consecutive sources; chunk
 // c the distances [edge[c kBinChunk], edge[(c + 1) kBinChunk)).  win[b nch + c]
 // = (l0, l1, r0, r1): every target within the chunk of some source of the block
-// has its unwrapped index in [l0, l1) (below) or [r0, r1) (above).
+// has its unwrapped index in [l0, l1) (below) or [r0, r1) (above).  span[b] =
+// [l0, r1) of the last chunk, which holds them all.
 __global__ void k_bin_windows(int M, int nsrc, int nblk, int nch, int periodic, double tol, const double* __restrict__ xs,
-                              const double* __restrict__ edge, int4* __restrict__ win) {
+                              const double* __restrict__ edge, int4* __restrict__ win, int2* __restrict__ span) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= nblk * nch) return;
   const int b = e / nch, c = e - b * nch;
   const double xa = xs[(int64_t)b * nsrc], xb = xs[min((b + 1) * nsrc, M) - 1];
   const BinWindow w = bin_window(xs, M, periodic != 0, xa, xb, edge[c * kBinChunk], edge[(c + 1) * kBinChunk], tol, c == 0);
   win[e] = make_int4(w.l0, w.l1, w.r0, w.r1);
+  if (c == nch - 1) span[b] = make_int2(w.l0, w.r1);
 }
 
 // One workgroup per block of kBinColumns consecutive sources.  Chunk by chunk

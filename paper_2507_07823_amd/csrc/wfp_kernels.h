@@ -77,7 +77,7 @@ __global__ void k_bin_table(int nbins, int W, int NQ, int ks, int ngl, double dt
                             const double* __restrict__ lagw, int deriv, double* __restrict__ C);
 __global__ void k_bin_windows(int M, int nsrc, int nblk, int nch, int periodic, double tol,
                               const double* __restrict__ xs, const double* __restrict__ edge,
-                              int4* __restrict__ win);
+                              int4* __restrict__ win, int2* __restrict__ span);
 // What the sums by bins read: the table, the bins' edges and lookup cells, and
 // the blocks of consecutive sources with their target windows and sums.
 struct BinArgs {

@@ -303,18 +303,16 @@ void bin_blocks(wfp_plan* P, int nsrc, wfp_plan::BinBlocks& K) {
   const int64_t M = P->M;
   K.nblk = (int)nblk(M, nsrc);
   K.win = P->alloc<int4>((size_t)K.nblk * B.nch);
+  K.span = P->alloc<int2>(K.nblk);
   hipLaunchKernelGGL(k_bin_windows, dim3(nblk((int64_t)K.nblk * B.nch, 256)), dim3(256), 0, s, (int)M, nsrc, K.nblk,
-                     B.nch, P->boundary == WFP_PERIODIC ? 1 : 0, bin_tol(P->dt), P->xs, B.edge, K.win);
+                     B.nch, P->boundary == WFP_PERIODIC ? 1 : 0, bin_tol(P->dt), P->xs, B.edge, K.win, K.span);
   HIPCHK(hipGetLastError());
-  std::vector<int4> last(K.nblk);
-  HIPCHK(hipMemcpy2DAsync(last.data(), sizeof(int4), K.win + (B.nch - 1), B.nch * sizeof(int4), sizeof(int4), K.nblk,
-                          hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
   std::vector<int2> span(K.nblk);
+  HIPCHK(hipMemcpyAsync(span.data(), K.span, K.nblk * sizeof(int2), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
   std::vector<int64_t> off(K.nblk);
   K.total = 0;
   for (int b = 0; b < K.nblk; ++b) {
-    span[b] = make_int2(last[b].x, last[b].w);
     off[b] = K.total;
     K.total += span[b].y - span[b].x;
   }
@@ -330,10 +328,8 @@ void bin_blocks(wfp_plan* P, int nsrc, wfp_plan::BinBlocks& K) {
       cov[3 * (size_t)w + im] = make_int2(a, std::max(a, e));
     }
   }
-  K.span = P->alloc<int2>(K.nblk);
   K.off = P->alloc<int64_t>(K.nblk);
   K.cov = P->alloc<int2>(cov.size());
-  upload(K.span, span, s);
   upload(K.off, off, s);
   upload(K.cov, cov, s);
   HIPCHK(hipStreamSynchronize(s));
