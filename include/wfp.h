@@ -105,10 +105,13 @@ typedef struct {
                               library's choice, which is one XCD's compute units when the local
                               sum reads 64 MB to 6 GB per level, else one stream   [0] */
   int32_t local_mode;      /* 1: local weights stored per pair (read every level); 2: evaluated on the
-                              fly every level (memory O(M); pair by pair, arithmetic O(pairs N_L p), or,
-                              from 112 neighbours per spring on with p <= 8, by bins of the distance on
-                              each of which every Q_m is a polynomial: one small matrix product per
-                              spring and one polynomial per pair); 3: stored once
+                              fly every level: pair by pair, arithmetic O(pairs N_L p), or by bins of the
+                              distance on each of which every Q_m is a polynomial (one small matrix
+                              product per spring and one polynomial per pair; p <= 8, at most 768 bins,
+                              which N_L <= 36 keeps to with one quadrature node per step), from 112
+                              neighbours per spring on where that is faster, by W, p and M; memory for
+                              the pairs' sums: (n / 2 + 16) M / 16 doubles pair by pair, n neighbours
+                              per spring, (n + 32) M / 32 by bins; 3: stored once
                               per unordered pair (Q_m depends on the distance alone) and applied to
                               both rows, about half the bytes of 1 (the gradient pass's
                               derivative weights likewise); 0: 2 by bins from 512 neighbours per spring
@@ -137,7 +140,7 @@ typedef struct {
   int32_t overlap_cus;         /* compute units of the concurrent history chain, -1: one stream */
   int32_t local_mode;          /* 1: stored local weights, 2: evaluated on the fly, 3: stored once per
                                   unordered pair */
-  int32_t reserved;
+  int32_t local_bins;          /* local_mode 2: 1 when the sum goes by distance bins, 0 pair by pair */
   int64_t n_weights_lag1;      /* nonzero stored local weights of lag 1 (part of n_weights_nonzero) */
   int32_t n_solve_tiles;       /* solve_mode 0: LDS tiles of the Jacobi solve (long nearby runs) */
   int32_t n_direct_tiles;      /* solve_mode 0: groups of small nearby runs solved by stored inverses */

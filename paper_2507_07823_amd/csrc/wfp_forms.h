@@ -1,0 +1,40 @@
+// Which form the local sum takes: the layout of the distance bins, and the
+// rules that choose between sums by bins, pair by pair and from stored weights.
+// Pure C++, no HIP.
+#pragma once
+
+#include <array>
+#include <cstdint>
+#include <vector>
+
+namespace wfp {
+
+// Distance bins of the local sum (the kernels are in wfp_bins.hip): bins per
+// chunk, lookup cells per chunk, the most lags (13 steps of 4) and bins.  With
+// one quadrature node per lag of the window the bins end at W = 36.
+constexpr int kBinChunk = 64, kBinCells = 4096, kMaxBinLags = 52, kMaxBins = 768;
+
+// The bins of a window and a quadrature rule: edges (units of dt and distances,
+// padded to whole chunks), lookup cells and chunks; the kernel's steps of four
+// lags and the most edges within a cell.
+struct BinLayout {
+  int nbins = 0, nch = 0, ks = 0, bumps = 0;
+  std::vector<double> D, edge, scales;
+  std::vector<std::array<int, 4>> chunk;      // first cell, cells, their place, first steps of the halves
+  std::vector<unsigned char> cells;
+};
+
+// Of a window of W steps of dt and parameter b, order p and quadrature nodes
+// glz; false where they do not fit the kernel's limits.
+bool bin_layout(int W, int p, double b, double dt, const std::vector<double>& glz, BinLayout& B);
+
+// Microseconds of a level's local sum with the weights on the fly, for so many
+// springs in the launch and neighbours a spring on average.
+double bins_us(const BinLayout& B, double springs, double neighbours);
+double pairs_us(int W, int p, double springs, double neighbours);
+
+// Whether weights on the fly are summed by bins; `gradient`: of a plan that
+// keeps levels for gradients.
+bool bins_over_pairs(const BinLayout& B, int W, int p, double springs, double neighbours, bool gradient);
+
+}  // namespace wfp

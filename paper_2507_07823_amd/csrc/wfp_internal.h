@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "../../include/wfp.h"
+#include "wfp_forms.h"
 #include "wfp_host.h"
 #include "wfp_kernels.h"
 
@@ -32,13 +33,8 @@ extern thread_local std::string g_last_error;
 // 35 % at 1373)
 constexpr double kPairOnceNeighbours = 96.0;
 
-// mean neighbours per spring from which weights on the fly are summed by
-// distance bins (measured on one MI355X, local sum in us by bins against pair
-// by pair: 85 / 74 at 97, M = 7e3; 999 / 733 at 101, M = 1e5, p = 6; 236 / 248
-// at 116, M = 2e4; 156 / 181 at 138, M = 1e4; 1047 / 3494 at 578, M = 1e5)
-constexpr double kBinNeighbours = 112.0;
-
-// and from which local_mode 0 prefers them to weights stored once per pair
+// mean neighbours per spring from which local_mode 0 prefers sums by distance
+// bins to weights stored once per pair
 // (the same at 289, M = 5e4: 549 / 449; at 413, M = 3e4: 328 / 347; at 578,
 // M = 1e5: 1047 / 1563; at 687, M = 5e4: 581 / 900; stored weights overlap the
 // history chain, these do not)

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "wfp_forms.h"
+
 namespace wfp {
 
 constexpr int kMaxFftStages = 24;
@@ -61,11 +63,9 @@ constexpr int kOtfRows = 16, kOtfChunk = 256;
 // wavefronts of a pair-once reduce workgroup (64 rows, one per lane)
 constexpr int kReduceWaves = 16;
 // Local sum by distance bins (wfp_bins.hip): columns (sources, or sources x
-// histories) per workgroup, bins per LDS chunk, targets side by side in a
-// wavefront, threads, lookup cells per chunk, the most lags (13 steps of 4) and
-// bins, steps between the K0
-constexpr int kBinColumns = 32, kBinChunk = 64, kBinTargets = 16, kBinThreads = 1024, kBinCells = 4096;
-constexpr int kMaxBinLags = 52, kMaxBins = 768, kBinSkip = 2;
+// histories) per workgroup, targets side by side in a wavefront, threads, steps
+// between the K0
+constexpr int kBinColumns = 32, kBinTargets = 16, kBinThreads = 1024, kBinSkip = 2;
 // LDS records of a column: a bin each, zero records on both sides; spaced so
 // that the columns a wavefront reads at once fall on different banks
 constexpr int kBinRecords = kBinChunk + 4;

@@ -335,71 +335,6 @@ void bin_blocks(wfp_plan* P, int nsrc, wfp_plan::BinBlocks& K) {
   HIPCHK(hipStreamSynchronize(s));
 }
 
-// The bins of a window and a quadrature rule, on the host: edges (units of dt
-// and distances, padded to whole chunks), lookup cells and chunks.
-struct BinLayout {
-  int nbins = 0, nch = 0, ks = 0, bumps = 0;
-  std::vector<double> D, edge, scales;
-  std::vector<int4> chunk;
-  std::vector<unsigned char> cells;
-};
-
-// False where they do not fit the kernel's limits.
-bool bin_layout(const wfp_plan* P, const std::vector<double>& glz, BinLayout& B) {
-  if (P->p > 8 || P->NQ > kMaxBinLags) return false;
-  // bin width: 0.1 dt leaves the degree-7 polynomials of the default window
-  // (b / W = 0.79) and p <= 8 within 1.4e-16 of the weights (p = 10 and 12 need
-  // more terms); a steeper window takes narrower bins
-  const double hmax = 0.1 * std::min(1.0, P->W / P->b * (27.631 / 35.0));
-  B.D = bin_edges(P->W, P->p, glz, hmax);
-  std::vector<double>&D = B.D, &edge = B.edge, &scales = B.scales;
-  std::vector<int4>& chunk = B.chunk;
-  std::vector<unsigned char>& cells = B.cells;
-  B.nbins = (int)D.size() - 1;
-  B.nch = (int)nblk(B.nbins, kBinChunk);
-  const int npad = B.nch * kBinChunk;
-  if (npad > kMaxBins) return false;
-  D.resize(npad + 1, D.back());
-  edge.assign(npad + 1, P->delta);
-  for (int i = 0; i < B.nbins; ++i) edge[i] = D[i] * P->dt;
-  // lookup cells of a chunk: as narrow as its narrowest bin (then a cell holds
-  // one edge at most) while they fit in kBinCells; at each cell's start the
-  // record (0 below the chunk, then one per bin), four to a word
-  scales.resize(B.nch);
-  chunk.resize(B.nch);
-  for (int c = 0; c < B.nch; ++c) {
-    const double* e = &edge[c * kBinChunk];
-    const int n = std::min(kBinChunk, B.nbins - c * kBinChunk);   // padding bins are empty
-    double narrow = P->delta;
-    for (int i = 0; i < n; ++i) narrow = std::min(narrow, e[i + 1] - e[i]);
-    const double sc = scales[c] = std::min(1.01 / narrow, (kBinCells - 8) / (e[n] - e[0]));
-    auto record = [&](double v) {
-      const int r = (int)(std::upper_bound(e, e + n + 1, v) - e);
-      return r > n ? kBinChunk + 1 : r;
-    };
-    const int c0 = (int)std::floor(e[0] * sc) - 1, c1 = (int)std::floor(e[n] * sc) + 1;
-    chunk[c] = make_int4(c0, c1 - c0 + 1, (int)(cells.size() / 4), 0);
-    if (c1 - c0 + 1 > kBinCells) return false;
-    for (int i = c0; i <= c1; ++i) {
-      const int r0 = record(i / sc - 1e-12 * P->delta), r1 = record((i + 1) / sc + 1e-12 * P->delta);
-      cells.push_back((unsigned char)r0);
-      B.bumps = std::max(B.bumps, std::min(r1, n + 1) - r0);
-    }
-    while (cells.size() % 4) cells.push_back((unsigned char)(kBinChunk + 1));
-  }
-  B.ks = (int)nblk(P->NQ, 4) <= 10 && B.bumps <= 2 ? 10 : 13;
-  if (B.bumps > 4) return false;
-  // first lag with weight in each half of a chunk (the lowest node's stencil
-  // at its lower edge), as steps of four lags
-  const double amax = 0.5 * (1.0 + *std::max_element(glz.begin(), glz.end()));
-  auto step0 = [&](int bin) {
-    const double d = D[bin];
-    return std::max(0, (int)std::floor(P->W - (P->W - d) * amax - 1e-6) - P->p / 2 + 1) / 4;
-  };
-  for (int c = 0; c < B.nch; ++c) chunk[c].w = step0(c * kBinChunk) | step0(c * kBinChunk + kBinChunk / 2) << 16;
-  return true;
-}
-
 // The bins, the table and the blocks of the local sum on the device.
 void build_bins(wfp_plan* P, const BinLayout& H) {
   wfp_plan::Bins& B = P->bins;
@@ -416,7 +351,8 @@ void build_bins(wfp_plan* P, const BinLayout& H) {
   upload(B.D, H.D, s);
   upload(B.edge, H.edge, s);
   HIPCHK(hipMemcpyAsync(B.cells, H.cells.data(), H.cells.size(), hipMemcpyHostToDevice, s));
-  upload(B.chunk, H.chunk, s);
+  static_assert(sizeof(int4) == sizeof(H.chunk[0]), "a chunk is four ints");
+  HIPCHK(hipMemcpyAsync(B.chunk, H.chunk.data(), H.chunk.size() * sizeof(int4), hipMemcpyHostToDevice, s));
   upload(B.scales, H.scales, s);
   B.C = bin_table(P, 0);
   HIPCHK(hipStreamSynchronize(s));
@@ -739,7 +675,10 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
   bool by_bins = false;
   {
     int mode = par->local_mode;
-    if ((mode == 0 || mode == 2) && (double)P->n_pairs >= kBinNeighbours * (double)M) by_bins = bin_layout(P, glz, bins);
+    const double mean = (double)P->n_pairs / (double)M;
+    if (mode == 0 || mode == 2)
+      by_bins = bin_layout(P->W, P->p, P->b, P->dt, glz, bins) &&
+                bins_over_pairs(bins, P->W, P->p, (double)M, mean, P->ckpt_every != 0);
     if (mode == 0) {
       // once per unordered pair (about half the set-up array and packed
       // weights) when that fits and either the springs have enough neighbours
@@ -2461,6 +2400,7 @@ wfp_status wfp_plan_info(const wfp_plan* P, wfp_info* info) {
   info->solve_mode = P->solve_global ? 1 : 0;
   info->overlap_cus = P->overlap_cus;
   info->local_mode = P->sym_stored ? 3 : (P->otf ? 2 : 1);
+  info->local_bins = P->use_bins ? 1 : 0;
   info->n_weights_lag1 = P->n_weights_lag1;
   info->n_solve_tiles = P->solve_global ? 0 : P->ntile;
   info->n_direct_tiles = P->solve_global ? 0 : P->n_direct_tiles;

@@ -1,0 +1,152 @@
+// Checks of the local sum's forms (paper_2507_07823_amd/csrc/wfp_forms.cpp), built
+// with the sanitizers by tests/test_host_bins.py: the look-up of a distance's bin
+// over the layouts, and the rules against measured times.  Exit status 0 when
+// every check holds.
+#include <algorithm>
+#include <cmath>
+#include <cstdio>
+#include <random>
+#include <vector>
+
+#include "../../paper_2507_07823_amd/csrc/wfp_bins.h"
+#include "../../paper_2507_07823_amd/csrc/wfp_forms.h"
+#include "../../paper_2507_07823_amd/csrc/wfp_host.h"
+
+using namespace wfp;
+
+static int failures = 0;
+#define CHECK(c, ...)                                           \
+  do {                                                          \
+    if (!(c)) {                                                 \
+      std::fprintf(stderr, "FAIL %s:%d: ", __FILE__, __LINE__); \
+      std::fprintf(stderr, __VA_ARGS__);                        \
+      std::fprintf(stderr, "\n");                               \
+      ++failures;                                               \
+    }                                                           \
+  } while (0)
+
+static bool layout(int W, int p, double eps, int ngl, double dt, BinLayout& B) {
+  std::vector<double> z, w;
+  gauss_legendre(ngl, z, w);
+  return bin_layout(W, p, std::log(1.0 / eps), dt, z, B);
+}
+
+// The kernel's look-up of a distance in a chunk: the cell's record, then at most
+// `bumps` edges (two for the kernel of layouts with one), record r = bin r - 1.
+static int look_up(const BinLayout& B, int c, double z) {
+  const int* ch = B.chunk[c].data();
+  const int at = bin_cell(z, B.scales[c], ch[0], ch[1] - 1);
+  CHECK(at >= 0 && at < ch[1] && 4 * ch[2] + at < (int)B.cells.size(), "cell %d of %d", at, ch[1]);
+  int r = B.cells[4 * ch[2] + at];
+  const int bumps = B.ks == 13 ? 4 : std::max(1, B.bumps);
+  for (int s = 0; s < bumps; ++s) {
+    const double top = r <= kBinChunk ? B.edge[c * kBinChunk + r] : 1e300;
+    if (z >= top) ++r;
+  }
+  return r;
+}
+
+static void check_look_up() {
+  std::mt19937_64 g(3);
+  std::uniform_real_distribution<double> u(0.0, 1.0);
+  int fits = 0;
+  for (int p : {2, 4, 6, 8})
+    for (double eps : {1e-3, 1e-6, 1e-9, 1e-12})
+      for (double dt : {5e-3, 1e-5, 2e-7}) {
+        const int W = (int)std::lround(2.0 * std::log(1.0 / eps) / (kPi * 0.5));
+        for (int ngl : {W, 30}) {
+          BinLayout B;
+          if (!layout(W, p, eps, ngl, dt, B)) continue;
+          ++fits;
+          CHECK(B.bumps >= 1 && B.bumps <= 4 && (B.ks == 13 || (B.bumps <= 2 && W + p / 2 <= 40)), "kernel limits");
+          std::vector<double> zs{0.0, W * dt, 1.0, 6.0, 1e30};
+          for (int i = 0; i < 2000; ++i) zs.push_back(1.1 * W * dt * u(g));
+          for (double e : B.edge)
+            for (int k = -1; k <= 1; ++k) zs.push_back(std::fabs(e * (1.0 + k * 2.3e-16)));
+          for (double z : zs)
+            for (int c = 0; c < B.nch; ++c) {
+              const int r = look_up(B, c, z);
+              const double* e = &B.edge[c * kBinChunk];
+              // below the chunk, in its bin r - 1, or above (empty bins and beyond)
+              const bool ok = z < e[0] ? r == 0 : (z >= e[kBinChunk] ? r >= 1 && (r == kBinChunk + 1 || e[r - 1] == e[r])
+                                                                      : r >= 1 && r <= kBinChunk && z >= e[r - 1] && z < e[r]);
+              CHECK(ok, "W %d p %d eps %g: distance %.17g in chunk %d: record %d", W, p, eps, z, c, r);
+              if (failures > 5) return;
+            }
+        }
+      }
+  CHECK(fits >= 60, "%d layouts fit", fits);
+  // limits: too many bins, too high an order
+  BinLayout B;
+  CHECK(!layout(37, 8, 1e-12, 37, 1e-3, B) && !layout(35, 8, 1e-12, 40, 1e-3, B) && !layout(35, 10, 1e-12, 35, 1e-3, B),
+        "layouts beyond the limits");
+  CHECK(layout(18, 8, 1e-6, 18, 1e-3, B) && B.ks == 13 && layout(36, 8, 1e-12, 36, 1e-3, B) && B.ks == 10, "steps");
+}
+
+// Measured levels: time pair by pair over time by bins, at so many springs and
+// neighbours, of marches and gradients.  The rule takes no form that measured
+// 1.1 times slower, nor leaves one that measured 1.3 times faster.
+struct Row {
+  int W;
+  double eps;
+  int p, M, n, gradient;
+  double ratio;
+};
+static const Row kRows[] = {
+    {35, 1e-12, 2, 2000, 134, 0, 0.589}, {35, 1e-12, 2, 2000, 223, 0, 0.697}, {35, 1e-12, 2, 2000, 379, 0, 0.841},
+    {35, 1e-12, 2, 20000, 137, 0, 0.681}, {35, 1e-12, 2, 20000, 231, 0, 0.833},
+    {35, 1e-12, 2, 20000, 398, 0, 1.059}, {35, 1e-12, 2, 100000, 137, 0, 0.660},
+    {35, 1e-12, 2, 100000, 231, 0, 0.757}, {35, 1e-12, 2, 100000, 400, 0, 1.113},
+    {35, 1e-12, 4, 2000, 134, 0, 0.674}, {35, 1e-12, 4, 2000, 223, 0, 0.799}, {35, 1e-12, 4, 2000, 379, 0, 0.968},
+    {35, 1e-12, 4, 20000, 137, 0, 0.833}, {35, 1e-12, 4, 20000, 231, 0, 1.015},
+    {35, 1e-12, 4, 20000, 398, 0, 1.369}, {35, 1e-12, 4, 100000, 137, 0, 0.829},
+    {35, 1e-12, 4, 100000, 231, 0, 0.960}, {35, 1e-12, 4, 100000, 400, 0, 1.449},
+    {35, 1e-12, 6, 2000, 134, 0, 0.809}, {35, 1e-12, 6, 2000, 223, 0, 0.937}, {35, 1e-12, 6, 2000, 379, 0, 1.162},
+    {35, 1e-12, 6, 20000, 137, 0, 1.023}, {35, 1e-12, 6, 20000, 231, 0, 1.239},
+    {35, 1e-12, 6, 20000, 398, 0, 1.640}, {35, 1e-12, 6, 100000, 137, 0, 1.047},
+    {35, 1e-12, 6, 100000, 231, 0, 1.220}, {35, 1e-12, 6, 100000, 400, 0, 1.858},
+    {35, 1e-12, 8, 2000, 134, 0, 0.917}, {35, 1e-12, 8, 2000, 223, 0, 1.056}, {35, 1e-12, 8, 2000, 379, 0, 1.312},
+    {35, 1e-12, 8, 20000, 137, 0, 1.201}, {35, 1e-12, 8, 20000, 231, 0, 1.449},
+    {35, 1e-12, 8, 20000, 398, 0, 1.974}, {35, 1e-12, 8, 100000, 137, 0, 1.246},
+    {35, 1e-12, 8, 100000, 231, 0, 1.455}, {35, 1e-12, 8, 100000, 400, 0, 2.244},
+    {18, 1e-06, 2, 2000, 134, 0, 0.771}, {18, 1e-06, 2, 2000, 379, 0, 0.969},
+    {18, 1e-06, 2, 20000, 137, 0, 0.819}, {18, 1e-06, 2, 20000, 231, 0, 0.937},
+    {18, 1e-06, 2, 20000, 398, 0, 1.149}, {18, 1e-06, 4, 2000, 134, 0, 0.751},
+    {18, 1e-06, 4, 2000, 379, 0, 0.946}, {18, 1e-06, 4, 20000, 137, 0, 0.816},
+    {18, 1e-06, 4, 20000, 231, 0, 0.956}, {18, 1e-06, 4, 20000, 398, 0, 1.194},
+    {18, 1e-06, 6, 2000, 134, 0, 0.819}, {18, 1e-06, 6, 2000, 379, 0, 1.044},
+    {18, 1e-06, 6, 20000, 137, 0, 0.914}, {18, 1e-06, 6, 20000, 231, 0, 1.065},
+    {18, 1e-06, 6, 20000, 398, 0, 1.349}, {18, 1e-06, 8, 2000, 134, 0, 0.951},
+    {18, 1e-06, 8, 2000, 379, 0, 1.214}, {18, 1e-06, 8, 20000, 137, 0, 1.153},
+    {18, 1e-06, 8, 20000, 231, 0, 1.344}, {18, 1e-06, 8, 20000, 398, 0, 1.732},
+    {20, 1e-12, 2, 20000, 137, 0, 0.653}, {20, 1e-12, 2, 20000, 231, 0, 0.756},
+    {20, 1e-12, 2, 20000, 398, 0, 0.952}, {20, 1e-12, 4, 20000, 137, 0, 0.745},
+    {20, 1e-12, 4, 20000, 231, 0, 0.883}, {20, 1e-12, 4, 20000, 398, 0, 1.128},
+    {20, 1e-12, 6, 20000, 137, 0, 0.848}, {20, 1e-12, 6, 20000, 231, 0, 1.014},
+    {20, 1e-12, 6, 20000, 398, 0, 1.325}, {20, 1e-12, 8, 20000, 137, 0, 1.024},
+    {20, 1e-12, 8, 20000, 231, 0, 1.239}, {20, 1e-12, 8, 20000, 398, 0, 1.653},
+    {35, 1e-12, 2, 30000, 137, 1, 0.527}, {35, 1e-12, 2, 30000, 231, 1, 0.762},
+    {35, 1e-12, 2, 30000, 399, 1, 1.027}, {35, 1e-12, 4, 30000, 137, 1, 0.648},
+    {35, 1e-12, 4, 30000, 231, 1, 0.948}, {35, 1e-12, 4, 30000, 399, 1, 1.303},
+    {35, 1e-12, 6, 30000, 137, 1, 0.826}, {35, 1e-12, 6, 30000, 231, 1, 1.222},
+    {35, 1e-12, 6, 30000, 399, 1, 1.695}, {35, 1e-12, 8, 30000, 137, 1, 1.010},
+    {35, 1e-12, 8, 30000, 231, 1, 1.506}, {35, 1e-12, 8, 30000, 399, 1, 2.106},
+};
+
+static void check_pairs_rule() {
+  for (const Row& r : kRows) {
+    BinLayout B;
+    CHECK(layout(r.W, r.p, r.eps, r.W, 1e-3, B), "layout");
+    const bool bins = bins_over_pairs(B, r.W, r.p, r.M, r.n, r.gradient != 0);
+    CHECK(bins ? r.ratio > 1.0 / 1.1 : r.ratio < 1.3, "W %d p %d M %d, %d neighbours, gradient %d: by bins %d, measured %.2f",
+          r.W, r.p, r.M, r.n, r.gradient, bins, r.ratio);
+  }
+}
+
+int main() {
+  check_look_up();
+  check_pairs_rule();
+  if (failures) return 1;
+  std::printf("form checks passed\n");
+  return 0;
+}
