@@ -115,7 +115,8 @@ typedef struct {
                               per unordered pair (Q_m depends on the distance alone) and applied to
                               both rows, about half the bytes of 1 (the gradient pass's
                               derivative weights likewise); 0: 2 by bins from 512 neighbours per spring
-                              on (p <= 8, W + p/2 <= 46); else 3 when half of
+                              on (p <= 8, W + p/2 <= 46) where the level is shorter so (M = 3000: from
+                              1300 neighbours, M = 3e4: from 512); else 3 when half of
                               the per-pair set-up fits in 60% of the free device memory and
                               either the springs have 96 or more neighbours on average or the
                               per-pair weights would not fit, else 1 when they fit, else on

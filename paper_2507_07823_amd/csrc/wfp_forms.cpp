@@ -105,7 +105,29 @@ double pairs_us(int W, int p, double springs, double neighbours) {
 // 237, 307 and 372), where that pass leaves the chip idle.
 bool bins_over_pairs(const BinLayout& B, int W, int p, double springs, double neighbours, bool gradient) {
   const double share = !gradient ? 1.0 : (springs < 4096.0 ? 0.9 : 1.17);
-  return neighbours >= 112.0 && share * bins_us(B, springs, neighbours) <= pairs_us(W, p, springs, neighbours);
+  return neighbours >= kBinNeighbours && share * bins_us(B, springs, neighbours) <= pairs_us(W, p, springs, neighbours);
+}
+
+// Bound by the weights' stream (W / 2 + p lags a pair), or by a row's range on
+// small problems.  Measured (model) at W = 35, p = 8: M = 600 and 416 neighbours 39
+// us (41), 1e3 and 708 59 (54), 3e3 and 536 56 (58), 1e4 and 553 166 (163), 3e4 and
+// 559 444 (465); p = 4 at 3e4 382 (395).
+double once_us(int W, int p, double springs, double neighbours) {
+  const double bytes = 8.0 * 0.5 * springs * neighbours * (0.5 * W + p);
+  return std::max(22.0 + 0.045 * neighbours, 15.0 + bytes / 3.8e6);
+}
+
+// From 64 MB of weights on stored sums run beside the history chain, which then
+// costs no time of its own (25 us); but where the springs closer than dt are so many
+// (28) that the solve goes by global sweeps, the sweeps wait for compute units (25
+// us the other way).  A gradient runs on one stream.  Levels measured, stored over
+// by bins, at W = 35 and p = 8: 0.80 at M = 3e3 and 914 neighbours, 1.25 at 1305; 0.81
+// at 5e3 and 544; 0.97 at 1e4 and 553, 1.25 at 880; 1.43 at 3e4 and 559; p = 4: 0.76 at
+// 1e4 and 553, 1.06 at 880; 1.18 at 3e4 and 559.
+bool bins_over_once(const BinLayout& B, int W, int p, double springs, double neighbours, double nearby, bool gradient) {
+  const bool beside = !gradient && 4.0 * springs * neighbours * (0.5 * W + p) >= 64.0 * 1024 * 1024;
+  const double chain = !beside ? 0.0 : (nearby >= 28.0 ? -25.0 : 25.0);
+  return neighbours >= 512.0 && 1.02 * bins_us(B, springs, neighbours) + chain <= once_us(W, p, springs, neighbours);
 }
 
 }  // namespace wfp

@@ -33,8 +33,17 @@ bool bin_layout(int W, int p, double b, double dt, const std::vector<double>& gl
 double bins_us(const BinLayout& B, double springs, double neighbours);
 double pairs_us(int W, int p, double springs, double neighbours);
 
+// No plan with fewer neighbours a spring takes bins.
+constexpr double kBinNeighbours = 112.0;
+
 // Whether weights on the fly are summed by bins; `gradient`: of a plan that
 // keeps levels for gradients.
 bool bins_over_pairs(const BinLayout& B, int W, int p, double springs, double neighbours, bool gradient);
+
+// Microseconds of a level's local sum with the weights stored once per unordered
+// pair, and whether local_mode 0 takes bins in its place; `nearby`: springs closer
+// than dt on average.
+double once_us(int W, int p, double springs, double neighbours);
+bool bins_over_once(const BinLayout& B, int W, int p, double springs, double neighbours, double nearby, bool gradient);
 
 }  // namespace wfp

@@ -33,13 +33,8 @@ extern thread_local std::string g_last_error;
 // 35 % at 1373)
 constexpr double kPairOnceNeighbours = 96.0;
 
-// mean neighbours per spring from which local_mode 0 prefers sums by distance
-// bins to weights stored once per pair
-// (the same at 289, M = 5e4: 549 / 449; at 413, M = 3e4: 328 / 347; at 578,
-// M = 1e5: 1047 / 1563; at 687, M = 5e4: 581 / 900; stored weights overlap the
-// history chain, these do not)
-constexpr double kBinsOverPairs = 512.0;
-// and from which batch instances do (their launches fill the chip together)
+// mean neighbours per spring from which batch instances prefer sums by distance
+// bins to stored weights (their launches fill the chip together)
 constexpr double kBatchBinsOverPairs = 400.0;
 // LDS of the pair-once stored local sum for H value sets.
 inline size_t sym_lds(int NQ, int H) { return (size_t)H * NQ * (kSymChunk / H + 2) * sizeof(double); }

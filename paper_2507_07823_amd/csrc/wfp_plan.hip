@@ -676,7 +676,7 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
   {
     int mode = par->local_mode;
     const double mean = (double)P->n_pairs / (double)M;
-    if (mode == 0 || mode == 2)
+    if ((mode == 0 || mode == 2) && mean >= kBinNeighbours)
       by_bins = bin_layout(P->W, P->p, P->b, P->dt, glz, bins) &&
                 bins_over_pairs(bins, P->W, P->p, (double)M, mean, P->ckpt_every != 0);
     if (mode == 0) {
@@ -692,7 +692,10 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
       const double need = 8.0 * (double)tot * 1.7;
       const bool fits1 = need < 0.6 * (double)fr, fits3 = 0.5 * need < 0.6 * (double)fr;
       const bool dense = (double)P->n_pairs >= kPairOnceNeighbours * (double)M;
-      if (by_bins && P->NQ <= kMaxOtfGradLags && (double)P->n_pairs >= kBinsOverPairs * (double)M) mode = 2;
+      const double nearby = (double)std::accumulate(nc.begin(), nc.end(), (int64_t)0) / (double)M - 1.0;
+      if (by_bins && P->NQ <= kMaxOtfGradLags &&
+          bins_over_once(bins, P->W, P->p, (double)M, mean, nearby, P->ckpt_every != 0))
+        mode = 2;
       else if (fits3 && (dense || !fits1)) mode = 3;
       else if (fits1) mode = 1;
       else mode = 2;

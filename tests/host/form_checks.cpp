@@ -143,9 +143,51 @@ static void check_pairs_rule() {
   }
 }
 
+// The same for weights stored once per pair over sums by bins, with n / W springs
+// closer than dt.
+static const Row kStored[] = {
+    {35, 1e-12, 8, 1000, 708, 0, 0.616}, {35, 1e-12, 8, 3000, 536, 0, 0.640}, {35, 1e-12, 8, 3000, 914, 0, 0.800},
+    {35, 1e-12, 8, 3000, 1305, 0, 1.251}, {35, 1e-12, 8, 5000, 544, 0, 0.814},
+    {35, 1e-12, 8, 10000, 553, 0, 0.972}, {35, 1e-12, 8, 10000, 880, 0, 1.247},
+    {35, 1e-12, 8, 10000, 1446, 0, 1.900}, {35, 1e-12, 8, 30000, 559, 0, 1.434},
+    {35, 1e-12, 8, 30000, 895, 0, 2.013}, {35, 1e-12, 8, 60000, 559, 0, 1.420},
+    {35, 1e-12, 4, 1000, 708, 0, 0.739}, {35, 1e-12, 4, 3000, 536, 0, 0.541}, {35, 1e-12, 4, 3000, 914, 0, 0.655},
+    {35, 1e-12, 4, 3000, 1305, 0, 1.069}, {35, 1e-12, 4, 5000, 544, 0, 0.700},
+    {35, 1e-12, 4, 10000, 553, 0, 0.763}, {35, 1e-12, 4, 10000, 880, 0, 1.058},
+    {35, 1e-12, 4, 10000, 1446, 0, 1.616}, {35, 1e-12, 4, 30000, 559, 0, 1.176},
+    {35, 1e-12, 4, 30000, 895, 0, 1.651}, {35, 1e-12, 4, 60000, 559, 0, 1.150},
+    {18, 1e-06, 8, 1000, 708, 0, 0.844}, {18, 1e-06, 8, 3000, 536, 0, 1.181}, {18, 1e-06, 8, 3000, 914, 0, 1.274},
+    {18, 1e-06, 8, 3000, 1305, 0, 1.275}, {18, 1e-06, 8, 5000, 544, 0, 1.443},
+    {18, 1e-06, 8, 10000, 553, 0, 1.615}, {18, 1e-06, 8, 10000, 880, 0, 1.958},
+    {18, 1e-06, 8, 10000, 1446, 0, 2.072}, {18, 1e-06, 8, 30000, 559, 0, 2.336},
+    {18, 1e-06, 8, 30000, 895, 0, 2.828}, {18, 1e-06, 8, 60000, 559, 0, 1.521},
+    {18, 1e-06, 4, 1000, 708, 0, 0.753}, {18, 1e-06, 4, 3000, 536, 0, 1.097}, {18, 1e-06, 4, 3000, 914, 0, 1.187},
+    {18, 1e-06, 4, 3000, 1305, 0, 1.147}, {18, 1e-06, 4, 5000, 544, 0, 1.330},
+    {18, 1e-06, 4, 10000, 553, 0, 1.432}, {18, 1e-06, 4, 10000, 880, 0, 1.719},
+    {18, 1e-06, 4, 10000, 1446, 0, 1.772}, {18, 1e-06, 4, 30000, 559, 0, 2.048},
+    {18, 1e-06, 4, 30000, 895, 0, 2.452}, {18, 1e-06, 4, 60000, 559, 0, 1.105},
+    {35, 1e-12, 8, 1000, 708, 1, 0.977}, {35, 1e-12, 8, 3000, 536, 1, 0.986},
+    {35, 1e-12, 8, 10000, 553, 1, 1.142}, {35, 1e-12, 8, 20000, 558, 1, 1.207},
+    {35, 1e-12, 4, 1000, 708, 1, 0.898}, {35, 1e-12, 4, 3000, 536, 1, 0.896},
+    {35, 1e-12, 4, 10000, 553, 1, 0.982}, {35, 1e-12, 4, 20000, 558, 1, 1.033},
+    {18, 1e-06, 8, 1000, 708, 1, 1.158}, {18, 1e-06, 8, 3000, 536, 1, 1.089},
+    {18, 1e-06, 8, 10000, 553, 1, 1.297}, {18, 1e-06, 8, 20000, 558, 1, 1.358},
+};
+
+static void check_stored_rule() {
+  for (const Row& r : kStored) {
+    BinLayout B;
+    CHECK(layout(r.W, r.p, r.eps, r.W, 1e-3, B), "layout");
+    const bool bins = bins_over_once(B, r.W, r.p, r.M, r.n, (double)r.n / r.W, r.gradient != 0);
+    CHECK(bins ? r.ratio > 1.0 / 1.1 : r.ratio < 1.3, "W %d p %d M %d, %d neighbours, gradient %d: by bins %d, measured %.2f",
+          r.W, r.p, r.M, r.n, r.gradient, bins, r.ratio);
+  }
+}
+
 int main() {
   check_look_up();
   check_pairs_rule();
+  check_stored_rule();
   if (failures) return 1;
   std::printf("form checks passed\n");
   return 0;

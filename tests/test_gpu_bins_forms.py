@@ -65,6 +65,16 @@ def test_form_of_weights_on_the_fly(wfp, M, n, p, bins):
     plan.close()
 
 
+# springs, neighbours, order -> the library's choice
+@pytest.mark.parametrize("M,n,p,mode", [(1000, 900, 8, 3), (3000, 560, 8, 3), (3000, 1450, 8, 2), (5000, 560, 4, 3),
+                                        (10000, 560, 4, 3), (10000, 1000, 8, 2), (30000, 560, 8, 2), (30000, 400, 8, 3)])
+def test_form_by_default(wfp, M, n, p, mode):
+    prob = _problem("slab", M, 2e-4, n)
+    plan = wfp.Plan(prob, 2e-4, p=p, K=4000)
+    assert plan.info["local_mode"] == mode and plan.info["local_bins"] == (1 if mode == 2 else 0)
+    plan.close()
+
+
 # each layout (windows, quadratures, orders), and sizes at the edges of blocks (32
 # sources) and of the reduction's rows (64); steps of four lags: 10, or 13 in the
 # kernel that also takes cells with up to four edges
