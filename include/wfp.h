@@ -310,8 +310,10 @@ wfp_status wfp_plan_autotune(wfp_plan* plan, int32_t trial_levels, int32_t* over
  *                     local_mode 0 here: stored for the instances with the fewest
  *                     neighbour pairs while their weights fit in 45 % of the free
  *                     device memory, once per pair where the springs have 96 or
- *                     more neighbours or only half fits, else on the fly; on the
- *                     fly by bins from 400 neighbours per spring on, p = 8 and W + p/2 <= 40).
+ *                     more neighbours or only half fits, else on the fly; by bins
+ *                     from 400 neighbours per spring on (p = 8, W + p/2 <= 40, N_L <= 36)
+ *                     where the batch's instances of that kind make the launch the
+ *                     shorter one).
  *                     Synchronous.
  *                     Errors: WFP_EDOMAIN (free space, or an instance whose
  *                     stages exceed the LDS), WFP_EINVAL (checkpoint_every != 0:

@@ -1,9 +1,12 @@
 // Batched form: many independent periodic problems marched in lockstep, each
 // stage of a level one launch over an (instance, block) work list, the whole
 // level captured once in a HIP graph (the level index lives on the device).
-// Each instance is an ordinary plan (wfp_plan_create); the batch only adds the
+// Each instance is an ordinary plan (create_plan); the batch only adds the
 // descriptor table, the work lists, the graph and the launch-shape autotuner.
 #include "wfp_internal.h"
+
+#include <map>
+#include <tuple>
 
 struct wfp_batch {
   int device = 0;
@@ -67,9 +70,6 @@ struct wfp_batch {
 };
 
 namespace {
-
-// The batched kernel by distance bins takes up to 40 lags.
-bool batched_bins(const wfp_plan* P) { return P->use_bins && P->bins.ks == 10 && P->bins.bumps <= 2; }
 
 InstDesc describe(const wfp_plan* P) {
   InstDesc d{};
@@ -166,7 +166,7 @@ InstDesc describe(const wfp_plan* P) {
   d.otf_nw = P->otf_nw;
   d.otf_part = P->otf_part;
   d.otf_rowacc = P->otf_rowacc;
-  if (batched_bins(P)) d.bins = P->bin_args(P->bblk, P->bins.C);
+  if (P->use_bins) d.bins = P->bin_args(P->bblk, P->bins.C);
   d.sym = P->sym_stored ? 1 : 0;
   d.sym_spl = P->sym_spl;
   d.sym_rb = P->sym_rb;
@@ -229,10 +229,6 @@ void build_batch(wfp_batch* B) {
   for (int i = 0; i < n; ++i) {
     // the spread grid of the separate spread pass
     if (!B->plans[i]->gsp) B->plans[i]->gsp = B->plans[i]->alloc<double>(B->plans[i]->nf);
-    if (B->plans[i]->use_bins && !batched_bins(B->plans[i])) {
-      B->plans[i]->otf_part = B->plans[i]->alloc<double>(B->plans[i]->otf_tot_part);
-      B->plans[i]->otf_rowacc = B->plans[i]->alloc<double>(B->plans[i]->M);
-    }
     const wfp_plan* P = B->plans[i];
     desc[i] = describe(P);
     for (int b = 0; b < (int)nblk(P->nf, 256); ++b) sp.push_back(make_int2(i, b));
@@ -245,7 +241,7 @@ void build_batch(wfp_batch* B) {
       for (int bb = 0; bb < (int)nblk(M, 64); ++bb) symr.push_back(make_int2(i, bb));
     } else if (P->otf) {
       if (P->p != 8) fail(WFP_EDOMAIN, "batched on-the-fly local sums take p = 8");
-      if (batched_bins(P)) {
+      if (P->use_bins) {
         bin.push_back(make_int2(i, P->bblk.nblk));
         for (int bb = 0; bb < (int)nblk(M, 64); ++bb) binr.push_back(make_int2(i, bb));
       } else {
@@ -492,35 +488,69 @@ int64_t count_pairs(const double* x, int64_t M, double delta) {
   return tot;
 }
 
-// Local-weight mode of every instance whose parameters leave it to the
-// library: by distance bins for springs with many neighbours; of the others,
-// stored weights for the instances with the fewest pairs while their
-// packed weights fit in 45 % of the free device memory (and the set-up array
-// of one instance in 25 %), on the fly for the rest.
-std::vector<int> choose_local_modes(int n, const wfp_problem* probs, const wfp_params* pars) {
+// Local-weight mode of an instance, and the form of its weights on the fly.
+struct Form {
+  int mode = 0;
+  OtfForm otf = OtfForm::kPairs;
+};
+
+// Of every instance.  Where the parameters leave the mode to the library: by
+// distance bins for springs with many neighbours, as far as that is the shorter
+// launch; of the others, stored weights for the instances with the fewest pairs
+// while their packed weights fit in 45 % of the free device memory (and the set-up
+// array of one instance in 25 %), on the fly for the rest.  The batched kernel by
+// bins takes p = 8 and ten steps of four lags; where an instance's bins do not fit
+// it, weights on the fly go pair by pair.
+std::vector<Form> choose_forms(int n, const wfp_problem* probs, const wfp_params* pars) {
   size_t fr = 0, to = 0;
   HIPCHK(hipMemGetInfo(&fr, &to));
-  std::vector<int> mode(n);
-  std::vector<std::pair<double, int>> cand;
-  std::vector<double> packed(n), dense(n);
-  std::vector<char> many(n, 0);
+  std::vector<Form> form(n);
+  std::vector<double> pairs(n, 0.0), packed(n), dense(n);
+  std::vector<char> fits(n, 0);                   // the batched kernel by bins
+  std::map<std::tuple<int, int, double, double>, BinLayout> layouts;   // nch = 0: does not fit
+  BinLayout most;
+  int longest = 0;
+  double springs[2] = {0, 0}, all[2] = {0, 0};    // of the library's choice, and of weights on the fly
+  auto group = [&](int i) { return pars[i].local_mode == 0 ? 0 : 1; };
+  auto candidate = [&](int i) {
+    return fits[i] && pairs[i] >= (group(i) ? kBinNeighbours : kBatchBinNeighbours) * (double)probs[i].M;
+  };
   for (int i = 0; i < n; ++i) {
-    mode[i] = pars[i].local_mode;
-    if (mode[i] != 0) continue;
+    form[i].mode = pars[i].local_mode;
+    if (form[i].mode != 0 && form[i].mode != 2) continue;
     const double eps = pars[i].eps_window > 0 ? pars[i].eps_window : 1e-12;
     const double gamma = pars[i].gamma > 0 ? pars[i].gamma : 0.5;
     const int W = pars[i].W > 0 ? pars[i].W : (int)std::lround(2.0 * std::log(1.0 / eps) / (kPi * gamma));
-    const int p = pars[i].p > 0 ? pars[i].p : 8;
-    const double pairs = (double)count_pairs(probs[i].x, probs[i].M, W * pars[i].dt);
-    packed[i] = 8.0 * pairs * (W / 2 + p);        // nonzero lags per pair
-    dense[i] = 8.0 * pairs * (W + p / 2);
-    many[i] = pairs >= kPairOnceNeighbours * (double)probs[i].M ? 1 : 0;
-    // by distance bins (the batched kernel takes p = 8 and up to 40 lags)
-    if (p == 8 && W + p / 2 <= 40 && pairs >= kBatchBinsOverPairs * (double)probs[i].M) {
-      mode[i] = 2;
-      continue;
+    const int p = pars[i].p > 0 ? pars[i].p : 8, ngl = pars[i].n_gl_local > 0 ? pars[i].n_gl_local : W;
+    pairs[i] = (double)count_pairs(probs[i].x, probs[i].M, W * pars[i].dt);
+    packed[i] = 8.0 * pairs[i] * (W / 2 + p);     // nonzero lags per pair
+    dense[i] = 8.0 * pairs[i] * (W + p / 2);
+    if (p != 8 || ngl > 64 || pairs[i] < kBinNeighbours * (double)probs[i].M) continue;
+    const auto key = std::make_tuple(W, ngl, eps, pars[i].dt);
+    if (!layouts.count(key)) {
+      std::vector<double> z, w;
+      gauss_legendre(ngl, z, w);
+      BinLayout B;
+      if (!bin_layout(W, p, std::log(1.0 / eps), pars[i].dt, z, B) || B.ks != 10) B.nch = 0;
+      layouts[key] = B;
     }
-    cand.push_back({packed[i], i});
+    const BinLayout& B = layouts[key];
+    fits[i] = B.nch > 0;
+    if (!candidate(i)) continue;
+    if (B.nch > most.nch) most = B;
+    longest = std::max(longest, W);
+    springs[group(i)] += (double)probs[i].M;
+    all[group(i)] += pairs[i];
+  }
+  const BatchBins bins = batch_bins(most, longest, springs[0], all[0], springs[1], all[1]);
+  std::vector<std::pair<double, int>> cand;
+  for (int i = 0; i < n; ++i) {
+    if (form[i].mode == 2 || (form[i].mode == 0 && bins.choice && candidate(i))) {
+      form[i].mode = 2;
+      if (candidate(i) && (group(i) ? bins.on_the_fly : bins.choice)) form[i].otf = OtfForm::kBins;
+    } else if (form[i].mode == 0) {
+      cand.push_back({packed[i], i});
+    }
   }
   std::sort(cand.begin(), cand.end());
   double used = 0.0;
@@ -528,19 +558,21 @@ std::vector<int> choose_local_modes(int n, const wfp_problem* probs, const wfp_p
     const int i = c.second;
     // as for a plan: once per unordered pair (half the bytes) for springs
     // with many neighbours or where per-pair weights would not fit
+    const bool many = pairs[i] >= kPairOnceNeighbours * (double)probs[i].M;
     const bool fits1 = used + packed[i] <= 0.45 * (double)fr && dense[i] <= 0.25 * (double)fr;
     const bool fits3 = used + 0.5 * packed[i] <= 0.45 * (double)fr && 0.5 * dense[i] <= 0.25 * (double)fr;
-    if (fits3 && (many[i] || !fits1)) {
-      mode[i] = 3;
+    if (fits3 && (many || !fits1)) {
+      form[i].mode = 3;
       used += 0.5 * packed[i];
     } else if (fits1) {
-      mode[i] = 1;
+      form[i].mode = 1;
       used += packed[i];
     } else {
-      mode[i] = 2;
+      form[i].mode = 2;
+      if (fits[i]) form[i].otf = OtfForm::kBins;
     }
   }
-  return mode;
+  return form;
 }
 
 }  // namespace
@@ -576,15 +608,20 @@ wfp_status wfp_batch_create(int32_t n, const wfp_problem* probs, const wfp_param
     HIPCHK(hipEventCreateWithFlags(&B->ev_out, hipEventDisableTiming));
     HIPCHK(hipEventCreateWithFlags(&B->ev_fork, hipEventDisableTiming));
     HIPCHK(hipEventCreateWithFlags(&B->ev_join, hipEventDisableTiming));
-    const std::vector<int> modes = choose_local_modes(n, probs, pars);
+    auto instance = [](int i) { return "instance " + std::to_string(i) + ": "; };
+    for (int32_t i = 0; i < n; ++i) {
+      const wfp_status s = guard([&] { validate(&probs[i], &pars[i]); });
+      if (s != WFP_OK) throw Error{s, instance(i) + g_last_error};
+    }
+    const std::vector<Form> forms = choose_forms(n, probs, pars);
     for (int32_t i = 0; i < n; ++i) {
       wfp_plan* P = nullptr;
       // the batch overlaps instances instead of streams: one stream per plan
       wfp_params pi = pars[i];
       pi.overlap_cus = -1;
-      pi.local_mode = modes[i];
-      const wfp_status s = wfp_plan_create(&probs[i], &pi, B->bs, &P);
-      if (s != WFP_OK) throw Error{s, "instance " + std::to_string(i) + ": " + g_last_error};
+      pi.local_mode = forms[i].mode;
+      const wfp_status s = create_plan(&probs[i], &pi, B->bs, forms[i].otf, &P);
+      if (s != WFP_OK) throw Error{s, instance(i) + g_last_error};
       B->plans.push_back(P);
     }
     build_batch(B);

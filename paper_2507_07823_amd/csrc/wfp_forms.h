@@ -46,4 +46,15 @@ bool bins_over_pairs(const BinLayout& B, int W, int p, double springs, double ne
 double once_us(int W, int p, double springs, double neighbours);
 bool bins_over_once(const BinLayout& B, int W, int p, double springs, double neighbours, double nearby, bool gradient);
 
+// The forms of a batch's instances that may go by bins: those whose mode is the
+// library's choice (stored once per pair otherwise) and those with weights on the
+// fly (pair by pair otherwise), each as one group.  W: the longest window; B: the
+// layout of most chunks.
+constexpr double kBatchBinNeighbours = 400.0;   // of the first group's instances, a spring
+struct BatchBins {
+  bool choice, on_the_fly;
+};
+BatchBins batch_bins(const BinLayout& B, int W, double choice_springs, double choice_pairs, double otf_springs,
+                     double otf_pairs);
+
 }  // namespace wfp

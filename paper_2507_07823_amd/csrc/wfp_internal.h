@@ -33,9 +33,6 @@ extern thread_local std::string g_last_error;
 // 35 % at 1373)
 constexpr double kPairOnceNeighbours = 96.0;
 
-// mean neighbours per spring from which batch instances prefer sums by distance
-// bins to stored weights (their launches fill the chip together)
-constexpr double kBatchBinsOverPairs = 400.0;
 // LDS of the pair-once stored local sum for H value sets.
 inline size_t sym_lds(int NQ, int H) { return (size_t)H * NQ * (kSymChunk / H + 2) * sizeof(double); }
 // most lags of the on-the-fly position gradient: local_mode 0 leaves longer
@@ -123,6 +120,14 @@ inline FftPlan make_fft_plan(int64_t n) {
 
 
 wfp_status guard(const std::function<void()>& f);
+
+// Host-only checks of the problem and parameters (no HIP call).
+void validate(const wfp_problem* prob, const wfp_params* par);
+
+// wfp_plan_create with the form of weights on the fly: by the plan's own rule,
+// pair by pair, or by bins wherever their layout fits.
+enum class OtfForm { kRule, kPairs, kBins };
+wfp_status create_plan(const wfp_problem* prob, const wfp_params* par, void* stream, OtfForm form, wfp_plan** out);
 
 }  // namespace wfpi
 

@@ -83,8 +83,10 @@ void zero_state(wfp_plan* P) {
   P->ck_from0 = true;
 }
 
-// Host-only checks of the problem and parameters (no HIP call), so invalid
-// input is reported before any device work.
+}  // namespace
+
+namespace wfpi {
+// Invalid input is reported before any device work.
 void validate(const wfp_problem* prob, const wfp_params* par) {
   if (!prob || !par) fail(WFP_EINVAL, "NULL problem or params");
   if (prob->M < 1) fail(WFP_EINVAL, "M must be >= 1");
@@ -141,6 +143,9 @@ void validate(const wfp_problem* prob, const wfp_params* par) {
         fail(WFP_EDOMAIN, "free space: receiver outside Omega");
   }
 }
+}  // namespace wfpi
+
+namespace {
 
 hipEvent_t take_event(wfp_plan* P) {
   if (!P->free_events.empty()) {
@@ -383,7 +388,7 @@ void launch_bins(wfp_plan* P, hipStream_t s, const double* hist, int64_t L, cons
   if (fwd) hipLaunchKernelGGL(k_local_bins_reduce, rows, threads, 0, s, (int)P->M, A, K.part2, scale, out2);
 }
 
-void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
+void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par, OtfForm form) {
   validate(prob, par);
   const int64_t M = prob->M;
   if (M < 1) fail(WFP_EINVAL, "M must be >= 1");
@@ -676,9 +681,9 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par) {
   {
     int mode = par->local_mode;
     const double mean = (double)P->n_pairs / (double)M;
-    if ((mode == 0 || mode == 2) && mean >= kBinNeighbours)
+    if ((mode == 0 || mode == 2) && form != OtfForm::kPairs && (form == OtfForm::kBins || mean >= kBinNeighbours))
       by_bins = bin_layout(P->W, P->p, P->b, P->dt, glz, bins) &&
-                bins_over_pairs(bins, P->W, P->p, (double)M, mean, P->ckpt_every != 0);
+                (form == OtfForm::kBins || bins_over_pairs(bins, P->W, P->p, (double)M, mean, P->ckpt_every != 0));
     if (mode == 0) {
       // once per unordered pair (about half the set-up array and packed
       // weights) when that fits and either the springs have enough neighbours
@@ -2340,11 +2345,8 @@ wfp_status guard(const std::function<void()>& f) {
     return WFP_EHIP;
   }
 }
-}  // namespace wfpi
 
-extern "C" {
-
-wfp_status wfp_plan_create(const wfp_problem* prob, const wfp_params* par, void* stream, wfp_plan** out) {
+wfp_status create_plan(const wfp_problem* prob, const wfp_params* par, void* stream, OtfForm form, wfp_plan** out) {
   if (!out) {
     g_last_error = "out is NULL";
     return WFP_EINVAL;
@@ -2356,7 +2358,7 @@ wfp_status wfp_plan_create(const wfp_problem* prob, const wfp_params* par, void*
     P = new wfp_plan();
     HIPCHK(hipGetDevice(&P->device));
     P->stream = (hipStream_t)stream;
-    build(P, prob, par);
+    build(P, prob, par, form);
   });
   if (st != WFP_OK) {
     delete P;
@@ -2364,6 +2366,13 @@ wfp_status wfp_plan_create(const wfp_problem* prob, const wfp_params* par, void*
   }
   *out = P;
   return WFP_OK;
+}
+}  // namespace wfpi
+
+extern "C" {
+
+wfp_status wfp_plan_create(const wfp_problem* prob, const wfp_params* par, void* stream, wfp_plan** out) {
+  return create_plan(prob, par, stream, OtfForm::kRule, out);
 }
 
 void wfp_plan_destroy(wfp_plan* plan) {

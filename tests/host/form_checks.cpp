@@ -184,7 +184,33 @@ static void check_stored_rule() {
   }
 }
 
+// Batches of equal instances by the library's choice (W = 35, p = 8), stored over by
+// bins; and weights on the fly beside them, which share the launch.
+static void check_batch_rule() {
+  struct {
+    int n, M, neighbours;
+    double ratio;
+  } rows[] = {{1, 600, 450, 0.84}, {2, 600, 450, 0.82}, {8, 600, 450, 1.06}, {64, 600, 450, 1.0}, {1, 3000, 434, 0.82},
+              {4, 3000, 434, 0.97}, {16, 3000, 434, 1.11}, {1, 10000, 446, 0.88}, {4, 10000, 446, 1.18},
+              {1, 1000, 705, 1.02}, {4, 1000, 705, 1.22}, {16, 1000, 705, 1.61}};
+  BinLayout B;
+  CHECK(layout(35, 8, 1e-12, 35, 1e-3, B), "layout");
+  for (const auto& r : rows) {
+    const double springs = (double)r.n * r.M;
+    const BatchBins b = batch_bins(B, 35, springs, springs * r.neighbours, 0.0, 0.0);
+    CHECK(!b.on_the_fly && (b.choice ? r.ratio > 1.0 / 1.1 : r.ratio < 1.1), "%d instances of %d, %d neighbours: by bins %d",
+          r.n, r.M, r.neighbours, b.choice);
+  }
+  const BatchBins none = batch_bins(B, 35, 0.0, 0.0, 0.0, 0.0);
+  CHECK(!none.choice && !none.on_the_fly, "an empty batch");
+  CHECK(!batch_bins(B, 35, 0.0, 0.0, 300.0, 300.0 * 116).on_the_fly, "a few springs on the fly");
+  CHECK(batch_bins(B, 35, 0.0, 0.0, 12000.0, 12000.0 * 127).on_the_fly, "many springs on the fly");
+  const BatchBins both = batch_bins(B, 35, 450.0, 450.0 * 450, 129.0, 129.0 * 129);
+  CHECK(both.choice && both.on_the_fly, "one launch for both groups");
+}
+
 int main() {
+  check_batch_rule();
   check_look_up();
   check_pairs_rule();
   check_stored_rule();

@@ -139,3 +139,43 @@ def test_bins_gradient_equals_stored_weights(wfp, case):
         print(f"{case}: {err:.2e}", flush=True)
         # 24 levels of the sums above, forward and back
         assert err < 24 * TOL
+
+
+# instances, springs, neighbours, parameters -> the library's choice: by bins only
+# where they fit the batched kernel (768 bins, 40 lags, two edges a cell) and the
+# launch is the shorter one
+@pytest.mark.parametrize("n,M,nb,kw,mode", [(8, 1500, 450, dict(n_gl_local=40), 3), (8, 1500, 450, dict(eps_window=1e-6), 3),
+                                            (1, 600, 580, {}, 3), (8, 3000, 480, {}, 2), (8, 3000, 480, dict(p=6), 3)])
+def test_batch_form_by_default(wfp, n, M, nb, kw, mode):
+    import torch
+    dt, levels = 1e-3, 4
+    W = 18 if "eps_window" in kw else 35
+    probs = [dict(_problem("slab", M, dt, nb, W), x_recv=np.zeros(0)) for _ in range(n)]
+    for i, p in enumerate(probs):
+        p["x"] = p["x"] + 1e-4 * i
+    b = wfp.Batch(probs, [dt] * n, **kw)
+    infos = [b.plan(i).info for i in range(n)]
+    assert all(i["n_pairs"] > 400 * M for i in infos)
+    assert [i["local_mode"] for i in infos] == [mode] * n
+    assert [i["local_bins"] for i in infos] == [1 if mode == 2 else 0] * n
+    out = [torch.empty(M, dtype=torch.float64, device="cuda") for _ in range(n)]
+    b.run(levels, out)
+    b.close()
+    for i in (0, n - 1):
+        plan = wfp.Plan(probs[i], dt, local_mode=1, **kw)
+        ref = plan.march(levels)[0][-1]
+        plan.close()
+        assert float((out[i] - ref).abs().max() / ref.abs().max()) < levels * TOL
+
+
+# explicit weights on the fly: pair by pair where the bins do not fit or a few springs
+# would wait for a whole round, without the tables of the bins
+@pytest.mark.parametrize("n,M,nb,kw,bins", [(4, 1500, 200, dict(eps_window=1e-6), 0), (2, 300, 150, {}, 0),
+                                            (8, 1500, 150, {}, 1)])
+def test_batch_form_of_weights_on_the_fly(wfp, n, M, nb, kw, bins):
+    probs = [dict(_problem("slab", M, 1e-3, nb, 18 if kw else 35), x_recv=np.zeros(0)) for _ in range(n)]
+    b = wfp.Batch(probs, [1e-3] * n, local_mode=2, **kw)
+    infos = [b.plan(i).info for i in range(n)]
+    assert [(i["local_mode"], i["local_bins"]) for i in infos] == [(2, bins)] * n
+    b.run(2)
+    b.close()
