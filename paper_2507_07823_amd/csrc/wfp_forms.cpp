@@ -104,6 +104,9 @@ double pairs_us(int W, int p, double springs, double neighbours) {
 // and 386 neighbours for p = 8, 6, 4 and 2), and closer than the march's at 2e3 (136,
 // 237, 307 and 372), where that pass leaves the chip idle.
 bool bins_over_pairs(const BinLayout& B, int W, int p, double springs, double neighbours, bool gradient) {
+  // (short launches pair by pair are at their cheapest at 140 to 200 neighbours: 62 us
+  // for 77 by bins at M = 3e3 and 159)
+  if (!gradient && springs < 4096.0 && neighbours < 200.0) return false;
   const double share = !gradient ? 1.0 : (springs < 4096.0 ? 0.9 : 1.17);
   return neighbours >= kBinNeighbours && share * bins_us(B, springs, neighbours) <= pairs_us(W, p, springs, neighbours);
 }

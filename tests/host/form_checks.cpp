@@ -93,6 +93,7 @@ struct Row {
   double ratio;
 };
 static const Row kRows[] = {
+    {35, 1e-12, 8, 3000, 159, 0, 0.90}, {35, 1e-12, 8, 2000, 174, 0, 0.85},
     {35, 1e-12, 2, 2000, 134, 0, 0.589}, {35, 1e-12, 2, 2000, 223, 0, 0.697}, {35, 1e-12, 2, 2000, 379, 0, 0.841},
     {35, 1e-12, 2, 20000, 137, 0, 0.681}, {35, 1e-12, 2, 20000, 231, 0, 0.833},
     {35, 1e-12, 2, 20000, 398, 0, 1.059}, {35, 1e-12, 2, 100000, 137, 0, 0.660},
