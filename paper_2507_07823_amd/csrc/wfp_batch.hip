@@ -35,6 +35,7 @@ struct wfp_batch {
   int64_t* lvl0_d = nullptr;
   bool uout_set = false;
   size_t lds_a = 0, lds_b = 0, lds_c = 0, lds_til = 0, lds_otf = 0, lds_sym = 0;
+  int rows_sym = 0;   // rows per block of the pair-once stored sums
   // Jacobi sweeps of the global-solve instances, 16 or 64 rows an item, by decreasing
   // sweep count: sweep `it` launches the prefix of cnt_sw[it] items
   int max_sweeps = 0;
@@ -226,6 +227,10 @@ void build_batch(wfp_batch* B) {
   // otf, loc4, loc8, g8, g4: (instance, blocks); g8 / g4: instances whose
   // lag blocks are short (the plan's lanes per lag), 4 rows per block
   std::vector<int2> inc, loc4, loc8, wa, wb, wc, dir, til, rows, otf, otfr, g8, g4, rcv, sp, sym, symr, bin, binr;
+  int64_t stored_once = 0;
+  for (const wfp_plan* P : B->plans)
+    if (P->sym_stored) stored_once += P->M;
+  B->rows_sym = sym_rows(stored_once);
   for (int i = 0; i < n; ++i) {
     // the spread grid of the separate spread pass
     if (!B->plans[i]->gsp) B->plans[i]->gsp = B->plans[i]->alloc<double>(B->plans[i]->nf);
@@ -236,7 +241,7 @@ void build_batch(wfp_batch* B) {
     const int rpb = 256 / desc[i].pp;
     for (int b = 0; b < (int)nblk(M, rpb); ++b) inc.push_back(make_int2(i, b));
     if (P->sym_stored) {
-      sym.push_back(make_int2(i, (int)nblk(M, kBatchSymRows)));
+      sym.push_back(make_int2(i, (int)nblk(M, B->rows_sym)));
       B->lds_sym = std::max(B->lds_sym, sym_lds(P->NQ, 1));
       for (int bb = 0; bb < (int)nblk(M, 64); ++bb) symr.push_back(make_int2(i, bb));
     } else if (P->otf) {
@@ -382,7 +387,7 @@ void enqueue_level(wfp_batch* B) {
   }
   if (B->n_sym) {
     bl.work = B->wl_sym;
-    hipLaunchKernelGGL(kb_local_sym, dim3(B->n_sym), dim3(kSymThreads), B->lds_sym, s, bl);
+    hipLaunchKernelGGL(kb_local_sym, dim3(B->n_sym), dim3(kSymThreads), B->lds_sym, s, bl, B->rows_sym);
     bl.work = B->wl_symr;
     hipLaunchKernelGGL(kb_local_sym_reduce, dim3(B->n_symr), dim3(64 * kReduceWaves), 0, s, bl);
   }

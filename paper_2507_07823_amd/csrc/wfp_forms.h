@@ -57,4 +57,12 @@ struct BatchBins {
 BatchBins batch_bins(const BinLayout& B, int W, double choice_springs, double choice_pairs, double otf_springs,
                      double otf_pairs);
 
+// Rows per block (of 8 wavefronts) of the pair-once stored local sum, by all the rows
+// of a launch: one per wavefront, or two once that leaves two blocks per compute unit.
+// More (the sources' values staged for more rows) do not pay: at 206 sources per range
+// 16 rows take 323 us and 32 rows 362 us (M = 3e4), at 50 both 295 us (M = 1e5); at M =
+// 1e3, 8 rows 17.0 us and 16 rows 21.1; a batch of one instance of M = 600 with 450
+// neighbours 88 and 106 us a level.
+inline int sym_rows(int64_t rows) { return rows >= 16 * 512 ? 16 : 8; }
+
 }  // namespace wfp

@@ -101,9 +101,8 @@ constexpr int kSweepWaves = 8;        // wavefronts of a block of the global Jac
 // (a solve of 7 sweeps, 64 rows against 16: 0.64 / 0.17 ms at M = 3000, all
 // coupled, 0.26 / 0.17 at M = 2e4)
 __host__ __device__ constexpr int sweep_rows(int64_t M) { return M < 64 * 512 ? 16 : 64; }
-constexpr int kSymThreads = 512;      // pair-once stored local sum: threads of a block,
-constexpr int kSymChunk = 128;        // sources whose values it stages at a time,
-constexpr int kBatchSymRows = 16;     // and rows per block in a batch
+constexpr int kSymThreads = 512;      // pair-once stored local sum: threads of a block
+constexpr int kSymChunk = 128;        // and sources whose values it stages at a time
 constexpr int kMaxOtfLags = 48;      // lags 1 .. NQ - 1 of a row staged by the symmetric local sum
 template <int P>
 __global__ void k_local_otf_sym(int M, int NH, int NQ, int64_t L, const int* __restrict__ up_end,
@@ -457,7 +456,7 @@ __global__ void kb_local_otf(BatchLaunch b);
 __global__ void kb_local_otf_reduce(BatchLaunch b);
 __global__ void kb_local_bins(BatchLaunch bl);
 __global__ void kb_local_bins_reduce(BatchLaunch bl);
-__global__ void kb_local_sym(BatchLaunch b);
+__global__ void kb_local_sym(BatchLaunch b, int rows);
 __global__ void kb_local_sym_reduce(BatchLaunch b);
 __global__ void kb_spread_grid(BatchLaunch b);
 __global__ void kb_hist_a(BatchLaunch b, int from_grid);

@@ -2664,20 +2664,20 @@ __global__ void __launch_bounds__(256) kb_local_otf_reduce(BatchLaunch b) {
 }
 
 // Weights stored once per unordered pair (lags >= 1 in one pass, as in a
-// plan's on-the-fly schedule): the rows over (instance, block of 4 rows)
+// plan's on-the-fly schedule): the rows over (instance, block of `rows` rows)
 // items, then the per-row totals over (instance, 64 rows) items, scaled by
 // beta_j / 2 into the instance's local sum.
-__global__ void __launch_bounds__(kSymThreads) kb_local_sym(BatchLaunch b) {
+__global__ void __launch_bounds__(kSymThreads) kb_local_sym(BatchLaunch b, int rows) {
   const int2 w = b.work[xcd_block(blockIdx.x, gridDim.x)];
   if (w.x < 0) return;   // block-uniform
   const InstDesc& d = b.desc[w.x];
   if (*b.level >= d.end) return;   // the instance has marched its own levels (block-uniform)
   const int s0 = mod_slot(*b.level, d.NH);
   if (d.sym_spl == 2)
-    sym_block<2, 1>(d.M, d.NQ, 1, kBatchSymRows, d.otf_up_end, d.sym_rb, d.sym_acx, d.sym_q, d.sym_upb, d.hist, s0,
+    sym_block<2, 1>(d.M, d.NQ, 1, rows, d.otf_up_end, d.sym_rb, d.sym_acx, d.sym_q, d.sym_upb, d.hist, s0,
                     d.NH, nullptr, 0, 0, d.otf_rowacc, nullptr, d.sym_colpart, nullptr, w.y);
   else
-    sym_block<1, 1>(d.M, d.NQ, 1, kBatchSymRows, d.otf_up_end, d.sym_rb, d.sym_acx, d.sym_q, d.sym_upb, d.hist, s0,
+    sym_block<1, 1>(d.M, d.NQ, 1, rows, d.otf_up_end, d.sym_rb, d.sym_acx, d.sym_q, d.sym_upb, d.hist, s0,
                     d.NH, nullptr, 0, 0, d.otf_rowacc, nullptr, d.sym_colpart, nullptr, w.y);
 }
 

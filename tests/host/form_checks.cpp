@@ -210,7 +210,15 @@ static void check_batch_rule() {
   CHECK(both.choice && both.on_the_fly, "one launch for both groups");
 }
 
+// Blocks of the pair-once sum: of a plan and of a batch alike, few rows are spread
+// over as many blocks as they can be.
+static void check_rows() {
+  CHECK(sym_rows(1) == 8 && sym_rows(600) == 8 && sym_rows(8191) == 8 && sym_rows(8192) == 16 && sym_rows(100000) == 16,
+        "rows per block");
+}
+
 int main() {
+  check_rows();
   check_batch_rule();
   check_look_up();
   check_pairs_rule();
