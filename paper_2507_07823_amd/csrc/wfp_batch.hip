@@ -36,7 +36,7 @@ struct wfp_batch {
   bool uout_set = false;
   size_t lds_a = 0, lds_b = 0, lds_c = 0, lds_til = 0, lds_otf = 0, lds_sym = 0;
   int rows_sym = 0;   // rows per block of the pair-once stored sums
-  // Jacobi sweeps of the global-solve instances, 16 or 64 rows an item, by decreasing
+  // Jacobi sweeps of the global-solve instances, a block of rows an item, by decreasing
   // sweep count: sweep `it` launches the prefix of cnt_sw[it] items
   int max_sweeps = 0;
   std::vector<int> cnt_sw;
@@ -146,6 +146,9 @@ InstDesc describe(const wfp_plan* P) {
   d.g_off = P->g_off;
   d.g_lim = P->g_lim;
   d.g_ud = P->g_ud;
+  d.g_rows = P->g_rows;
+  d.g_ptr = P->g_ptr;
+  d.g_col = P->g_col;
   d.g_val = P->g_val;
   d.g_dinv = P->g_dinv;
   d.g_rhs = P->g_rhs;
@@ -287,7 +290,8 @@ void build_batch(wfp_batch* B) {
   B->cnt_sw.assign(std::max(B->max_sweeps, 1), 0);
   for (int i : order) {
     const wfp_plan* P = B->plans[i];
-    for (int b = 0; b < (int)nblk(P->M, sweep_rows(P->M)); ++b) sw.push_back(make_int2(i, b));
+    const int rows = P->g_rows == kSweepByRow ? kSweepWaves : P->g_rows;
+    for (int b = 0; b < (int)nblk(P->M, rows); ++b) sw.push_back(make_int2(i, b));
     for (int it = 1; it < P->iters; ++it) B->cnt_sw[it] = (int)sw.size();
   }
   B->lds_c = B->lds_a;

@@ -65,4 +65,20 @@ BatchBins batch_bins(const BinLayout& B, int W, double choice_springs, double ch
 // neighbours 88 and 106 us a level.
 inline int sym_rows(int64_t rows) { return rows >= 16 * 512 ? 16 : 8; }
 
+// Rows per block of the solve's global sweeps: 64 or 16 with the coupling stored once
+// per pair, by diagonals, or kSweepByRow: a wavefront per row, from a row's values and
+// columns.  A sweep of few rows is a chain of latencies, of which the last has the
+// fewest, as long as its 12 bytes an entry stay in the L2 (30 MB); of many it is the
+// stream of the values, of which the diagonals need a third; 16 rows where long runs
+// would leave blocks of 64 too few.  One sweep, us, wavefronts / 64 / 16 rows: M = 2e3
+// and 40 nearby springs 2.7 / 3.8 / 4.3, 160: 3.2 / 6.3 / 4.9, 640: 5.1 / 19.7 / 8.1; 8e3 and
+// 80 4.3 / 4.9 / 6.2, 320: 6.8 / 11.0 / 6.9, 640: 12.4 / 19.5 / 11.3; 1.6e4 and 40 5.6 / 3.8 /
+// 9.5, 320: 14.5 / 10.5 / 10.8, 640: 22.7 / 28.9 / 20.2; 3e4 and 80 12.2 / 7.0 / 17.5, 320: 24.8
+// / 20.4 / 19.5; 2e5 and 80 69 / 31 / 96.
+constexpr int kSweepByRow = 1;
+inline int sweep_rows(int64_t M, double nearby) {
+  if (M <= 8192 && nearby * (double)M <= 2.5e6) return kSweepByRow;
+  return M < 32768 && nearby > 300.0 ? 16 : 64;
+}
+
 }  // namespace wfp

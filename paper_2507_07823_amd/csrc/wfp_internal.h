@@ -286,6 +286,8 @@ struct wfp_plan {
   bool solve_global = false, g_wave = false;
   int64_t* g_off = nullptr;               // sweeps: first value of each 64 rows,
   int2 *g_lim = nullptr, *g_ud = nullptr; // their longest upper and lower run, and each row's
+  int g_rows = 0;                         // rows per block; a wavefront a row takes its
+  int *g_ptr = nullptr, *g_col = nullptr; // values and columns instead
   double *g_val = nullptr, *g_dinv = nullptr, *g_rhs = nullptr, *g_xa = nullptr, *g_xb = nullptr;
   // direct solve of small runs
   int n_direct_tiles = 0;

@@ -97,10 +97,6 @@ __global__ void k_local_bins_reduce(int M, BinArgs A, const double* __restrict__
 // sources per LDS chunk of the on-the-fly derivative local sums
 constexpr int kOtfDerivChunk = 112;
 constexpr int kSweepWaves = 8;        // wavefronts of a block of the global Jacobi sweeps
-// and its rows: 16 while blocks of 64 would be fewer than two per compute unit
-// (a solve of 7 sweeps, 64 rows against 16: 0.64 / 0.17 ms at M = 3000, all
-// coupled, 0.26 / 0.17 at M = 2e4)
-__host__ __device__ constexpr int sweep_rows(int64_t M) { return M < 64 * 512 ? 16 : 64; }
 constexpr int kSymThreads = 512;      // pair-once stored local sum: threads of a block
 constexpr int kSymChunk = 128;        // and sources whose values it stages at a time
 constexpr int kMaxOtfLags = 48;      // lags 1 .. NQ - 1 of a row staged by the symmetric local sum
@@ -217,6 +213,11 @@ __global__ void k_jacobi_sweep(int M, const int64_t* __restrict__ off, const int
                                const double* __restrict__ rhs, const double* __restrict__ xin,
                                double* __restrict__ xout, double* __restrict__ save_row,
                                const int* __restrict__ perm);
+__global__ void k_jacobi_sweep_wave(int M, const int* __restrict__ ptr, const int* __restrict__ col,
+                                    const double* __restrict__ val, const double* __restrict__ dinv,
+                                    const double* __restrict__ rhs, const double* __restrict__ xin,
+                                    double* __restrict__ xout, double* __restrict__ save_row,
+                                    const int* __restrict__ perm);
 __global__ void k_pack_diagonals(int M, const int64_t* __restrict__ off, const int2* __restrict__ lim,
                                  const int2* __restrict__ updown, const int64_t* __restrict__ q0,
                                  const double* __restrict__ Q, const double* __restrict__ beta,
@@ -412,6 +413,8 @@ struct InstDesc {
   const double* iw;
   const int64_t* g_off;
   const int2 *g_lim, *g_ud;
+  int g_rows;
+  const int *g_ptr, *g_col;
   const double *g_val, *g_dinv;
   double *g_rhs, *g_xa, *g_xb;
   // local weights on the fly (p = 8), each unordered pair once

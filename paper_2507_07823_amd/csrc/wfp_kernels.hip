@@ -1736,7 +1736,7 @@ __global__ void k_solve_rhs(int M, const double* __restrict__ ginc, const double
 // the 64 rows (zero past a row's own).  A row's lower entries are those of the
 // springs down[j] .. 1 places below it.  A block takes RW = 64 rows, its
 // wavefronts every kSweepWaves-th diagonal, or 16 rows and four diagonals a
-// wavefront where 64 would leave the chip idle; the parts are added in order.
+// wavefront (sweep_rows); the parts are added in order.
 // Bound by the values' stream; against a row's values and columns stored per
 // ordered pair (24 bytes a pair for 8), the solve with its 10 sweeps takes 3.77
 // ms for 6.74 at M = 1e6 and 266 nearby springs a row.
@@ -1813,6 +1813,34 @@ template __global__ void k_jacobi_sweep<16>(int, const int64_t*, const int2*, co
                                             const double*, const double*, const double*, double*, double*, const int*);
 template __global__ void k_jacobi_sweep<64>(int, const int64_t*, const int2*, const int2*, const double*, const double*,
                                             const double*, const double*, const double*, double*, double*, const int*);
+
+// The same sweep from a row's values and columns, a wavefront per row (lanes over
+// the row's entries): for few rows of short runs (sweep_rows).
+__device__ __forceinline__ void k_jacobi_sweep_wave_body(int M, const int* __restrict__ ptr,
+                               const int* __restrict__ col, const double* __restrict__ val,
+                               const double* __restrict__ dinv, const double* __restrict__ rhs,
+                               const double* __restrict__ xin, double* __restrict__ xout,
+                               double* __restrict__ save_row, const int* __restrict__ perm, int bid) {
+  const int lane = threadIdx.x & 63;
+  const int j = bid * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  if (j >= M) return;
+  double acc = 0.0;
+  for (int k = ptr[j] + lane; k < ptr[j + 1]; k += 64) acc = fma(val[k], xin[col[k]], acc);
+  acc = wave_sum(acc);
+  if (lane == 0) {
+    const double v = (rhs[j] - acc) * dinv[j];
+    xout[j] = v;
+    if (save_row) save_row[perm[j]] = v;
+  }
+}
+
+__global__ void __launch_bounds__(256)
+k_jacobi_sweep_wave(int M, const int* __restrict__ ptr, const int* __restrict__ col,
+                    const double* __restrict__ val, const double* __restrict__ dinv,
+                    const double* __restrict__ rhs, const double* __restrict__ xin, double* __restrict__ xout,
+                    double* __restrict__ save_row, const int* __restrict__ perm) {
+  k_jacobi_sweep_wave_body(M, ptr, col, val, dinv, rhs, xin, xout, save_row, perm, blockIdx.x);
+}
 
 // The diagonals of the sweeps, from the lag-0 weights of the nearby pairs (row
 // j's own at q0[j], its upper ones after it); a thread per (diagonal, row) of
@@ -2779,7 +2807,9 @@ __global__ void __launch_bounds__(64 * kSweepWaves) kb_jacobi_sweep(BatchLaunch 
   double* slot = d.hist + (int64_t)mod_slot(*b.level, d.NH) * d.M;
   const double* xin = (it & 1) ? d.g_xa : d.g_xb;
   double* xout = (it == d.iters - 1) ? slot : ((it & 1) ? d.g_xb : d.g_xa);
-  if (sweep_rows(d.M) == 64)
+  if (d.g_rows == kSweepByRow)
+    k_jacobi_sweep_wave_body(d.M, d.g_ptr, d.g_col, d.g_val, d.g_dinv, d.g_rhs, xin, xout, nullptr, nullptr, w.y);
+  else if (d.g_rows == 64)
     k_jacobi_sweep_body<64>(d.M, d.g_off, d.g_lim, d.g_ud, d.g_val, d.beta, d.g_dinv, d.g_rhs, xin, xout, nullptr,
                             nullptr, w.y);
   else

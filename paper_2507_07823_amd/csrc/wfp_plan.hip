@@ -1218,48 +1218,79 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par, OtfForm 
       // every row by global sweeps; the direct and tiled paths are not used
       P->n_direct_tiles = 0;
       P->ntile = 0;
-      // per row: nearby springs above and below it (contiguous both ways); per
-      // 64 rows: the longest of them
-      const int64_t nch = nblk(M, 64);
-      std::vector<int2> ud(M), lim(nch, make_int2(0, 0));
-      std::vector<int64_t> goff(nch), grq(M);
-      int64_t entries = 0, total = 0;
+      int64_t entries = 0;
+      std::vector<int64_t> grq(M);
       for (int64_t g = 0; g < M; ++g) {
-        const int below = (int)((g - ns[g] + M) % M);
-        ud[g] = make_int2(nc[g] - 1 - below, below);
         entries += nc[g] - 1;
         grq[g] = lag0(g, g);
-        lim[g / 64].x = std::max(lim[g / 64].x, ud[g].x);
-      }
-      for (int64_t g = 0; g < M; ++g) {
-        // the pair's value is read from the lower spring's run
-        while (ud[g].y > 0 && ud[(g - ud[g].y + M) % M].x < ud[g].y) --ud[g].y;
-        lim[g / 64].y = std::max(lim[g / 64].y, ud[g].y);
-      }
-      for (int64_t c = 0; c < nch; ++c) {
-        goff[c] = total;
-        total += 64 * (int64_t)lim[c].x;
       }
       P->g_wave = entries > 16 * M;
-      P->g_off = P->alloc<int64_t>(nch);
-      P->g_lim = P->alloc<int2>(nch);
-      P->g_ud = P->alloc<int2>(M);
-      P->g_val = P->alloc<double>(std::max<int64_t>(total, 1));
+      P->g_rows = sweep_rows(M, (double)entries / (double)M);
       P->g_dinv = P->alloc<double>(M);
       P->g_rhs = P->alloc<double>(M);
       P->g_xa = P->alloc<double>(M);
       P->g_xb = P->alloc<double>(M);
-      upload(P->g_off, goff, s);
-      upload(P->g_lim, lim, s);
-      upload(P->g_ud, ud, s);
       int64_t* rq_d = P->alloc<int64_t>(M);
       upload(rq_d, grq, s);
-      hipLaunchKernelGGL(k_gather_solve, dim3(nblk(M, 256)), dim3(256), 0, s, (int64_t)0, (const int64_t*)nullptr, P->Q,
-                         (double*)nullptr, (int64_t)M, rq_d, P->g_dinv);
-      hipLaunchKernelGGL(k_pack_diagonals, dim3((unsigned)nch), dim3(256), 0, s, (int)M, P->g_off, P->g_lim, P->g_ud,
-                         rq_d, P->Q, P->beta, P->g_val);
+      std::vector<int> gp(M + 1, 0), gc;
+      std::vector<int64_t> geq, goff;
+      std::vector<int2> ud, lim;
+      int64_t* eq_d = nullptr;
+      if (P->g_rows == kSweepByRow) {
+        // per row: its values and columns
+        for (int64_t g = 0; g < M; ++g) {
+          for (int k = 0; k < nc[g]; ++k) {
+            const int64_t l = (ns[g] + k) % M;
+            if (l == g) continue;
+            gc.push_back((int)l);
+            geq.push_back(lag0(g, l));
+          }
+          gp[g + 1] = (int)gc.size();
+        }
+        P->g_ptr = P->alloc<int>(M + 1);
+        P->g_col = P->alloc<int>(gc.size());
+        P->g_val = P->alloc<double>(gc.size());
+        eq_d = P->alloc<int64_t>(geq.size());
+        upload(P->g_ptr, gp, s);
+        upload(P->g_col, gc, s);
+        upload(eq_d, geq, s);
+      } else {
+        // per row: nearby springs above and below it (contiguous both ways); per
+        // 64 rows: the longest of them
+        const int64_t nch = nblk(M, 64);
+        ud.resize(M);
+        lim.assign(nch, make_int2(0, 0));
+        goff.resize(nch);
+        int64_t total = 0;
+        for (int64_t g = 0; g < M; ++g) {
+          const int below = (int)((g - ns[g] + M) % M);
+          ud[g] = make_int2(nc[g] - 1 - below, below);
+          lim[g / 64].x = std::max(lim[g / 64].x, ud[g].x);
+        }
+        for (int64_t g = 0; g < M; ++g) {
+          // the pair's value is read from the lower spring's run
+          while (ud[g].y > 0 && ud[(g - ud[g].y + M) % M].x < ud[g].y) --ud[g].y;
+          lim[g / 64].y = std::max(lim[g / 64].y, ud[g].y);
+        }
+        for (int64_t c = 0; c < nch; ++c) {
+          goff[c] = total;
+          total += 64 * (int64_t)lim[c].x;
+        }
+        P->g_off = P->alloc<int64_t>(nch);
+        P->g_lim = P->alloc<int2>(nch);
+        P->g_ud = P->alloc<int2>(M);
+        P->g_val = P->alloc<double>(std::max<int64_t>(total, 1));
+        upload(P->g_off, goff, s);
+        upload(P->g_lim, lim, s);
+        upload(P->g_ud, ud, s);
+        hipLaunchKernelGGL(k_pack_diagonals, dim3((unsigned)nch), dim3(256), 0, s, (int)M, P->g_off, P->g_lim, P->g_ud,
+                           rq_d, P->Q, P->beta, P->g_val);
+      }
+      hipLaunchKernelGGL(k_gather_solve, dim3(nblk(std::max<int64_t>((int64_t)geq.size(), M), 256)), dim3(256), 0, s,
+                         (int64_t)geq.size(), eq_d, P->Q, P->g_val, (int64_t)M, rq_d, P->g_dinv);
       HIPCHK(hipGetLastError());
       HIPCHK(hipStreamSynchronize(s));
+      if (eq_d) P->release(eq_d);
       P->release(rq_d);
     }
     if (P->ntile > 0) {
@@ -1764,10 +1795,14 @@ void march_level(wfp_plan* P, const StateRef& S, int64_t L, bool driven, const E
       for (int it = 1; it < P->iters; ++it) {
         const bool last = it == P->iters - 1;
         double* out = last ? slot : xb;
-        const int rw = sweep_rows(P->M);
-        hipLaunchKernelGGL(rw == 64 ? k_jacobi_sweep<64> : k_jacobi_sweep<16>, dim3(8 * nblk(nblk(P->M, rw), 8)),
-                           dim3(64 * kSweepWaves), 0, s, (int)P->M, P->g_off, P->g_lim, P->g_ud, P->g_val, P->beta,
-                           P->g_dinv, P->g_rhs, xa, out, last ? save : nullptr, P->perm);
+        const int rw = P->g_rows;
+        if (rw == kSweepByRow)
+          hipLaunchKernelGGL(k_jacobi_sweep_wave, dim3(nblk(P->M, 4)), dim3(256), 0, s, (int)P->M,
+                             P->g_ptr, P->g_col, P->g_val, P->g_dinv, P->g_rhs, xa, out, last ? save : nullptr, P->perm);
+        else
+          hipLaunchKernelGGL(rw == 64 ? k_jacobi_sweep<64> : k_jacobi_sweep<16>, dim3(8 * nblk(nblk(P->M, rw), 8)),
+                             dim3(64 * kSweepWaves), 0, s, (int)P->M, P->g_off, P->g_lim, P->g_ud, P->g_val, P->beta,
+                             P->g_dinv, P->g_rhs, xa, out, last ? save : nullptr, P->perm);
         std::swap(xa, xb);
       }
     }

@@ -217,8 +217,28 @@ static void check_rows() {
         "rows per block");
 }
 
+// Sweeps of the solve: measured, us, by wavefronts, 64 and 16 rows a block.
+static void check_sweeps() {
+  struct {
+    int M, nearby;
+    double wave, r64, r16;
+  } rows[] = {{300, 160, 2.92, 7.09, 4.89},    {1000, 24, 2.58, 3.38, 3.77},    {1000, 320, 3.40, 11.23, 5.24},
+              {2000, 160, 3.19, 6.29, 4.91},   {2000, 640, 5.07, 19.71, 8.14},  {4000, 40, 3.10, 3.60, 4.15},
+              {4000, 640, 8.21, 19.63, 8.12},  {4000, 1300, 14.96, 47.05, 13.99}, {8000, 24, 3.69, 3.39, 5.23},
+              {8000, 160, 4.81, 6.54, 6.46},   {8000, 1300, 20.77, 50.50, 18.43}, {16000, 24, 5.56, 3.47, 7.73},
+              {16000, 160, 8.70, 7.46, 10.38}, {16000, 640, 22.73, 28.91, 20.17}, {30000, 40, 8.77, 5.10, 16.10},
+              {30000, 160, 16.93, 10.06, 17.88}, {30000, 1300, 107.82, 68.05, 58.39}, {60000, 80, 23.13, 11.13, 30.18},
+              {200000, 320, 198.22, 98.25, 122.53}};
+  for (const auto& r : rows) {
+    const int form = sweep_rows(r.M, r.nearby);
+    const double got = form == kSweepByRow ? r.wave : (form == 64 ? r.r64 : r.r16);
+    CHECK(got <= 1.15 * std::min(r.wave, std::min(r.r64, r.r16)), "M %d, %d nearby: %d rows, %.2f us", r.M, r.nearby, form, got);
+  }
+}
+
 int main() {
   check_rows();
+  check_sweeps();
   check_batch_rule();
   check_look_up();
   check_pairs_rule();
