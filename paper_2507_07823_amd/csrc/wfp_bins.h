@@ -13,13 +13,14 @@
 
 namespace wfp {
 
-// Place of distance z in a chunk's lookup cells c0 .. c0 + ctop of width
+// Place of distance |z| in a chunk's lookup cells c0 .. c0 + ctop of width
 // 1 / scale: the nearest one for distances outside the chunk.  Cut off before the
 // conversion to int, whose range z scale leaves where a block of sources reaches
 // across the box (1.1 at a step of 2e-7) and for missing sources (1e30 away, or
 // 2 pi less that across the seam).
 WFP_HD int bin_cell(double z, double scale, int c0, int ctop) {
-  return (int)fmin(fmax(z * scale, (double)c0), (double)(c0 + ctop)) - c0;
+  const int c = (int)fmin(fabs(z) * scale, (double)(c0 + ctop)) - c0;
+  return c > 0 ? c : 0;
 }
 
 // What a window leaves to spare: a share of the step, and the rounding of the

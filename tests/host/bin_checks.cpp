@@ -33,7 +33,7 @@ static void check_cells() {
     const int c0 = (int)std::floor(e * scale) - 1, ctop = 1 + (int)(4094 * u(g));
     const double zs[] = {0.0, e, 50.0 * dt * u(g), 6.3 * u(g), 1e30, 2e30, 6.3 - 1e30, -6.3 * u(g), (c0 + ctop) / scale, 2147483647.0 / scale};
     for (double z : zs) {
-      const double want = std::fmax(std::fmin(std::trunc(z * scale) - c0, ctop), 0.0);
+      const double want = std::fmax(std::fmin(std::floor(std::fabs(z) * scale) - c0, ctop), 0.0);
       const int got = bin_cell(z, scale, c0, ctop);
       CHECK(got == (int)want, "cell of %.17g (scale %.17g, %d cells from %d): %d, not %d", z, scale, ctop + 1, c0, got,
             (int)want);
