@@ -437,11 +437,11 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par, OtfForm 
                                       : (int)std::ceil(P->W * P->h_rbc / P->dt - 1e-12);
   // fine grid: the smallest even 2^a 5^b >= 2 (2K+1) whose half length
   // n = n1 n2 splits with n1 = the largest 2^a 5^b divisor not above sqrt(n)
-  // or 256 (the column pass holds 38 n1 complex values in LDS) and
+  // or 256 (the column pass has one thread per mode of its two columns) and
   // n2 <= 8192 (one row in LDS)
   auto split = [](int64_t n, int64_t& n1) {
     n1 = 0;
-    for (int64_t d = 1; d * d <= n && d <= 256; ++d)
+    for (int64_t d = 1; d * d <= n && 2 * d <= kHistBThreads; ++d)
       if (n % d == 0 && is_pow2_pow5(d)) n1 = d;
     return n1 > 0 && n / n1 <= 8192;
   };
