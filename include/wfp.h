@@ -249,9 +249,9 @@ wfp_status wfp_local_part(wfp_plan* plan, double* out);
  * density levels and one of checkpoint_every derivative terms; with grad_x,
  * derivative weights as large as the local weights (stored per ordered pair
  * or once per pair, as the weights are; with weights on the fly their
- * derivatives are evaluated on the fly too: by bins, from a second table; else
- * each pair once, in the pass that also forms the next adjoint level's local
- * sum; a few buffers of the size of the forward one are added).  With recorded levels
+ * derivatives are evaluated on the fly too: by bins, from a second table, into two
+ * buffers of (n + 16) M / 16 doubles; else each pair once, in the pass that also
+ * forms the next adjoint level's local sum, into three of the forward one's size).  With recorded levels
  * (checkpoint_every < 0) the recorded blocks take the place of the replay.
  * Asynchronous on the plan's stream.
  * Errors: WFP_EINVAL, WFP_EDOMAIN (free space; grad_x with the weights on

@@ -187,10 +187,11 @@ __global__ void k_bin_windows(int M, int nsrc, int nblk, int nch, int periodic, 
 // part[off[b] + (u - first)], chunk by chunk in a fixed order: the first chunk
 // whose windows hold it stores, later ones add.
 //
-// Bound by the LDS reads of the records (four 16-byte reads a pair, about 8 ms
-// of the below) and then the matrix cores (4 to 5 ms), one after the other.
-// M = 1e6, 5750 neighbours a spring: 14.7 ms with the reduction, for 250 pair by
-// pair; M = 1e5, 578: 1.05 for 3.5; M = 2e4, 116: 0.24 for 0.25.
+// Bound by the instructions of the visits (look-up and polynomial of a pair) and the
+// products, one after the other, and by the chunks' staging and barriers between them.
+// Clumped springs, M = 1e6 and 5763 neighbours / 2e4 and 116, us with the reduction:
+// 14506 / 228; without the products 10682 / 123, without the visits 8308 / 211, with
+// constants for the records' reads 14135 / 225.  Pair by pair 250 ms / 236 us.
 //
 // H = 2: the two derivative sums of the gradient pass in one visit of the
 // pairs, for half as many sources: weights (1/2) dQ_m/dd sign(x_j - x_l) with
