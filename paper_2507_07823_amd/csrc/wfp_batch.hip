@@ -230,10 +230,13 @@ void build_batch(wfp_batch* B) {
   // otf, loc4, loc8, g8, g4: (instance, blocks); g8 / g4: instances whose
   // lag blocks are short (the plan's lanes per lag), 4 rows per block
   std::vector<int2> inc, loc4, loc8, wa, wb, wc, dir, til, rows, otf, otfr, g8, g4, rcv, sp, sym, symr, bin, binr;
-  int64_t stored_once = 0;
+  int64_t once_rows = 0, once_pairs = 0;
   for (const wfp_plan* P : B->plans)
-    if (P->sym_stored) stored_once += P->M;
-  B->rows_sym = sym_rows(stored_once);
+    if (P->sym_stored) {
+      once_rows += P->M;
+      once_pairs += P->n_pairs;
+    }
+  B->rows_sym = sym_rows(once_rows, (double)once_pairs / (double)std::max<int64_t>(once_rows, 1));
   for (int i = 0; i < n; ++i) {
     // the spread grid of the separate spread pass
     if (!B->plans[i]->gsp) B->plans[i]->gsp = B->plans[i]->alloc<double>(B->plans[i]->nf);

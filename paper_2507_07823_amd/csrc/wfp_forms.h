@@ -58,12 +58,14 @@ BatchBins batch_bins(const BinLayout& B, int W, double choice_springs, double ch
                      double otf_pairs);
 
 // Rows per block (of 8 wavefronts) of the pair-once stored local sum, by all the rows
-// of a launch: one per wavefront, or two once that leaves two blocks per compute unit.
-// More (the sources' values staged for more rows) do not pay: at 206 sources per range
-// 16 rows take 323 us and 32 rows 362 us (M = 3e4), at 50 both 295 us (M = 1e5); at M =
-// 1e3, 8 rows 17.0 us and 16 rows 21.1; a batch of one instance of M = 600 with 450
-// neighbours 88 and 106 us a level.
-inline int sym_rows(int64_t rows) { return rows >= 16 * 512 ? 16 : 8; }
+// of a launch and their neighbours: one per wavefront, or two for many rows of short
+// ranges, whose sources' values then serve twice the rows.  Levels, 16 / 8 rows: M = 1e4
+// with 138 neighbours beside the history chain 53.8 / 56.5 us, 6e4 with 201 366 / 365, 3e4
+// with 300 297 / 288, 994 861 / 792, 6e4 with 798 1379 / 1316, 1984 3246 / 3091; a gradient
+// at 2e4 and 987 neighbours 1403 / 1342, 1349 before the values were staged; a batch of
+// one instance of M = 600 with 450 106 / 88.  32 rows do not pay: M = 3e4 with 400, 406 us
+// for 378.
+inline int sym_rows(int64_t rows, double neighbours) { return rows >= 16 * 512 && neighbours < 256.0 ? 16 : 8; }
 
 // Rows per block of the solve's global sweeps: 64 or 16 with the coupling stored once
 // per pair, by diagonals, or kSweepByRow: a wavefront per row, from a row's values and

@@ -1432,6 +1432,8 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par, OtfForm 
 // pipelined one (lags >= 2 ahead, lag 1 after the previous solve).
 bool otf_schedule(const wfp_plan* P) { return P->otf && !P->sym_stored; }
 
+int sym_rows(const wfp_plan* P) { return wfp::sym_rows(P->M, (double)P->n_pairs / (double)P->M); }
+
 void launch_local_otf(wfp_plan* P, hipStream_t s, const double* hist, int64_t L, const double* scale, double* out,
                       hipEvent_t ea = nullptr, hipEvent_t eb = nullptr) {
   const int nblocks = 8 * (int)nblk(P->otf_nblk, 8);
@@ -1444,8 +1446,8 @@ void launch_local_otf(wfp_plan* P, hipStream_t s, const double* hist, int64_t L,
                         P->otf_rowacc, P->otf_part)
   if (P->sym_stored) {
     hipExtLaunchKernelGGL(P->sym_spl == 2 ? k_local_sym_rows<2> : k_local_sym_rows<1>,
-                          dim3(8 * nblk(nblk(P->M, sym_rows(P->M)), 8)), dim3(kSymThreads), sym_lds(P->NQ, 1), s, ea,
-                          nullptr, 0, (int)P->M, P->NH, P->NQ, L, 1, sym_rows(P->M), P->otf_up_end, hist, P->sym_rb, P->sym_acx, P->sym_q,
+                          dim3(8 * nblk(nblk(P->M, sym_rows(P)), 8)), dim3(kSymThreads), sym_lds(P->NQ, 1), s, ea,
+                          nullptr, 0, (int)P->M, P->NH, P->NQ, L, 1, sym_rows(P), P->otf_up_end, hist, P->sym_rb, P->sym_acx, P->sym_q,
                           P->sym_upb, P->otf_rowacc, P->sym_colpart);
     hipExtLaunchKernelGGL(k_local_sym_reduce, dim3(nblk(P->M, 64)), dim3(64 * kReduceWaves), 0, s, nullptr, eb, 0, (int)P->M,
                           P->sym_cov, P->sym_upb, P->otf_rowacc, P->sym_colpart, scale, out);
@@ -1541,8 +1543,8 @@ void launch_local_big(wfp_plan* P, hipStream_t s, const double* hist, int64_t L,
                       hipEvent_t eb = nullptr) {
   if (P->sym_stored) {
     hipExtLaunchKernelGGL(P->sym_spl == 2 ? k_local_sym_rows<2> : k_local_sym_rows<1>,
-                          dim3(8 * nblk(nblk(P->M, sym_rows(P->M)), 8)), dim3(kSymThreads), sym_lds(P->NQ, 1), s, ea,
-                          nullptr, 0, (int)P->M, P->NH, P->NQ, L, 2, sym_rows(P->M), P->otf_up_end, hist, P->sym_rb,
+                          dim3(8 * nblk(nblk(P->M, sym_rows(P)), 8)), dim3(kSymThreads), sym_lds(P->NQ, 1), s, ea,
+                          nullptr, 0, (int)P->M, P->NH, P->NQ, L, 2, sym_rows(P), P->otf_up_end, hist, P->sym_rb,
                           P->sym_acx, P->sym_q, P->sym_upb, P->otf_rowacc, P->sym_colpart);
     hipExtLaunchKernelGGL(k_local_sym_reduce, dim3(nblk(P->M, 64)), dim3(64 * kReduceWaves), 0, s, nullptr, eb, 0, (int)P->M,
                           P->sym_cov, P->sym_upb, P->otf_rowacc, P->sym_colpart, P->half_beta,
@@ -1616,7 +1618,7 @@ StoredArgs stored_args(wfp_plan* P, const double* hist, int64_t L) {
     d.rb = P->sym_rb;
     d.acx = P->sym_acx;
     d.Q = P->sym_q;
-    d.rows = sym_rows(P->M);
+    d.rows = sym_rows(P);
     d.periodic = P->boundary == WFP_PERIODIC ? 1 : 0;
     d.kmax = P->sym_kmax;
     d.up_end = P->otf_up_end;
@@ -2318,8 +2320,8 @@ void run_adjoint(wfp_plan* P, int64_t N, const double* e, double* grad_beta, dou
         deriv_field(P, adj);
         if (P->sym_stored) {
           hipLaunchKernelGGL(P->sym_spl == 2 ? k_local_sym_deriv2<2> : k_local_sym_deriv2<1>,
-                             dim3(8 * nblk(nblk(M, sym_rows(P->M)), 8)), dim3(kSymThreads), sym_lds(P->NQ, 2), s, (int)M,
-                             P->NQ, P->NH, sym_rows(P->M), P->otf_up_end, (const double*)segsig, (int64_t)(hd + L - a),
+                             dim3(8 * nblk(nblk(M, sym_rows(P)), 8)), dim3(kSymThreads), sym_lds(P->NQ, 2), s, (int)M,
+                             P->NQ, P->NH, sym_rows(P), P->otf_up_end, (const double*)segsig, (int64_t)(hd + L - a),
                              (const double*)P->ahist, Rv, P->symd_rb, P->symd_acx, P->symd_q, P->sym_upb,
                              P->symd_row1, P->symd_row2, P->symd_col1, P->symd_col2);
           hipLaunchKernelGGL(k_local_sym_reduce, dim3(nblk(M, 64)), dim3(64 * kReduceWaves), 0, s, (int)M, P->sym_cov, P->sym_upb,

@@ -213,8 +213,9 @@ static void check_batch_rule() {
 // Blocks of the pair-once sum: of a plan and of a batch alike, few rows are spread
 // over as many blocks as they can be.
 static void check_rows() {
-  CHECK(sym_rows(1) == 8 && sym_rows(600) == 8 && sym_rows(8191) == 8 && sym_rows(8192) == 16 && sym_rows(100000) == 16,
-        "rows per block");
+  CHECK(sym_rows(1, 1.0) == 8 && sym_rows(600, 450.0) == 8 && sym_rows(8191, 100.0) == 8, "few rows");
+  CHECK(sym_rows(20000, 987.0) == 8 && sym_rows(60000, 1984.0) == 8, "long ranges");
+  CHECK(sym_rows(10000, 138.0) == 16 && sym_rows(100000, 101.0) == 16, "many rows of short ranges");
 }
 
 // Sweeps of the solve: measured, us, by wavefronts, 64 and 16 rows a block.
