@@ -12,7 +12,9 @@ bool bin_layout(int W, int p, double b, double dt, const std::vector<double>& gl
   const int NQ = W + p / 2;
   const double delta = W * dt;
   B = BinLayout();
-  if (p > 8 || NQ > kMaxBinLags) return false;
+  // (a window of up to p / 2 steps has no room for an intermediate pair's stencil above
+  // lag 0; the sums pair by pair let it start there, at the upper end's clamp)
+  if (p > 8 || NQ > kMaxBinLags || W <= p / 2) return false;
   // bin width: 0.1 dt leaves the degree-7 polynomials of the default window
   // (b / W = 0.79) and p <= 8 within 1.4e-16 of the weights (p = 10 and 12 need
   // more terms); a steeper window takes narrower bins

@@ -78,6 +78,8 @@ static void check_look_up() {
   CHECK(fits >= 60, "%d layouts fit", fits);
   // limits: too many bins, too high an order
   BinLayout B;
+  CHECK(!layout(4, 8, 5e-3, 4, 1e-3, B) && !layout(1, 2, 0.3, 1, 1e-3, B) && layout(5, 8, 5e-3, 5, 1e-3, B),
+        "windows too short for the stencil");
   CHECK(!layout(37, 8, 1e-12, 37, 1e-3, B) && !layout(35, 8, 1e-12, 40, 1e-3, B) && !layout(35, 10, 1e-12, 35, 1e-3, B),
         "layouts beyond the limits");
   CHECK(layout(18, 8, 1e-6, 18, 1e-3, B) && B.ks == 13 && layout(36, 8, 1e-12, 36, 1e-3, B) && B.ks == 10, "steps");

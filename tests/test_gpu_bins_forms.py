@@ -118,6 +118,20 @@ def test_bins_equal_stored_weights(wfp, case):
     assert err < TOL
 
 
+@pytest.mark.parametrize("W,p", [(4, 8), (5, 8), (3, 6), (4, 6)])
+def test_shortest_windows(wfp, W, p):
+    """A window of p / 2 steps goes pair by pair, one step more by bins; both as with
+    the weights stored."""
+    kw = dict(p=p, W=W, eps_window=5e-3)
+    prob = _problem("slab", 6020, 1e-3, 500, W)
+    i, a = _local(wfp, prob, 1e-3, 2, **kw)
+    assert i["local_mode"] == 2 and i["local_bins"] == (1 if W > p // 2 else 0)
+    j, b = _local(wfp, prob, 1e-3, 3, **kw)
+    err = np.max(np.abs(a - b)) / np.max(np.abs(b))
+    print(f"W={W} p={p}: {err:.2e}", flush=True)
+    assert err < TOL
+
+
 @pytest.mark.parametrize("case", [CASES[3], CASES[7], CASES[10], CASES[13]], ids=_ids)
 def test_bins_gradient_equals_stored_weights(wfp, case):
     """Both gradients (the derivative sums take blocks of 16 sources and two
