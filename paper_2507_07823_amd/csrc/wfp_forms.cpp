@@ -99,7 +99,7 @@ double pairs_us(int W, int p, double springs, double neighbours) {
 }
 
 // The line lies where the two meet: at W = 35 by 112 neighbours for p = 8 from M =
-// 7e3 on (measured 115 at 2e4 and 1e5) and 190 at 2e3 (210), for p = 4 by 240 (225
+// 7e3 on (measured 115 at 2e4 and 1e5) and 200 at 2e3 (210), for p = 4 by 240 (225
 // to 242) and 360 (405), for p = 2 by 340 (335 to 357) and 510.  A gradient takes
 // two more sums by bins in a pass of twice the blocks, against one pass pair by
 // pair: there the lines lie 1.1 to 1.25 times as far out at M = 3e4 (136, 180, 273
@@ -125,12 +125,12 @@ double once_us(int W, int p, double springs, double neighbours) {
 // From 64 MB of weights on stored sums run beside the history chain, which then
 // costs no time of its own (25 us); but where the springs closer than dt are so many
 // (28) that the solve goes by global sweeps, the sweeps wait for compute units (25
-// us the other way).  A gradient runs on one stream.  Levels measured, stored over
+// us the other way).  Gradients and callers who ask for it run on one stream.  Levels measured, stored over
 // by bins, at W = 35 and p = 8: 0.80 at M = 3e3 and 914 neighbours, 1.25 at 1305; 0.81
 // at 5e3 and 544; 0.97 at 1e4 and 553, 1.25 at 880; 1.43 at 3e4 and 559; p = 4: 0.76 at
 // 1e4 and 553, 1.06 at 880; 1.18 at 3e4 and 559.
-bool bins_over_once(const BinLayout& B, int W, int p, double springs, double neighbours, double nearby, bool gradient) {
-  const bool beside = !gradient && 4.0 * springs * neighbours * (0.5 * W + p) >= 64.0 * 1024 * 1024;
+bool bins_over_once(const BinLayout& B, int W, int p, double springs, double neighbours, double nearby, bool one_stream) {
+  const bool beside = !one_stream && 4.0 * springs * neighbours * (0.5 * W + p) >= 64.0 * 1024 * 1024;
   const double chain = !beside ? 0.0 : (nearby >= 28.0 ? -25.0 : 25.0);
   return neighbours >= 512.0 && 1.02 * bins_us(B, springs, neighbours) + chain <= once_us(W, p, springs, neighbours);
 }

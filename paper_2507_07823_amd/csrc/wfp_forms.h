@@ -44,7 +44,7 @@ bool bins_over_pairs(const BinLayout& B, int W, int p, double springs, double ne
 // pair, and whether local_mode 0 takes bins in its place; `nearby`: springs closer
 // than dt on average.
 double once_us(int W, int p, double springs, double neighbours);
-bool bins_over_once(const BinLayout& B, int W, int p, double springs, double neighbours, double nearby, bool gradient);
+bool bins_over_once(const BinLayout& B, int W, int p, double springs, double neighbours, double nearby, bool one_stream);
 
 // The forms of a batch's instances that may go by bins: those whose mode is the
 // library's choice (stored once per pair otherwise) and those with weights on the

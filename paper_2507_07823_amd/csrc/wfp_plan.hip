@@ -699,7 +699,7 @@ void build(wfp_plan* P, const wfp_problem* prob, const wfp_params* par, OtfForm 
       const bool dense = (double)P->n_pairs >= kPairOnceNeighbours * (double)M;
       const double nearby = (double)std::accumulate(nc.begin(), nc.end(), (int64_t)0) / (double)M - 1.0;
       if (by_bins && P->NQ <= kMaxOtfGradLags &&
-          bins_over_once(bins, P->W, P->p, (double)M, mean, nearby, P->ckpt_every != 0))
+          bins_over_once(bins, P->W, P->p, (double)M, mean, nearby, P->ckpt_every != 0 || par->overlap_cus < 0))
         mode = 2;
       else if (fits3 && (dense || !fits1)) mode = 3;
       else if (fits1) mode = 1;
